@@ -101,13 +101,13 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void ce
     double *yv = reinterpret_cast<double *>(my + L.yv);
     double *M = reinterpret_cast<double *>(my + L.mat);
     const int64_t total = a.num;
-    const int64_t G = gridDim.x;
-    int64_t cur = blockIdx.x, nxt = blockIdx.x + G;
+    const QueuePlace queue(blockIdx.x, gridDim.x);
+    int64_t cur = blockIdx.x, nxt = queue.second(blockIdx.x);
     DFetch F;
     if (cur < total) dense_fetch(a, cur, F);
     while (cur < total) {
         int qv = 0;
-        if (lane == 0) qv = int(atomicInc(reinterpret_cast<unsigned *>(a.queue), 0xffffffffu));
+        if (lane == 0 && a.queue) qv = queue.pop(a.queue);
         const int64_t k = F.k;
         const int m = uniform(F.m), n = uniform(F.n), ldm = dense_ldm(m);
         const int64_t co = F.co;
@@ -458,9 +458,10 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void ce
         }
         dsync();
         cur = nxt;
-        nxt = 2 * G + lane_get(qv, 0);
+        nxt = queue.item(lane_get(qv, 0));
     }
-    if (lane == 0) finish_launch(a.queue, a.done, nullptr);
+    drain_memory();
+    if (lane == 0) finish_launch(a.queue, nullptr);
 }
 
 }  // namespace

@@ -126,7 +126,7 @@ __global__ __launch_bounds__(NT) void certify_kernel(CertArgs a)
     const int64_t total = a.num;
     int64_t item = blockIdx.x;
     while (item < total) {
-        if (tid == 0) sh->next = int(gridDim.x) + atomicAdd(a.queue, 1);
+        if (tid == 0) sh->next = int(gridDim.x) + (a.queue ? atomicAdd(a.queue, 1) : 0);
         const int64_t k = !a.order1 ? item : (item < a.n1 ? a.order1[item] : a.order2[item - a.n1]);
         int m, n;
         int64_t ao, ro, co;
@@ -608,7 +608,8 @@ __global__ __launch_bounds__(NT) void certify_kernel(CertArgs a)
         item = sh->next;
         __syncthreads();
     }
-    if (tid == 0) finish_launch(a.queue, a.done, nullptr);
+    drain_memory();
+    if (tid == 0) finish_launch(a.queue, nullptr);
 }
 
 
@@ -647,10 +648,11 @@ __global__ __launch_bounds__(64 * W) void certify_wave_kernel(CertArgs a)
     }
     char *my = smem + off + int64_t(wave) * a.wave_bytes;
     const int64_t total = a.num;
-    int64_t item = int64_t(blockIdx.x) * W + wave;
+    const QueuePlace queue(blockIdx.x * W + wave, gridDim.x * W);
+    int64_t item = int64_t(blockIdx.x) * W + wave, next = queue.second(int(item));
     while (item < total) {
-        int nxt = 0;
-        if (lane == 0) nxt = int(gridDim.x) * W + atomicAdd(a.queue, 1);
+        int qv = 0;
+        if (lane == 0 && a.queue) qv = queue.pop(a.queue);
         const int64_t k = item;
         int m, n;
         int64_t ao, ro, co;
@@ -1075,10 +1077,12 @@ __global__ __launch_bounds__(64 * W) void certify_wave_kernel(CertArgs a)
             }
         }
         wave_sync();
-        item = lane_get(nxt, 0);
+        item = next;
+        next = queue.item(lane_get(qv, 0));
     }
+    drain_memory();
     __syncthreads();
-    if (threadIdx.x == 0) finish_launch(a.queue, a.done, nullptr);
+    if (threadIdx.x == 0) finish_launch(a.queue, nullptr);
 }
 
 template <int NT>

@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "internal.h"
+
 namespace lpb {
 
 constexpr int kLE = 0, kGE = 1, kEQ = 2;
@@ -206,18 +208,50 @@ __device__ __forceinline__ void wave_argmin_dpp(T &k1, int &k2, int &p)
     p = lane_get(p, src);
 }
 
-// Called once per workgroup (one thread) when it leaves its work loop: the
-// last workgroup to finish returns the launch's counters to 0 for the next
-// launch on the stream.  Every queue atomic of a workgroup has returned
-// before it gets here (its result decides the loop exit).
-__device__ __forceinline__ void finish_launch(int32_t *queue, int32_t *done, int32_t *extra)
-{
-    const int fin = atomicAdd(done, 1);
-    if (fin == int(gridDim.x) - 1) {
-        atomicExch(queue, 0);
-        atomicExch(done, 0);
-        if (extra) atomicExch(extra, 0);
+// Worker b of `workers` in a launch's work queue: its first two items are b and
+// second(); later ones come from pop() (one lane) through item().
+struct QueuePlace {
+    int groups, g, members;
+    __device__ __forceinline__ QueuePlace(int b, int workers)
+    {
+        groups = min(kQueues, workers);
+        g = b % groups;
+        members = (workers - g + groups - 1) / groups;
     }
+    __device__ __forceinline__ int64_t second(int b) const { return b + int64_t(groups) * members; }
+    // The counter is read here and used when the current LP is done.  (An
+    // increment with wrap at 2^32 - 1 is a plain +1 here; unlike an add it is
+    // not rewritten into a wavefront-combined atomic whose result is broadcast,
+    // and waited for, right away.)
+    __device__ __forceinline__ int pop(int32_t *queue) const
+    {
+        return int(atomicInc(reinterpret_cast<unsigned *>(queue + kQueueLine * g), 0xffffffffu));
+    }
+    __device__ __forceinline__ int64_t item(int popped) const
+    {
+        return g + int64_t(groups) * (2 * int64_t(members) + popped);
+    }
+};
+
+// Waits until every memory access of this wavefront has returned, a queue
+// counter popped ahead and not needed any more among them.
+__device__ __forceinline__ void drain_memory() { __builtin_amdgcn_s_waitcnt(0); }
+
+// Called once per workgroup (one thread, after drain_memory in every wavefront)
+// when it leaves its work loop: the last workgroup to finish returns the
+// launch's counters to 0 for the next launch on the stream.
+__device__ __forceinline__ void finish_launch(int32_t *queue, int32_t *extra)
+{
+    if (!queue) return;
+    const int groups = min(kQueues, int(gridDim.x)), g = int(blockIdx.x) % groups;
+    const int members = (int(gridDim.x) - g + groups - 1) / groups;
+    if (atomicAdd(queue + kQueueLine * g + 1, 1) != members - 1) return;
+    if (atomicAdd(queue + kQueueLine * kQueues, 1) != groups - 1) return;
+    for (int q = 0; q <= kQueues; ++q) {
+        atomicExch(queue + kQueueLine * q, 0);
+        atomicExch(queue + kQueueLine * q + 1, 0);
+    }
+    if (extra) atomicExch(extra, 0);
 }
 
 __device__ __forceinline__ uint64_t lanemask_lt(int lane)

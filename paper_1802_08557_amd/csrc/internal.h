@@ -19,6 +19,17 @@ struct SolveParams {
     int32_t pricing;   // 0: Dantzig; 1: steepest edge (d_j^2 / (1 + |column j|^2))
 };
 
+// The work queue of one launch: kQueues counters, each in a cache line of its
+// own, and per counter the workgroups that have finished (all 0 between
+// launches).  Worker b of the launch pops from counter b % kQueues, which hands
+// out the items congruent to it.  Atomics on one address take 12 ns each on
+// MI355X whatever the kernel around them does, so a single counter held every
+// launch over small LPs to 12 ns per LP -- 1.2 ms per 1e5 -- plus 12 ns per
+// workgroup at its end.
+constexpr int kQueues = 16;
+constexpr int kQueueLine = 32;                              // int32 per line
+constexpr int kQueueInts = (kQueues + 1) * kQueueLine;      // the last line counts finished counters
+
 // Everything one launch of the simplex kernel needs.  Device pointers unless noted.
 struct SolveArgs {
     int64_t num;              // work items in this launch (upper bound if num_dev is set)
@@ -42,9 +53,9 @@ struct SolveArgs {
     int32_t *enter_out;       // optional [num_lps]: entering Bland index at UNBOUNDED
     char *scratch;            // HBM tableau slots, one per workgroup of the launch
     int64_t slot_bytes;
-    int32_t *queue;           // work counter (0 at launch)
-    int32_t *done;            // finished workgroups (0 at launch); the last one to finish
-                              // resets queue, done and reset_extra to 0 for the next launch
+    int32_t *queue;           // kQueueInts work counters (0 at launch); the last workgroup to
+                              // finish resets them and reset_extra to 0 for the next launch.
+                              // NULL: the grid has a worker for every item
     int32_t *reset_extra;     // optional
     int32_t *defer_ids;       // wavefront kernel: LPs it could not take are appended here,
     int32_t *defer_count;     //   from defer_ids[defer_base] on (the workgroup kernel
@@ -88,7 +99,7 @@ struct CertArgs {
     int32_t *viol;            // optional [num]: rows the basis's x violates (wavefront kernel)
     char *scratch;            // LU matrices too large for LDS, one slot per workgroup
     int64_t slot_bytes;
-    int32_t *queue, *done;
+    int32_t *queue;           // as in SolveArgs
     // Workgroup kernel, optional: work item t is LP order1[t] for t < n1, else
     // order2[t - n1] (largest LPs first, so the launch does not end on one);
     // NULL: item t is LP t.
@@ -197,11 +208,11 @@ hipError_t launch_ldexp(int64_t count, const double *in, const int32_t *e, int64
 // slack/surplus of row i -> n + i, the artificial of row i -> n + m + i.
 
 // Statically allocated device scratch of lp_batch_solve_noalloc (noalloc.hip):
-// 256 bytes of work counters, the deferred-LP list (kNoAllocMaxLps entries),
+// 8 KiB of work counters, the deferred-LP list (kNoAllocMaxLps entries),
 // then the workgroup kernel's tableau slots.
 constexpr int64_t kNoAllocBytes = int64_t(16) << 20;
 constexpr int64_t kNoAllocMaxLps = int64_t(1) << 20;
-constexpr int64_t kNoAllocIdsAt = 256;
+constexpr int64_t kNoAllocIdsAt = 8192;
 constexpr int64_t kNoAllocSlotsAt = kNoAllocIdsAt + 4 * kNoAllocMaxLps;
 // Device address of this device's copy (the current device's).
 hipError_t noalloc_scratch_address(void **ptr);

@@ -56,10 +56,17 @@ struct Plan {
 
 // Counters of one solve pass (wavefront kernel + workgroup kernel).
 struct PassCounters {
-    int32_t *wq, *wd;  // wavefront queue / finished
-    int32_t *bq, *bd;  // workgroup queue / finished
-    int32_t *defer;    // LPs deferred by the wavefront kernel
+    int32_t *wq;     // wavefront kernel's queue
+    int32_t *bq;     // workgroup kernel's queue
+    int32_t *defer;  // LPs deferred by the wavefront kernel
 };
+
+// Layout of the context's work counters (int32): three counts in cache lines
+// of their own, then the queues.
+constexpr int kDeferAt = 0, kFbDeferAt = 32, kFbCountAt = 64, kQueuesAt = 128, kCounterInts = 4096;
+static_assert(kQueuesAt + 5 * lpb::kQueueInts <= kCounterInts, "counter layout");
+static_assert(4 * (kQueuesAt + 2 * lpb::kQueueInts) <= lpb::kNoAllocIdsAt, "no-allocation counters");
+inline int32_t *queue_at(int32_t *cnt, int q) { return cnt + kQueuesAt + q * lpb::kQueueInts; }
 
 bool wave_fit(const lp_ctx *ctx, int64_t mk, int64_t nk, bool fp32, bool gather)
 {
@@ -105,8 +112,6 @@ int launch_wave(lp_ctx *ctx, bool fp32, const lpb::SolveArgs &a, PassCounters pc
     w.ids = ids;
     w.num_dev = list_count;
     w.id_base = 0;
-    w.queue = pc.wq;
-    w.done = pc.wd;
     w.reset_extra = const_cast<int32_t *>(list_count);  // nothing reads it after this launch
     w.defer_ids = defer_ids;
     w.defer_count = pc.defer;
@@ -125,6 +130,7 @@ int launch_wave(lp_ctx *ctx, bool fp32, const lpb::SolveArgs &a, PassCounters pc
                             : lpb::simplex_wave_blocks_per_cu(fp32, rb, pf, int(lds));
     if (per_cu < 1) return fail(LP_ERR_HIP, "occupancy query failed for the wavefront kernel");
     const int64_t grid = std::min<int64_t>(num, int64_t(per_cu) * ctx->num_cu);
+    w.queue = grid == num && !list_count ? nullptr : pc.wq;
     Timer t(ctx, timing, stream, name);
     if (warm) HIP_TRY(lpb::launch_simplex_wave_warm(rb, w, int(grid), stream));
     else HIP_TRY(lpb::launch_simplex_wave(fp32, rb, pf, w, int(grid), stream));
@@ -190,7 +196,6 @@ int queue_pass(lp_ctx *ctx, const Plan &P, lpb::SolveArgs a, const lp_options &o
         }
     }
     a.queue = pc.bq;
-    a.done = pc.bd;
     a.num = P.num;
     if (n_wave > 0) {
         a.ids = defer_ids;
@@ -267,7 +272,7 @@ struct BinLaunch {
 // count); item t is LP ids[t] (LP t when ids is NULL).
 int launch_block(lp_ctx *ctx, bool fp32, lpb::SolveArgs a, const BinLaunch &B, const int32_t *ids, int64_t num,
                  const int32_t *num_dev, int32_t id_base, int32_t *reset_extra, int64_t grid_cap, int32_t *q,
-                 int32_t *d, hipStream_t stream, bool timing, const char *name)
+                 hipStream_t stream, bool timing, const char *name)
 {
     const int64_t ts = fp32 ? 4 : 8;
     const int ncol_worst = B.n_max + B.m_max;
@@ -295,7 +300,6 @@ int launch_block(lp_ctx *ctx, bool fp32, lpb::SolveArgs a, const BinLaunch &B, c
         a.scratch = static_cast<char *>(ctx->scratch.p);
     }
     a.queue = q;
-    a.done = d;
     a.ids = ids;
     a.num = num;
     a.num_dev = num_dev;
@@ -312,7 +316,7 @@ int launch_block(lp_ctx *ctx, bool fp32, lpb::SolveArgs a, const BinLaunch &B, c
 // context's table.  Synchronous.  The sampled LPs' outputs are overwritten
 // by the real solve that follows.
 int autotune_bin(lp_ctx *ctx, bool fp32, const lpb::SolveArgs &a, BinLaunch B, int bin, const int32_t *d_sample,
-                 int64_t n_sample, int32_t *q, int32_t *d, hipStream_t stream)
+                 int64_t n_sample, int32_t *q, hipStream_t stream)
 {
     hipEvent_t e0 = lpb::take_event(ctx), e1 = lpb::take_event(ctx);
     if (!e0 || !e1) return fail(LP_ERR_HIP, "could not create timing events");
@@ -330,7 +334,7 @@ int autotune_bin(lp_ctx *ctx, bool fp32, const lpb::SolveArgs &a, BinLaunch B, i
                 T.force_hbm = hbm != 0;
                 T.placement = hbm ? LP_PLACE_HBM : LP_PLACE_LDS;  // LDS whenever the tableau fits
                 HIP_TRY(hipEventRecord(e0, stream));
-                int rc = launch_block(ctx, fp32, a, T, d_sample, n_sample, nullptr, 0, nullptr, 0, q, d, stream,
+                int rc = launch_block(ctx, fp32, a, T, d_sample, n_sample, nullptr, 0, nullptr, 0, q, stream,
                                       false, "");
                 if (rc != LP_OK) return rc;
                 HIP_TRY(hipEventRecord(e1, stream));
@@ -372,8 +376,7 @@ int queue_binned(lp_ctx *ctx, const Plan &P, const lpb::SolveArgs &a, const lp_o
         BinLaunch B;
         B.m_max = sp.m_max;
         B.n_max = sp.n_max;
-        int rc = autotune_bin(ctx, fp32, a, B, sp.bin, d_samples + sp.sample_offset, sp.sample_count, pc.bq, pc.bd,
-                              stream);
+        int rc = autotune_bin(ctx, fp32, a, B, sp.bin, d_samples + sp.sample_offset, sp.sample_count, pc.bq, stream);
         if (rc != LP_OK) return rc;
     }
     if (n_wave > 0) {
@@ -391,8 +394,8 @@ int queue_binned(lp_ctx *ctx, const Plan &P, const lpb::SolveArgs &a, const lp_o
         B.force_hbm = tuned && it->second.force_hbm != 0;
         B.placement = tuned ? (B.force_hbm ? LP_PLACE_HBM : LP_PLACE_LDS) : opts.placement;
         if (opts.placement == LP_PLACE_HBM) B.force_hbm = true;
-        int rc = launch_block(ctx, fp32, a, B, d_block + sp.offset, sp.count, nullptr, 0, nullptr, 0, pc.bq, pc.bd,
-                              stream, timing, bname);
+        int rc = launch_block(ctx, fp32, a, B, d_block + sp.offset, sp.count, nullptr, 0, nullptr, 0, pc.bq, stream,
+                              timing, bname);
         if (rc != LP_OK) return rc;
     }
     if (n_wave > 0) {
@@ -402,7 +405,7 @@ int queue_binned(lp_ctx *ctx, const Plan &P, const lpb::SolveArgs &a, const lp_o
         B.n_max = wn_max;
         B.nt = 64;
         int rc = launch_block(ctx, fp32, a, B, d_block + n_block, n_wave, pc.defer, 0, pc.defer, ctx->num_cu,
-                              pc.bq, pc.bd, stream, timing, bname);
+                              pc.bq, stream, timing, bname);
         if (rc != LP_OK) return rc;
     }
     return LP_OK;
@@ -559,8 +562,8 @@ int lp_ctx_create(lp_ctx **out, int device)
     // lp_batch_solve_noalloc, which then reports it.
     ctx->noalloc_err = int(lpb::noalloc_scratch_address(&ctx->noalloc));
     if (ctx->noalloc_err != hipSuccess) ctx->noalloc = nullptr;
-    int rc = ctx->counters.ensure(4096);
-    if (rc == LP_OK && (lpb::launch_zero_i32(static_cast<int32_t *>(ctx->counters.p), 1024, nullptr) != hipSuccess ||
+    int rc = ctx->counters.ensure(sizeof(int32_t) * kCounterInts);
+    if (rc == LP_OK && (lpb::launch_zero_i32(static_cast<int32_t *>(ctx->counters.p), kCounterInts, nullptr) != hipSuccess ||
                         hipStreamSynchronize(nullptr) != hipSuccess))
         rc = fail(LP_ERR_HIP, "lp_ctx_create: could not clear the work counters");
     if (rc != LP_OK) {
@@ -826,12 +829,12 @@ int lp_batch_solve_ex(lp_ctx *ctx, int64_t num_lps, const double *A, const doubl
     }
     // Work counters, each returned to 0 by the last workgroup of its launch.
     int32_t *cnt = static_cast<int32_t *>(ctx->counters.p);
-    PassCounters main_pc{cnt + 0, cnt + 1, cnt + 2, cnt + 3, cnt + 4};
-    PassCounters fb_pc{cnt + 16, cnt + 17, cnt + 18, cnt + 19, cnt + 20};
-    int32_t *cert_q = cnt + 8, *cert_d = cnt + 9, *fb_count = cnt + 10;
+    PassCounters main_pc{queue_at(cnt, 0), queue_at(cnt, 1), cnt + kDeferAt};
+    PassCounters fb_pc{queue_at(cnt, 2), queue_at(cnt, 3), cnt + kFbDeferAt};
+    int32_t *cert_q = queue_at(cnt, 4), *fb_count = cnt + kFbCountAt;
     const bool timing = (opts.flags & LP_FLAG_TIME_KERNELS) != 0;
     if (ctx->counters_dirty) {
-        HIP_TRY(lpb::launch_zero_i32(cnt, 1024, stream));
+        HIP_TRY(lpb::launch_zero_i32(cnt, kCounterInts, stream));
         ctx->counters_dirty = false;
     }
     ctx->counters_dirty = true;  // until every launch below has been queued
@@ -867,7 +870,7 @@ int lp_batch_solve_ex(lp_ctx *ctx, int64_t num_lps, const double *A, const doubl
         ca.fb_ids = d_fb_ids; ca.fb_count = fb_count;
         ca.viol = nullptr;
         bool viol_counted = false;
-        ca.queue = cert_q; ca.done = cert_d;
+        ca.queue = cert_q;
         const lpb::SolveParams p64 = fill_params(opts, false);
         ca.tol_feas = p64.tol_feas;
         ca.tol_opt = p64.tol_opt;
@@ -1044,8 +1047,8 @@ int lp_batch_solve_noalloc(lp_ctx *ctx, int64_t num_lps, const double *A, const 
     // launch returns its counters to zero when it ends).
     char *base = static_cast<char *>(ctx->noalloc);
     int32_t *cnt = reinterpret_cast<int32_t *>(base);
-    HIP_TRY(lpb::launch_zero_i32(cnt, 64, stream));
-    PassCounters pc{cnt + 0, cnt + 1, cnt + 2, cnt + 3, cnt + 4};
+    HIP_TRY(lpb::launch_zero_i32(cnt, int(lpb::kNoAllocIdsAt / 4), stream));
+    PassCounters pc{queue_at(cnt, 0), queue_at(cnt, 1), cnt + kDeferAt};
     int32_t *defer_ids = reinterpret_cast<int32_t *>(base + lpb::kNoAllocIdsAt);
     return queue_pass(ctx, P, a, opts, pc, nullptr, num_lps, m, n, 0, defer_ids, nullptr, nullptr, stream, false,
                       "", "", base + lpb::kNoAllocSlotsAt, lpb::kNoAllocBytes - lpb::kNoAllocSlotsAt);

@@ -940,7 +940,7 @@ __global__ __launch_bounds__(NT) void simplex_kernel(SolveArgs a)
     const int64_t total = a.num_dev ? int64_t(a.id_base) + *a.num_dev : a.num;
     int64_t item = blockIdx.x;
     while (item < total) {
-        if (tid == 0) sh->next = gridDim.x + atomicAdd(a.queue, 1);
+        if (tid == 0) sh->next = gridDim.x + (a.queue ? atomicAdd(a.queue, 1) : 0);
         const int64_t k = a.ids ? int64_t(a.ids[item]) : item;
         LP<T, NT> P;
         P.k = k;
@@ -1042,7 +1042,8 @@ __global__ __launch_bounds__(NT) void simplex_kernel(SolveArgs a)
         item = sh->next;
         __syncthreads();
     }
-    if (tid == 0) finish_launch(a.queue, a.done, a.reset_extra);
+    drain_memory();
+    if (tid == 0) finish_launch(a.queue, a.reset_extra);
 }
 
 __global__ void zero_i32_kernel(int32_t *p, int count)

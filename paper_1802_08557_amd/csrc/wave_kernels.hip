@@ -708,20 +708,15 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(PFD > 0 ? 2 
     int *rowid = reinterpret_cast<int *>(smem + align16(4 * 64 * RB));
     const int64_t aux = wave_aux_bytes(RB, a.shared && a.row_subset);
     const int64_t total = a.num_dev ? int64_t(a.id_base) + *a.num_dev : a.num;
-    // Work items: blockIdx.x and blockIdx.x + G first, then 2G + the queue
-    // counter; the next item is always known one LP ahead, so its data can be
-    // in flight while the current LP pivots.
-    const int64_t G = gridDim.x;
-    int64_t cur = blockIdx.x, nxt = blockIdx.x + G;
+    // The next work item is always known one LP ahead, so its data can be in
+    // flight while the current LP pivots.
+    const QueuePlace queue(blockIdx.x, gridDim.x);
+    int64_t cur = blockIdx.x, nxt = queue.second(blockIdx.x);
     Fetch<RB, PFD> F;
     if (cur < total) fetch<RB, PFD>(a, cur, F);
     while (cur < total) {
-        // The queue counter is read here and used only when this LP is done.
-        // (An increment with wrap at 2^32 - 1 is a plain +1 here; unlike an add
-        // it is not rewritten into a wavefront-combined atomic whose result is
-        // broadcast, and waited for, right away.)
         int qv = 0;
-        if (lane == 0) qv = int(atomicInc(reinterpret_cast<unsigned *>(a.queue), 0xffffffffu));
+        if (lane == 0 && a.queue) qv = queue.pop(a.queue);
         const int64_t k = F.k;
         WaveLP<T, RB> P;
         P.k = k;
@@ -894,7 +889,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(PFD > 0 ? 2 
         fetch<RB, PFD>(a, nxt < total ? nxt : cur, F);
         if (!fits) {
             cur = nxt;
-            nxt = 2 * G + lane_get(qv, 0);
+            nxt = queue.item(lane_get(qv, 0));
             continue;
         }
         const bool invalid = __ballot(bad) != 0;
@@ -1010,7 +1005,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(PFD > 0 ? 2 
                 a.defer_ids[slot] = int32_t(k);
             }
             cur = nxt;
-            nxt = 2 * G + lane_get(qv, 0);
+            nxt = queue.item(lane_get(qv, 0));
             continue;
         }
 
@@ -1068,9 +1063,10 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(PFD > 0 ? 2 
             }
         }
         cur = nxt;
-        nxt = 2 * G + lane_get(qv, 0);
+        nxt = queue.item(lane_get(qv, 0));
     }
-    if (lane == 0) finish_launch(a.queue, a.done, a.reset_extra);
+    drain_memory();
+    if (lane == 0) finish_launch(a.queue, a.reset_extra);
 }
 
 
