@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "internal.h"
 
 namespace lpb {
@@ -17,9 +19,24 @@ constexpr int kRowNeg = 1, kRowDead = 8, kRowPad = 16;
 constexpr int LP_CERT_PRIMAL_OK_BIT = 1, LP_CERT_DUAL_OK_BIT = 2, LP_CERT_RAY_OK_BIT = 4,
               LP_CERT_SINGULAR_BIT = 8, LP_CERT_INFEASIBLE_OK_BIT = 16;
 
+// f(std::integral_constant<int, B>) ... f(std::integral_constant<int, E - 1>):
+// a loop over register arrays whose indices are constants from the start.
+template <int B, int E, typename F>
+__device__ __forceinline__ void static_for(F &&f)
+{
+    if constexpr (B < E) {
+        f(std::integral_constant<int, B>());
+        static_for<B + 1, E>(f);
+    }
+}
+
 template <typename T> __device__ __forceinline__ T t_inf();
 template <> __device__ __forceinline__ float t_inf<float>() { return __builtin_inff(); }
 template <> __device__ __forceinline__ double t_inf<double>() { return __builtin_inf(); }
+
+// Lanes where v holds.  (__ballot takes an integer: the condition is first
+// turned into one and compared again, two more instructions.)
+__device__ __forceinline__ uint64_t ballot(bool v) { return __builtin_amdgcn_ballot_w64(v); }
 
 // Wavefront-uniform read of lane l's value (l must be wavefront-uniform).
 __device__ __forceinline__ int lane_get(int v, int l) { return __builtin_amdgcn_readlane(v, l); }
@@ -193,6 +210,82 @@ __device__ __forceinline__ T wave_max_f(T v)
     v = fmax(a, b);
     swap32_f(v, a, b);
     return fmax(a, b);
+}
+
+// Unsigned minimum / maximum over the wavefront (all 64 lanes active).
+__device__ __forceinline__ uint32_t wave_min_u(uint32_t v)
+{
+    v = min(v, uint32_t(dpp_i<0xB1>(int(v))));
+    v = min(v, uint32_t(dpp_i<0x4E>(int(v))));
+    v = min(v, uint32_t(dpp_i<0x141>(int(v))));
+    v = min(v, uint32_t(dpp_i<0x140>(int(v))));
+    Pair32 p = swap16(int(v));
+    v = min(uint32_t(p.a), uint32_t(p.b));
+    p = swap32(int(v));
+    return min(uint32_t(p.a), uint32_t(p.b));
+}
+__device__ __forceinline__ uint32_t wave_max_u(uint32_t v) { return ~wave_min_u(~v); }
+
+// Lanes among `on` that hold the least (largest) value, as a mask; every value
+// of an `on` lane is >= +0 and not NaN, so its bits order like an unsigned
+// integer's.  FP64 compares high words first and low words only where those
+// tie: one 32-bit reduction instead of a 64-bit one, whose every step is three
+// dependent instructions.
+__device__ __forceinline__ uint64_t wave_min_nonneg(bool on, float v)
+{
+    const uint32_t u = __float_as_uint(v);
+    const uint32_t best = wave_min_u(on ? u : 0xffffffffu);
+    return ballot(on && u == best);
+}
+__device__ __forceinline__ uint64_t wave_min_nonneg(bool on, double v)
+{
+    const uint32_t hi = uint32_t(__double2hiint(v)), lo = uint32_t(__double2loint(v));
+    const uint32_t best = wave_min_u(on ? hi : 0xffffffffu);
+    const uint64_t tied = ballot(on && hi == best);
+    if (__builtin_expect(__popcll(tied) <= 1, 1)) return tied;
+    const bool in = on && hi == best;
+    const uint32_t low = wave_min_u(in ? lo : 0xffffffffu);
+    return ballot(in && lo == low);
+}
+__device__ __forceinline__ uint64_t wave_max_nonneg(bool on, float v)
+{
+    const uint32_t u = __float_as_uint(v);
+    const uint32_t best = wave_max_u(on ? u : 0u);
+    return ballot(on && u == best);
+}
+__device__ __forceinline__ uint64_t wave_max_nonneg(bool on, double v)
+{
+    const uint32_t hi = uint32_t(__double2hiint(v)), lo = uint32_t(__double2loint(v));
+    const uint32_t best = wave_max_u(on ? hi : 0u);
+    const uint64_t tied = ballot(on && hi == best);
+    if (__builtin_expect(__popcll(tied) <= 1, 1)) return tied;
+    const bool in = on && hi == best;
+    const uint32_t low = wave_max_u(in ? lo : 0u);
+    return ballot(in && lo == low);
+}
+
+// The 16 x 16 x 4 matrix product of each tableau type.  Lane (q = lane / 16,
+// lane % 16) holds column lane % 16 of the tile and, in component v, row
+// mfma_row(q, v).
+template <typename T> struct Tile;
+template <> struct Tile<double> {
+    using V = double __attribute__((ext_vector_type(4)));
+    static __device__ __forceinline__ V mma(double a, double b, V c)
+    {
+        return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+    }
+};
+template <> struct Tile<float> {
+    using V = float __attribute__((ext_vector_type(4)));
+    static __device__ __forceinline__ V mma(float a, float b, V c)
+    {
+        return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+    }
+};
+template <typename T>
+__device__ __forceinline__ int mfma_row(int q, int v)
+{
+    return sizeof(T) == 8 ? q + 4 * v : 4 * q + v;
 }
 
 template <typename T>

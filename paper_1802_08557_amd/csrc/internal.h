@@ -239,7 +239,7 @@ int simplex_wave_warm_blocks_per_cu(int rb, int lds_bytes);
 int simplex_wave_blocks_per_cu(bool fp32, int rb, bool pf, int lds_bytes);
 int wave_prefetch_elems();
 int64_t wave_lds_aux_bytes(int rb, bool gather);
-// LDS bytes of a column-major wavefront tableau with m rows and `cols` columns.
+// LDS bytes of a wavefront tableau with m rows and `cols` columns.
 int64_t wave_tab_bytes(int m, int cols, bool fp32);
 hipError_t simplex_wave_configure(int max_lds);
 

@@ -7,15 +7,21 @@
 //   * lane i (+64 r) owns row i: its basic variable, sign/sense flags, its
 //     right-hand side b_i and its pivot-column entry pcol_i; the objective
 //     row's right-hand side (minus the objective value) is a uniform value;
-//   * the constraint columns live in LDS, column-major (lane j's column is
-//     contiguous) with a column stride of an odd number of 16-byte units.
+//   * the constraint rows live in LDS, row-major, so that a pivot's row is one
+//     contiguous read and its column one read per lane.
 // Step 1 is a wavefront DPP/permlane reduction over the lanes' reduced costs;
-// Step 2 reads the entering column (contiguous, one element per lane) and
-// reduces the ratios against the row-owned right-hand sides; Step 3 sweeps each
-// lane's column in 16-byte vectors, sixteen rows per group -- all reads, then
-// the fma, then all writes -- with the rows' pivot-column entries broadcast
-// from column e in LDS, updates the right-hand sides in the row owners'
-// registers, then rewrites the swapped column and the pivot row.
+// Step 2 reads the entering column and reduces the ratios against the
+// row-owned right-hand sides; Step 3 keeps the pivot's column and row vectors
+// in registers (see Window) and updates the objective row and the right-hand
+// sides there; the tableau is swept once per eight pivots, on the matrix cores.
+// What bounds it: the dependent chain of each pivot (reductions, a division
+// before and after the ratio test, three LDS round trips) at the occupancy the
+// tableaux leave -- two wavefronts per SIMD for 50 x 50 FP64, one for 120 x 40 --
+// and, for LPs of few pivots, the read of A from HBM (a 50 x 50 batch cut off
+// after one pivot runs at 5.2 TB/s).  Measured against one or two pivots per
+// sweep of a column-major tableau on the vector units (same work queue): 1e5
+// uniform 50 x 50 FP64 1137 -> 830 us, its FP32 solve 940 -> 690 us, 1e5 support
+// LPs of 120 x 40 FP64 12.80 -> 7.82 ms, screened FP32 2.13 -> 1.63 ms.
 // The arithmetic of every element (fma(-pcol_i, prow_j, t_ij), prow_j =
 // t_lj / PE, Phase I and Phase II objective rows summed in row order) is the
 // same as in the workgroup kernel, so both give bitwise-identical results.
@@ -31,17 +37,14 @@
 namespace lpb {
 namespace {
 
-// Column stride (in elements) of the column-major LDS tableau: the smallest
-// odd multiple of 16 bytes that holds m rows.  Lane j's column is contiguous,
-// so the row sweep moves 16 bytes per lane per access, and an odd number of
-// 16-byte units between neighbouring lanes' columns keeps those accesses free
-// of bank conflicts.
+// Row stride (in elements) of the row-major LDS tableau with `cols` columns: any
+// number that is not a multiple of four, so that the lanes reading one column
+// (one element per row) meet at most two to a bank; lanes reading one row are
+// consecutive.
 template <typename T>
-__host__ __device__ constexpr int col_stride(int m)
+__host__ __device__ constexpr int row_stride(int cols)
 {
-    constexpr int R = 16 / int(sizeof(T));
-    const int u = (m + R - 1) / R;
-    return R * (u | 1);
+    return cols & 3 ? cols : cols + 1;
 }
 
 // Uniform value of row i from a per-row register array (row i lives in lane i % 64
@@ -62,383 +65,480 @@ __device__ __forceinline__ V row_get(const V (&arr)[RB], int i)
 
 template <typename T, int RB>
 struct WaveLP {
-    int m, n, N, C, ldm, nart;
+    int m, n, N, C, ld, nart;
     int64_t k, ro, co;
     const double *A, *b, *c;
-    T *tab;  // column-major: element (i, j) at tab[j * ldm + i], columns 0 .. N-1
+    T *tab;  // row-major: element (i, j) at tab[i * ld + j], columns 0 .. N-1
     int rowf[RB], basis[RB];
     T pcol[RB];
     T rhs[RB];  // right-hand side of row lane + 64 r
     T z;        // right-hand side of the objective row (uniform)
+    int rowat[RB], colat;  // row lane + 64 r of tab, column lane (lanes past the last: the last one's)
     int nonb;   // this lane's column
     T d;        // this lane's objective-row entry
     int iters, it1, degp, cap;
+    bool keep;  // the tableau is read again when the current phase ends
 };
 
-// Rows of one 16-byte vector of this lane's column: v[r] = fma(-w[r], prow,
-// v[r]) with w the same rows of the pivot column.
-template <typename T, typename V>
-__device__ __forceinline__ void update_vec(V &v, const V &w, T prow)
+// Pivots that the tableau in LDS does not hold yet, oldest first in np / pr:
+//     t_ij = fma(np[last]_i, pr[last]_j, ... fma(np[0]_i, pr[0]_j, tab_ij) ...)
+// with np the negated pivot columns (row owners' registers) and pr the scaled
+// pivot rows (column owners' registers).  A pivot's own row and column, which
+// it replaces rather than updates, are written to tab at once, and the
+// window's entries of that row and column become 0, so every entry goes
+// through the same operations in the same order as with one sweep of the
+// tableau per pivot.
+//
+// Why a window: a pivot reads one column and one row of the tableau, and with
+// the window both cost a short chain of fmas on registers.  The sweep, which
+// touches every entry, comes once per window -- for a 50 x 50 LP of 9
+// pivots hardly at all -- and is then a low-rank update on the matrix cores,
+// whose FP64 and FP32 products accumulate as a chain of fmas in k order, bit
+// for bit what the separate sweeps would do.
+//
+// The window holds NG whole groups of four pivots and the group being filled.
+template <typename T, int RB>
+struct Group {
+    T np[4][RB];
+    T pr[4];
+};
+template <typename T, int RB, int NG>
+struct Window {
+    Group<T, RB> grp[NG + 1];  // the whole groups, oldest first, end at grp[NG - 1]; grp[NG] is being filled
+    int n;                     // whole groups
+};
+
+// Exchanges rows of sixteen lanes among four registers: on return x[r] holds,
+// in lanes 16 k .. 16 k + 15, what lanes 16 r .. 16 r + 15 of x[k] held.
+__device__ __forceinline__ void transpose_rows(int &x0, int &x1, int &x2, int &x3)
 {
-    constexpr int R = 16 / int(sizeof(T));
-#pragma unroll
-    for (int r = 0; r < R; ++r) v[r] = fma(-w[r], prow, v[r]);
+    auto a = __builtin_amdgcn_permlane32_swap(x0, x2, false, false);
+    auto b = __builtin_amdgcn_permlane32_swap(x1, x3, false, false);
+    auto c = __builtin_amdgcn_permlane16_swap(a[0], b[0], false, false);
+    auto d = __builtin_amdgcn_permlane16_swap(a[1], b[1], false, false);
+    x0 = int(c[0]); x1 = int(c[1]); x2 = int(d[0]); x3 = int(d[1]);
+}
+__device__ __forceinline__ void transpose_rows(float &x0, float &x1, float &x2, float &x3)
+{
+    int a = __float_as_int(x0), b = __float_as_int(x1), c = __float_as_int(x2), d = __float_as_int(x3);
+    transpose_rows(a, b, c, d);
+    x0 = __int_as_float(a); x1 = __int_as_float(b); x2 = __int_as_float(c); x3 = __int_as_float(d);
+}
+__device__ __forceinline__ void transpose_rows(double &x0, double &x1, double &x2, double &x3)
+{
+    int al = __double2loint(x0), bl = __double2loint(x1), cl = __double2loint(x2), dl = __double2loint(x3);
+    int ah = __double2hiint(x0), bh = __double2hiint(x1), ch = __double2hiint(x2), dh = __double2hiint(x3);
+    transpose_rows(al, bl, cl, dl);
+    transpose_rows(ah, bh, ch, dh);
+    x0 = __hiloint2double(ah, al); x1 = __hiloint2double(bh, bl);
+    x2 = __hiloint2double(ch, cl); x3 = __hiloint2double(dh, dl);
 }
 
-// Step 3, register part: the scaled pivot row (returned; lane j's entry
-// prow_j = t_lj / PE, 1 / PE in column e), the objective row and every
-// right-hand side updated in their owners' registers, and the index arrays
-// swapped.  P.pcol must hold the pivot column (0 for dead and padding rows).
-// rowv: lane j's entry t_lj of the pivot row in the current tableau.
-template <typename T, int RB>
-__device__ __forceinline__ T pivot_head(WaveLP<T, RB> &P, int l, int e, T rowv)
+// The sweep of a tableau of NCT column tiles (see flush).
+template <int NCT, typename T, int RB, int NG>
+__device__ __forceinline__ void flush_tiles(WaveLP<T, RB> &L, const Window<T, RB, NG> &Q, int count)
+{
+    const int m = L.m, ld = L.ld;
+    // (Opaque to the compiler, which otherwise keeps every tile's bounds in
+    // scalar registers across the pivots.)
+    int q = threadIdx.x >> 4, c16 = threadIdx.x & 15;
+    asm volatile("" : "+v"(q), "+v"(c16));
+    const bool in = 16 * (NCT - 1) + c16 < L.N;  // this lane's column of the last column tile exists
+    const int whole = m >> 4, tail = m & 15;
+    // This lane's elements of row tile rt: component v at at[v][16 * column tile].
+    // Rows past m - 1 read row m - 1 and are not written.
+    struct Ptr { T *p[4]; };
+    auto place = [&](int rt) {
+        Ptr at;
+        static_for<0, 4>([&](auto v) { at.p[v] = L.tab + min(16 * rt + mfma_row<T>(q, v), m - 1) * ld + c16; });
+        return at;
+    };
+    using Row = typename Tile<T>::V[NCT];
+    auto load = [&](const Ptr &at, Row &c) {
+        static_for<0, NCT>([&](auto ct) {
+            if (ct < NCT - 1 || in)
+                static_for<0, 4>([&](auto v) { c[ct][int(v)] = at.p[v][16 * ct]; });
+        });
+    };
+    // Operand A of a group from a(group).
+    auto update = [&](auto a, Row &c) {
+        static_for<0, NG + 1>([&](auto g) {
+            if (NG - g >= count) return;
+            const T ag = a(Q.grp[g]);
+            static_for<0, NCT>([&](auto ct) { c[ct] = Tile<T>::mma(ag, Q.grp[g].pr[ct], c[ct]); });
+        });
+    };
+    Ptr at = place(0);
+    Row c;
+    static_for<0, NCT>([&](auto ct) { c[ct] = {T(0), T(0), T(0), T(0)}; });
+    load(at, c);
+    // Whole row tiles, the next one's reads in flight during the products.
+    static_for<0, 4 * RB>([&](auto rt) {
+        if (rt >= whole) return;
+        const Ptr next = place(rt + 1);
+        Row cn;
+        static_for<0, NCT>([&](auto ct) { cn[ct] = {T(0), T(0), T(0), T(0)}; });
+        load(next, cn);
+        update([&](const Group<T, RB> &g) { return g.np[rt & 3][rt >> 2]; }, c);
+        static_for<0, NCT>([&](auto ct) {
+            if (ct < NCT - 1 || in)
+                static_for<0, 4>([&](auto v) { at.p[v][16 * ct] = c[ct][int(v)]; });
+        });
+        at = next;
+        static_for<0, NCT>([&](auto ct) { c[ct] = cn[ct]; });
+    });
+    if (tail) {
+        update([&](const Group<T, RB> &g) {
+            T x = g.np[0][0];
+            static_for<1, 4 * RB>([&](auto rt) {
+                const T y = g.np[rt & 3][rt >> 2];
+                x = rt == whole ? y : x;
+            });
+            return x;
+        }, c);
+        static_for<0, NCT>([&](auto ct) {
+            if (ct < NCT - 1 || in)
+                static_for<0, 4>([&](auto v) {
+                    if (mfma_row<T>(q, v) < tail) at.p[v][16 * ct] = c[ct][int(v)];
+                });
+        });
+    }
+}
+
+// The sweep: tab takes the window's pivots, the last `count` of its NG + 1
+// groups (slots past the last pivot hold 0).  16 x 16 tiles, one rank-4
+// matrix product per group: operand A holds row 16 rt + lane % 16 and operand
+// B column 16 ct + lane % 16 of the group's pivot lane / 16, which is what its
+// registers hold after exchanging their rows of sixteen lanes.  The window's
+// registers are used up.
+template <typename T, int RB, int NG>
+__device__ __forceinline__ void flush(WaveLP<T, RB> &L, Window<T, RB, NG> &Q, int count)
+{
+    static_for<0, NG + 1>([&](auto g) {
+        if (NG - g >= count) return;
+        static_for<0, RB>([&](auto r) {
+            transpose_rows(Q.grp[g].np[0][r], Q.grp[g].np[1][r], Q.grp[g].np[2][r], Q.grp[g].np[3][r]);
+        });
+        transpose_rows(Q.grp[g].pr[0], Q.grp[g].pr[1], Q.grp[g].pr[2], Q.grp[g].pr[3]);
+    });
+    const int nct = (L.N + 15) >> 4;
+    if (nct == 4) flush_tiles<4>(L, Q, count);
+    else if (nct == 3) flush_tiles<3>(L, Q, count);
+    else if (nct == 2) flush_tiles<2>(L, Q, count);
+    else flush_tiles<1>(L, Q, count);
+}
+
+// This lane's rows of column e of the current tableau, S pivots in the group
+// being filled (anything past row m - 1).
+template <int S, typename T, int RB, int NG>
+__device__ __forceinline__ void column(const WaveLP<T, RB> &L, const Window<T, RB, NG> &Q, int e, T (&a)[RB])
+{
+    static_for<0, RB>([&](auto r) {
+        a[r] = L.tab[L.rowat[r] + e];
+    });
+    static_for<0, NG + 1>([&](auto g) {
+        if (g < NG && NG - g > Q.n) return;
+        static_for<0, (g < NG ? 4 : S)>([&](auto k) {
+            const T s = lane_get(Q.grp[g].pr[k], e);
+            static_for<0, RB>([&](auto r) { a[r] = fma(Q.grp[g].np[k][r], s, a[r]); });
+        });
+    });
+}
+
+// This lane's column of row l of the current tableau, S pivots in the group
+// being filled (anything past column C - 1).
+template <int S, typename T, int RB, int NG>
+__device__ __forceinline__ T row(const WaveLP<T, RB> &L, const Window<T, RB, NG> &Q, int l)
+{
+    T v = L.tab[l * L.ld + L.colat];
+    // The block of rows that holds row l, chosen once for all pivots.
+    static_for<0, RB>([&](auto r) {
+        if (RB > 1 && (l >> 6) != r) return;
+        static_for<0, NG + 1>([&](auto g) {
+            if (g < NG && NG - g > Q.n) return;
+            static_for<0, (g < NG ? 4 : S)>([&](auto k) {
+                v = fma(lane_get(Q.grp[g].np[k][r], l & 63), Q.grp[g].pr[k], v);
+            });
+        });
+    });
+    return v;
+}
+
+// Step 3 for the pivot on (l, e) of the current tableau: it becomes slot S of
+// the group being filled.  L.pcol holds the pivot column (0 for dead and
+// padding rows), rowv lane j's entry of the pivot row, prow_rhs the scaled
+// right-hand side of row l.  The objective row and every right-hand side are
+// updated in their owners' registers, and the index arrays swapped.  S = 4:
+// the slot is `slot`, known at run time, and unused slots hold 0.
+template <int S, typename T, int RB, int NG>
+__device__ __forceinline__ void push(WaveLP<T, RB> &L, Window<T, RB, NG> &Q, int l, int e, T rowv, T prow_rhs,
+                                     int slot = S)
 {
     const int lane = threadIdx.x;
-    const int m = P.m, C = P.C;
-    const T pe = row_get<RB>(P.pcol, l);
-    T prow = T(0);
-    if (lane < C) prow = (lane == e) ? T(1) / pe : rowv / pe;
-    const T de = lane_get(P.d, e);
-    if (lane < C) P.d = fma(-de, prow, (lane == e) ? T(0) : P.d);
-    // Right-hand sides: the objective row's (uniform) and every row's, in the
-    // row owners' registers (dead and padding rows carry pcol 0 and stay).
-    const T prow_rhs = row_get<RB>(P.rhs, l) / pe;
-    P.z = fma(-de, prow_rhs, P.z);
+    const int m = L.m, C = L.C;
+    const T pe = row_get<RB>(L.pcol, l);
+    const bool at_e = lane == e;
+    const T prow = (at_e ? T(1) : rowv) / pe;  // 1 / PE in column e
+    const T de = lane_get(L.d, e);
+    L.d = fma(-de, prow, at_e ? T(0) : L.d);
+    L.z = fma(-de, prow_rhs, L.z);
+    const T pre = lane_get(prow, e);
+    T *tab = L.tab;
+    bool at_l[RB];
 #pragma unroll
     for (int r = 0; r < RB; ++r) {
         const int i = lane + 64 * r;
-        if (i < m) P.rhs[r] = (i == l) ? prow_rhs : fma(-P.pcol[r], prow_rhs, P.rhs[r]);
+        at_l[r] = i == l;
+        if (i < m) {
+            L.rhs[r] = at_l[r] ? prow_rhs : fma(-L.pcol[r], prow_rhs, L.rhs[r]);
+            tab[i * L.ld + e] = at_l[r] ? pre : fma(-L.pcol[r], pre, T(0));
+        }
     }
-    const int bl = row_get<RB>(P.basis, l);
-    const int ne = lane_get(P.nonb, e);
+    if (lane < C && !at_e) tab[l * L.ld + lane] = prow;
+    // Row l and column e now come from tab alone.
+    static_for<0, NG + 1>([&](auto g) {
+        if (g < NG && NG - g > Q.n) return;
+        static_for<0, (g < NG ? 4 : S)>([&](auto k) {
+            Q.grp[g].pr[k] = at_e ? T(0) : Q.grp[g].pr[k];
+            static_for<0, RB>([&](auto r) { Q.grp[g].np[k][r] = at_l[r] ? T(0) : Q.grp[g].np[k][r]; });
+        });
+    });
+    static_for<(S < 4 ? S : 0), (S < 4 ? S + 1 : 4)>([&](auto k) {
+        const bool mine = S < 4 || k == slot;
+        const T y = at_e ? T(0) : prow, y0 = Q.grp[NG].pr[k];
+        Q.grp[NG].pr[k] = mine ? y : y0;
+        static_for<0, RB>([&](auto r) {
+            const T w = at_l[r] ? T(0) : -L.pcol[r], w0 = Q.grp[NG].np[k][r];
+            Q.grp[NG].np[k][r] = mine ? w : w0;
+        });
+    });
+    const int bl = row_get<RB>(L.basis, l);
+    const int ne = lane_get(L.nonb, e);
 #pragma unroll
     for (int r = 0; r < RB; ++r)
-        if (lane + 64 * r == l) P.basis[r] = ne;
-    if (lane == e) P.nonb = bl;
-    return prow;
+        if (at_l[r]) L.basis[r] = ne;
+    if (at_e) L.nonb = bl;
 }
 
-// Step 3, LDS part: sweep this lane's column in 16-byte vectors, G vectors
-// (16 rows) per group.  The same rows of the pivot column are read from
-// column e by every lane (one broadcast address per load); lane e rewrites
-// column e in the same sweep, but only rows whose pivot-column values every
-// lane has already read, since a wavefront's LDS accesses complete in program
-// order.  The pivot row and the swapped column are rewritten afterwards;
-// padding rows past m take whatever values and are never read back.
-template <typename T, int RB>
-__device__ __forceinline__ void pivot_sweep(WaveLP<T, RB> &P, int l, int e, T prow)
+// Slots S .. 3 of the group being filled hold no pivot.
+template <int S, typename T, int RB>
+__device__ __forceinline__ void pad_group(Group<T, RB> &g)
 {
-    using V = T __attribute__((ext_vector_type(16 / sizeof(T))));
-    constexpr int R = 16 / int(sizeof(T));
-    constexpr int G = 16 / R;  // vectors per group of 16 rows
-    const int lane = threadIdx.x;
-    const int m = P.m, C = P.C, ldm = P.ldm;
-    T *tab = P.tab;
-    if (lane < C) {
-        V *col = reinterpret_cast<V *>(tab + lane * ldm);
-        const V *pc = reinterpret_cast<const V *>(tab + e * ldm);
-        const int nv = (m + R - 1) / R;
-        int k0 = 0;
-        for (; k0 + G <= nv; k0 += G) {
-            V v[G], w[G];
-#pragma unroll
-            for (int g = 0; g < G; ++g) {
-                v[g] = col[k0 + g];
-                w[g] = pc[k0 + g];
-            }
-#pragma unroll
-            for (int g = 0; g < G; ++g) update_vec<T, V>(v[g], w[g], prow);
-#pragma unroll
-            for (int g = 0; g < G; ++g) col[k0 + g] = v[g];
-        }
-        for (; k0 < nv; ++k0) {
-            V v = col[k0];
-            const V w = pc[k0];
-            update_vec<T, V>(v, w, prow);
-            col[k0] = v;
-        }
-    }
-    const T pre = lane_get(prow, e);  // 1 / PE
-#pragma unroll
-    for (int r = 0; r < RB; ++r) {
-        const int i = lane + 64 * r;
-        if (i < m) tab[e * ldm + i] = (i == l) ? pre : fma(-P.pcol[r], pre, T(0));
-    }
-    if (lane < C) tab[lane * ldm + l] = prow;
+    static_for<S, 4>([&](auto k) {
+        g.pr[k] = T(0);
+        static_for<0, RB>([&](auto r) { g.np[k][r] = T(0); });
+    });
 }
 
-template <typename T, int RB>
-__device__ __forceinline__ void pivot(WaveLP<T, RB> &P, int l, int e)
+// The group being filled becomes the window's newest whole group.
+template <typename T, int RB, int NG>
+__device__ __forceinline__ void keep_group(Window<T, RB, NG> &Q)
 {
-    const int lane = threadIdx.x;
-    const T rowv = (lane < P.C) ? P.tab[lane * P.ldm + l] : T(0);
-    const T prow = pivot_head<T, RB>(P, l, e, rowv);
-    pivot_sweep<T, RB>(P, l, e, prow);
+    static_for<0, NG>([&](auto g) {
+        static_for<0, 4>([&](auto k) {
+            Q.grp[g].pr[k] = Q.grp[g + 1].pr[k];
+            static_for<0, RB>([&](auto r) { Q.grp[g].np[k][r] = Q.grp[g + 1].np[k][r]; });
+        });
+    });
+    ++Q.n;
 }
 
-// Two consecutive pivots in one sweep of the columns: (l1, e1), whose row
-// vector is prow1 and column P.pcol1 (row owners), then (l2, e2) of the
-// tableau the first leaves, with row vector prow2 and column pcol2.  Both
-// pivots' register parts are done.  Every entry is read once, takes the
-// first pivot's update and then the second's, and is written once; the
-// second pivot column's entries t'_ie2 = fma(-t_ie1, prow1_e2, t_ie2) are
-// formed from both columns' broadcast reads exactly as the first sweep would
-// have written them.  Rows l1 and l2 and columns e1 and e2, which the two
-// pivots replace rather than update, are rewritten afterwards with the
-// values two separate pivots leave there, so the result is the same bit for
-// bit.
-template <typename T, int RB>
-__device__ __forceinline__ void pivot_sweep2(WaveLP<T, RB> &P, int l1, int e1, T prow1, const T (&pcol1)[RB],
-                                             int l2, int e2, T prow2)
-{
-    using V = T __attribute__((ext_vector_type(16 / sizeof(T))));
-    constexpr int R = 16 / int(sizeof(T));
-    constexpr int G = 8 / R;  // vectors per group of 8 rows
-    const int lane = threadIdx.x;
-    const int m = P.m, C = P.C, ldm = P.ldm;
-    T *tab = P.tab;
-    const T p1e2 = lane_get(prow1, e2);
-    if (lane < C) {
-        V *col = reinterpret_cast<V *>(tab + lane * ldm);
-        const V *pc1 = reinterpret_cast<const V *>(tab + e1 * ldm);
-        const V *pc2 = reinterpret_cast<const V *>(tab + e2 * ldm);
-        const int nv = (m + R - 1) / R;
-        int k0 = 0;
-        for (; k0 + G <= nv; k0 += G) {
-            V v[G], w1[G], w2[G];
-#pragma unroll
-            for (int g = 0; g < G; ++g) {
-                v[g] = col[k0 + g];
-                w1[g] = pc1[k0 + g];
-                w2[g] = pc2[k0 + g];
-            }
-#pragma unroll
-            for (int g = 0; g < G; ++g) {
-#pragma unroll
-                for (int q = 0; q < R; ++q) {
-                    const T f2 = fma(-w1[g][q], p1e2, w2[g][q]);
-                    v[g][q] = fma(-f2, prow2, fma(-w1[g][q], prow1, v[g][q]));
-                }
-            }
-#pragma unroll
-            for (int g = 0; g < G; ++g) col[k0 + g] = v[g];
-        }
-        for (; k0 < nv; ++k0) {
-            V v = col[k0];
-            const V w1 = pc1[k0], w2 = pc2[k0];
-#pragma unroll
-            for (int q = 0; q < R; ++q) {
-                const T f2 = fma(-w1[q], p1e2, w2[q]);
-                v[q] = fma(-f2, prow2, fma(-w1[q], prow1, v[q]));
-            }
-            col[k0] = v;
-        }
+// The pivots outside the simplex loop (drive-out, crash, dual simplex): a window
+// whose slots are filled one at a time, unused ones 0.
+template <typename T, int RB, int NG>
+struct Pending {
+    Window<T, RB, NG> Q;
+    int s;  // pivots in Q.grp[NG]
+    __device__ __forceinline__ void clear()
+    {
+        Q.n = 0;
+        s = 0;
+        pad_group<0>(Q.grp[NG]);
     }
-    // Columns e1 and e2 (row owners), then rows l1 and l2 (column owners).
-    const T pre1 = lane_get(prow1, e1), p2e1 = lane_get(prow2, e1), pre2 = lane_get(prow2, e2);
+    // Loads column e into the per-row pivot-column registers (0 for dropped rows).
+    __device__ __forceinline__ void load_pcol(WaveLP<T, RB> &L, int e)
+    {
+        T a[RB];
+        column<4>(L, Q, e, a);
 #pragma unroll
-    for (int r = 0; r < RB; ++r) {
-        const int i = lane + 64 * r;
-        if (i < m) {
-            const T c1 = (i == l1) ? pre1 : fma(-pcol1[r], pre1, T(0));
-            tab[e1 * ldm + i] = (i == l2) ? p2e1 : fma(-P.pcol[r], p2e1, c1);
-            tab[e2 * ldm + i] = (i == l2) ? pre2 : fma(-P.pcol[r], pre2, T(0));
-        }
+        for (int r = 0; r < RB; ++r) L.pcol[r] = (L.rowf[r] & (kRowDead | kRowPad)) ? T(0) : a[r];
     }
-    if (lane < C && lane != e1 && lane != e2) {
-        if (l1 != l2) tab[lane * ldm + l1] = fma(-row_get<RB>(P.pcol, l1), prow2, prow1);
-        tab[lane * ldm + l2] = prow2;
+    __device__ __forceinline__ T load_row(WaveLP<T, RB> &L, int l) { return row<4>(L, Q, l); }
+    // Pivot on (l, e) whose column is in L.pcol and whose row is rowv.
+    __device__ __forceinline__ void pivot(WaveLP<T, RB> &L, int l, int e, T rowv)
+    {
+        push<4>(L, Q, l, e, rowv, row_get<RB>(L.rhs, l) / row_get<RB>(L.pcol, l), s);
+        if (++s < 4 || Q.n == NG) return;
+        keep_group(Q);
+        s = 0;
+        pad_group<0>(Q.grp[NG]);
     }
-}
-
-// Loads column e into the per-row pivot-column registers (0 for dropped rows).
-template <typename T, int RB>
-__device__ __forceinline__ void load_pcol(WaveLP<T, RB> &P, int e)
-{
-    const int lane = threadIdx.x;
-#pragma unroll
-    for (int r = 0; r < RB; ++r) {
-        const int i = lane + 64 * r;
-        T a = T(0);
-        if (i < P.m) a = P.tab[e * P.ldm + i];
-        P.pcol[r] = (P.rowf[r] & (kRowDead | kRowPad)) ? T(0) : a;
+    __device__ __forceinline__ bool full() const { return s == 4; }
+    // Brings the tableau in LDS up to date.
+    __device__ __forceinline__ void sweep(WaveLP<T, RB> &L)
+    {
+        flush(L, Q, Q.n + 1);
+        clear();
     }
-}
+};
 
 // Step 1: the entering column (wavefront-uniform), or -1 when none is eligible.
-// Dantzig: the largest d_j, ties to the smallest Bland index; Bland: the
-// smallest eligible Bland index.
+// Dantzig: the largest d_j (positive where eligible, so its bits order like
+// an unsigned integer's), ties to the smallest Bland index; Bland: the smallest
+// eligible Bland index.
 template <typename T>
 __device__ __forceinline__ int price(bool elig, T d, int nonb, bool bland)
 {
-    const int lane = threadIdx.x;
-    const uint64_t any = __ballot(elig);
+    const uint64_t any = ballot(elig);
     if (!any) return -1;
+    uint64_t tied = any;
     if (!bland) {
-        const T best = wave_max_f(elig ? d : -t_inf<T>());
-        const uint64_t tied = __ballot(elig && d == best);
-        if (__popcll(tied) == 1) return __builtin_ctzll(tied);
-        const bool in = (tied >> lane) & 1;
-        const int bmin = wave_min_i(in ? nonb : kBig);
-        return __builtin_ctzll(__ballot(in && nonb == bmin));
+        tied = wave_max_nonneg(elig, d);
+        if (__builtin_expect(__popcll(tied) == 1, 1)) return __builtin_ctzll(tied);
     }
-    const int bmin = wave_min_i(elig ? nonb : kBig);
-    return __builtin_ctzll(__ballot(elig && nonb == bmin));
+    const bool in = (tied >> (threadIdx.x & 63)) & 1;
+    const int bmin = wave_min_i(in ? nonb : kBig);
+    return __builtin_ctzll(ballot(in && nonb == bmin));
 }
 
-// PAIR: look one pivot ahead and sweep two pivots at once when it finds one
-// (off in the repair instantiation, whose few pivots do not pay for the
-// registers).
-template <typename T, int RB, bool PAIR = true>
-__device__ __forceinline__ int simplex(WaveLP<T, RB> &P, T eps_opt, const SolveParams &prm, int *enter)
+// Step 1 by steepest edge: each eligible lane sums the squares of its own
+// column over the live rows (the tableau must be swept), one partial sum per
+// component of a 16-byte vector of rows (the workgroup kernel's order).
+template <typename T, int RB>
+__device__ __forceinline__ int price_steepest(const WaveLP<T, RB> &P, bool elig)
 {
     const int lane = threadIdx.x;
-    const int m = P.m, N = P.N, ldm = P.ldm, nm = P.n + P.m;
-    const T tol_piv = T(prm.tol_piv);
-    T *tab = P.tab;
-    int deg_run = 0;
-    for (;;) {
-        if (P.iters >= P.cap) return kIterLimit;
-        const bool bland = prm.k_deg > 0 && deg_run >= prm.k_deg;
-        // Step 1.
-        const bool elig = lane < N && P.d > eps_opt && P.nonb < nm;
-        int e;
-        if (prm.pricing == 1 && !bland) {
-            // Steepest edge: each eligible lane sums the squares of its own
-            // column over the live rows (contiguous in LDS).
-            const uint64_t dead0 = __ballot((P.rowf[0] & (kRowDead | kRowPad)) != 0);
-            const uint64_t dead1 = RB > 1 ? __ballot((P.rowf[RB - 1] & (kRowDead | kRowPad)) != 0) : 0;
-            // 16-byte vectors down the column (padding rows past m are
-            // masked like dead ones), one partial sum per vector component.
-            using V = T __attribute__((ext_vector_type(16 / sizeof(T))));
-            constexpr int R = 16 / int(sizeof(T));
-            T acc[R];
+    const uint64_t dead0 = ballot((P.rowf[0] & (kRowDead | kRowPad)) != 0);
+    const uint64_t dead1 = RB > 1 ? ballot((P.rowf[RB - 1] & (kRowDead | kRowPad)) != 0) : 0;
+    constexpr int R = 16 / int(sizeof(T));
+    T acc[R];
 #pragma unroll
-            for (int q = 0; q < R; ++q) acc[q] = T(0);
-            if (elig) {
-                const V *col = reinterpret_cast<const V *>(tab + lane * ldm);
+    for (int q = 0; q < R; ++q) acc[q] = T(0);
+    if (elig) {
 #pragma unroll 2
-                for (int i0 = 0; i0 < m; i0 += R) {
-                    const V t = col[i0 / R];
+        for (int i0 = 0; i0 < P.m; i0 += R) {
 #pragma unroll
-                    for (int q = 0; q < R; ++q) {
-                        const int i = i0 + q;
-                        const uint64_t dm = i < 64 ? dead0 : dead1;
-                        acc[q] = ((dm >> (i & 63)) & 1) ? acc[q] : fma(t[q], t[q], acc[q]);
-                    }
-                }
+            for (int q = 0; q < R; ++q) {
+                const int i = i0 + q;
+                const T t = i < P.m ? P.tab[i * P.ld + lane] : T(0);
+                const uint64_t dm = i < 64 ? dead0 : dead1;
+                acc[q] = ((dm >> (i & 63)) & 1) ? acc[q] : fma(t, t, acc[q]);
             }
-            T w = T(1);
+        }
+    }
+    T w = T(1);
 #pragma unroll
-            for (int q = 0; q < R; ++q) w += acc[q];
-            e = price<T>(elig, elig ? P.d * P.d / w : T(0), P.nonb, false);
+    for (int q = 0; q < R; ++q) w += acc[q];
+    const T key = elig ? P.d * P.d / w : T(0);
+    const uint64_t any = ballot(elig);
+    if (!any) return -1;
+    const T best = wave_max_f(elig ? key : -t_inf<T>());
+    const uint64_t tied = ballot(elig && key == best);
+    if (__popcll(tied) == 1) return __builtin_ctzll(tied);
+    const bool in = (tied >> lane) & 1;
+    const int bmin = wave_min_i(in ? P.nonb : kBig);
+    return __builtin_ctzll(ballot(in && P.nonb == bmin));
+}
+
+// One iteration with S pivots in the group being filled.  Returns -1 to go
+// on, else the status (the group then still holds S pivots).
+template <int S, typename T, int RB, int NG>
+__device__ __forceinline__ int step(WaveLP<T, RB> &P, Window<T, RB, NG> &Q, T eps_opt, const SolveParams &prm,
+                                    int &deg_run, int *enter)
+{
+    const int lane = threadIdx.x;
+    if (P.iters >= P.cap) return kIterLimit;
+    const bool bland = prm.k_deg > 0 && deg_run >= prm.k_deg;
+    // Step 1.
+    const bool elig = lane < P.N && P.d > eps_opt && P.nonb < P.n + P.m;
+    int e;
+    if (S == 0 && prm.pricing == 1 && !bland) e = price_steepest<T, RB>(P, elig);
+    else e = price<T>(elig, P.d, P.nonb, bland);
+    if (e < 0) return kOptimal;
+    // Step 2: each lane's best row (ties to the smaller basic index), then
+    // the wavefront minimum ratio, ties to the smallest basic index.
+    T a[RB];
+    column<S>(P, Q, e, a);
+    const T tol_piv = T(prm.tol_piv);
+    T th_loc = t_inf<T>();
+    int bb_loc = kBig, row_loc = -1;
+    bool cand = false;
+#pragma unroll
+    for (int r = 0; r < RB; ++r) {
+        const bool live = !(P.rowf[r] & (kRowDead | kRowPad));
+        P.pcol[r] = live ? a[r] : T(0);
+        // (The division runs on every lane: a branch around it costs more.)
+        T th = (P.rhs[r] > T(0) ? P.rhs[r] : T(0)) / a[r];
+        asm("" : "+v"(th));
+        const int bb = P.basis[r];
+        const bool ok = live && a[r] > tol_piv && th == th;
+        const bool take = ok && (r == 0 || !cand || th < th_loc || (th == th_loc && bb < bb_loc));
+        th_loc = take ? th : th_loc;
+        bb_loc = take ? bb : bb_loc;
+        row_loc = take ? int(threadIdx.x) + 64 * r : row_loc;
+        cand |= ok;
+    }
+    if (!ballot(cand)) { *enter = lane_get(P.nonb, e); return kUnbounded; }
+    const uint64_t tied = wave_min_nonneg(cand, th_loc);
+    int src;
+    if (__builtin_expect(__popcll(tied) == 1, 1)) {
+        src = __builtin_ctzll(tied);
+    } else {
+        const bool in = (tied >> lane) & 1;
+        const int bmin = wave_min_i(in ? bb_loc : kBig);
+        src = __builtin_ctzll(ballot(in && bb_loc == bmin));
+    }
+    const int l = RB == 1 ? src : lane_get(row_loc, src);
+    const T th = lane_get(th_loc, src);
+    if (th == T(0)) { ++deg_run; ++P.degp; } else deg_run = 0;
+    const T rowv = row<S>(P, Q, l);
+    // The scaled right-hand side of row l is the ratio itself where it is positive.
+    const T bl = row_get<RB>(P.rhs, l);
+    T prow_rhs = th;
+    if (!(bl > T(0))) prow_rhs = bl / row_get<RB>(P.pcol, l);
+    push<S>(P, Q, l, e, rowv, prow_rhs);
+    ++P.iters;
+    return -1;
+}
+
+// Steps S .. 3 of a group.  Returns -1 to go on with the next group, else the
+// status; the group's unused slots then hold 0.
+template <int S, typename T, int RB, int NG>
+__device__ __forceinline__ int run_group(WaveLP<T, RB> &P, Window<T, RB, NG> &Q, T eps_opt, const SolveParams &prm,
+                                         int &deg_run, int *enter)
+{
+    if constexpr (S < 4) {
+        const int r = step<S>(P, Q, eps_opt, prm, deg_run, enter);
+        if (r >= 0) {
+            pad_group<S>(Q.grp[NG]);
+            return r;
+        }
+        // Steepest edge reads every column: a sweep after every pivot.
+        if (S == 0 && prm.pricing == 1) {
+            pad_group<1>(Q.grp[NG]);
+            return -1;
+        }
+        return run_group<S + 1>(P, Q, eps_opt, prm, deg_run, enter);
+    }
+    return -1;
+}
+
+template <typename T, int RB, int NG>
+__device__ __forceinline__ int simplex(WaveLP<T, RB> &P, T eps_opt, const SolveParams &prm, int *enter)
+{
+    int deg_run = 0;
+    Window<T, RB, NG> Q;
+    Q.n = 0;
+    for (;;) {
+        const int r = run_group<0>(P, Q, eps_opt, prm, deg_run, enter);
+        if (r >= 0 && !P.keep) return r;
+        if (r >= 0 || Q.n == NG || prm.pricing == 1) {
+            flush(P, Q, Q.n + 1);
+            Q.n = 0;
+            if (r >= 0) return r;
         } else {
-            e = price<T>(elig, P.d, P.nonb, bland);
+            keep_group(Q);
         }
-        if (e < 0) return kOptimal;
-        // Step 2: each lane's best row (ties to the smaller basic index), then
-        // the wavefront minimum ratio, ties to the smallest basic index.
-        T th_loc = t_inf<T>();
-        int bb_loc = kBig, row_loc = -1;
-#pragma unroll
-        for (int r = 0; r < RB; ++r) {
-            const int i = lane + 64 * r;
-            const bool live = !(P.rowf[r] & (kRowDead | kRowPad));
-            T a = T(0), bi = T(0);
-            if (i < m) { a = tab[e * ldm + i]; bi = P.rhs[r]; }
-            P.pcol[r] = live ? a : T(0);
-            if (live && a > tol_piv) {
-                const T th = (bi > T(0) ? bi : T(0)) / a;
-                const int bb = P.basis[r];
-                if (th < th_loc || (th == th_loc && bb < bb_loc)) { th_loc = th; bb_loc = bb; row_loc = i; }
-            }
-        }
-        if (!__ballot(row_loc >= 0)) { *enter = lane_get(P.nonb, e); return kUnbounded; }
-        const T best = wave_min_f(th_loc);
-        const uint64_t tied = __ballot(row_loc >= 0 && th_loc == best);
-        int src;
-        if (__popcll(tied) == 1) {
-            src = __builtin_ctzll(tied);
-        } else {
-            const bool in = (tied >> lane) & 1;
-            const int bmin = wave_min_i(in ? bb_loc : kBig);
-            src = __builtin_ctzll(__ballot(in && bb_loc == bmin));
-        }
-        const int l = lane_get(row_loc, src);
-        if (lane_get(th_loc, src) == T(0)) { ++deg_run; ++P.degp; } else deg_run = 0;
-        if (!PAIR || prm.pricing == 1 || P.iters + 1 >= P.cap) {
-            pivot<T, RB>(P, l, e);
-            ++P.iters;
-            continue;
-        }
-        // Look one pivot ahead: this pivot's register part (objective row,
-        // right-hand sides, indices) is all Steps 1 and 2 of the next
-        // iteration need, with the one column they read formed from its
-        // stored entries and this pivot's vectors.  When they find a second
-        // pivot both go through one sweep of the columns (pivot_sweep2).
-        T pcol1[RB];
-#pragma unroll
-        for (int r = 0; r < RB; ++r) pcol1[r] = P.pcol[r];
-        const T prow1 = pivot_head<T, RB>(P, l, e, (lane < P.C) ? tab[lane * ldm + l] : T(0));
-        const bool bland2 = prm.k_deg > 0 && deg_run >= prm.k_deg;
-        // Column e now holds the variable that left; its reduced cost -d_e / PE
-        // is negative, so e2 != e.
-        const int e2 = price<T>(lane < N && P.d > eps_opt && P.nonb < nm, P.d, P.nonb, bland2);
-        int l2 = -1;
-        T th2 = T(0);
-        if (e2 >= 0) {
-            const T p1e2 = lane_get(prow1, e2);
-            T th_loc2 = t_inf<T>();
-            int bb_loc2 = kBig, row_loc2 = -1;
-#pragma unroll
-            for (int r = 0; r < RB; ++r) {
-                const int i = lane + 64 * r;
-                const bool live = !(P.rowf[r] & (kRowDead | kRowPad));
-                T a = T(0), bi = T(0);
-                if (i < m) {
-                    a = (i == l) ? p1e2 : fma(-pcol1[r], p1e2, tab[e2 * ldm + i]);
-                    bi = P.rhs[r];
-                }
-                P.pcol[r] = live ? a : T(0);
-                if (live && a > tol_piv) {
-                    const T th = (bi > T(0) ? bi : T(0)) / a;
-                    const int bb = P.basis[r];
-                    if (th < th_loc2 || (th == th_loc2 && bb < bb_loc2)) { th_loc2 = th; bb_loc2 = bb; row_loc2 = i; }
-                }
-            }
-            if (__ballot(row_loc2 >= 0)) {
-                const T best2 = wave_min_f(th_loc2);
-                const uint64_t tied2 = __ballot(row_loc2 >= 0 && th_loc2 == best2);
-                int src2;
-                if (__popcll(tied2) == 1) {
-                    src2 = __builtin_ctzll(tied2);
-                } else {
-                    const bool in = (tied2 >> lane) & 1;
-                    const int bmin = wave_min_i(in ? bb_loc2 : kBig);
-                    src2 = __builtin_ctzll(__ballot(in && bb_loc2 == bmin));
-                }
-                l2 = lane_get(row_loc2, src2);
-                th2 = lane_get(th_loc2, src2);
-            }
-        }
-        if (l2 < 0) {
-            // Optimal or unbounded after this pivot: it goes alone, and the
-            // next iteration reaches the same outcome.
-#pragma unroll
-            for (int r = 0; r < RB; ++r) P.pcol[r] = pcol1[r];
-            pivot_sweep<T, RB>(P, l, e, prow1);
-            ++P.iters;
-            continue;
-        }
-        if (th2 == T(0)) { ++deg_run; ++P.degp; } else deg_run = 0;
-        // Lane j's entry of row l2 in the tableau the first pivot leaves.
-        T row2 = T(0);
-        if (lane < P.C)
-            row2 = (l2 == l) ? prow1
-                             : fma(-row_get<RB>(pcol1, l2), prow1, (lane == e) ? T(0) : tab[lane * ldm + l2]);
-        const T prow2 = pivot_head<T, RB>(P, l2, e2, row2);
-        pivot_sweep2<T, RB>(P, l, e, prow1, pcol1, l2, e2, prow2);
-        P.iters += 2;
     }
 }
 
@@ -454,11 +554,11 @@ __device__ __forceinline__ int simplex(WaveLP<T, RB> &P, T eps_opt, const SolveP
 // is the start basis plus the slacks of any omitted rows.  Returns false when
 // a pivot entry falls below tol_piv or the start basis is not square on its
 // tight rows.
-template <typename T, int RB>
-__device__ bool crash(WaveLP<T, RB> &P, const SolveArgs &a, int64_t k)
+template <typename T, int RB, int NG>
+__device__ __forceinline__ bool crash(WaveLP<T, RB> &P, Pending<T, RB, NG> &W, const SolveArgs &a, int64_t k)
 {
     const int lane = threadIdx.x;
-    const int n = P.n, m = P.m, ldm = P.ldm;
+    const int n = P.n, m = P.m;
     const int wm = a.warm_rows ? a.warm_m : m;
     const int32_t *wb = a.warm_rows ? a.warm_basis + k * int64_t(wm) : a.warm_basis + P.ro;
     const int32_t *wr = a.warm_rows ? a.warm_rows + k * int64_t(wm) : nullptr;
@@ -476,10 +576,10 @@ __device__ bool crash(WaveLP<T, RB> &P, const SolveArgs &a, int64_t k)
             v = wb[r];
             if (v >= n && v < n + wm) qs = wr ? wr[v - n] : v - n;  // the row of a basic slack
         }
-        nstruct += __popcll(__ballot(r < wm && v >= 0 && v < n));
+        nstruct += __popcll(ballot(r < wm && v >= 0 && v < n));
         for (int pass = 0; pass < 2; ++pass) {
             const int qq = pass == 0 ? q : qs;
-            uint64_t bits = __ballot(qq >= 0 && qq < m);
+            uint64_t bits = ballot(qq >= 0 && qq < m);
             while (bits) {
                 const int src = __builtin_ctzll(bits);
                 bits &= bits - 1;
@@ -497,39 +597,43 @@ __device__ bool crash(WaveLP<T, RB> &P, const SolveArgs &a, int64_t k)
 #pragma unroll
     for (int r = 0; r < RB; ++r) ntight += __popcll(cand[r]);
     if (ntight != nstruct) return false;
-    for (int r0 = 0; r0 < wm; r0 += 64) {
-        const int r = r0 + lane;
-        const int v = r < wm ? wb[r] : -1;
-        uint64_t bits = __ballot(r < wm && v >= 0 && v < n);
-        while (bits) {
-            const int src = __builtin_ctzll(bits);
-            bits &= bits - 1;
-            const int j = lane_get(v, src);
-            const uint64_t at = __ballot(P.nonb == j);
-            if (!at) return false;  // listed twice
-            const int c = __builtin_ctzll(at);
-            T best = T(-1);
-            int rl = -1;
-#pragma unroll
-            for (int rb = 0; rb < RB; ++rb) {
-                const int i = lane + 64 * rb;
-                if (i < m && ((cand[rb] >> lane) & 1)) {
-                    const T t = fabs(P.tab[c * ldm + i]);
-                    if (t > best) { best = t; rl = i; }
-                }
-            }
-            const T bmax = wave_max_f(best);
-            if (!(bmax > tol_piv)) return false;
-            const int l = lane_get(rl, __builtin_ctzll(__ballot(rl >= 0 && best == bmax)));
-#pragma unroll
-            for (int rb = 0; rb < RB; ++rb)
-                if ((l >> 6) == rb) cand[rb] &= ~(uint64_t(1) << (l & 63));
-            load_pcol<T, RB>(P, c);
-            pivot<T, RB>(P, l, c);
-            ++P.iters;
+    int r0 = -64, v = -1;
+    uint64_t bits = 0;
+    for (;;) {
+        // The next basic structural, in row order.
+        while (!bits && r0 + 64 < wm) {
+            r0 += 64;
+            v = r0 + lane < wm ? wb[r0 + lane] : -1;
+            bits = ballot(v >= 0 && v < n);
         }
+        if (!bits || W.full()) W.sweep(P);
+        if (!bits) return true;
+        const int src = __builtin_ctzll(bits);
+        bits &= bits - 1;
+        const int j = lane_get(v, src);
+        const uint64_t at = ballot(P.nonb == j);
+        if (!at) return false;  // listed twice
+        const int c = __builtin_ctzll(at);
+        W.load_pcol(P, c);
+        T best = T(-1);
+        int rl = -1;
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) {
+            const int i = lane + 64 * rb;
+            if (i < m && ((cand[rb] >> lane) & 1)) {
+                const T t = fabs(P.pcol[rb]);
+                if (t > best) { best = t; rl = i; }
+            }
+        }
+        const T bmax = wave_max_f(best);
+        if (!(bmax > tol_piv)) return false;
+        const int l = lane_get(rl, __builtin_ctzll(ballot(rl >= 0 && best == bmax)));
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb)
+            if ((l >> 6) == rb) cand[rb] &= ~(uint64_t(1) << (l & 63));
+        W.pivot(P, l, c, W.load_row(P, l));
+        ++P.iters;
     }
-    return true;
 }
 
 // Repair of a start basis from a single-precision solve (the final basis of
@@ -541,22 +645,24 @@ __device__ bool crash(WaveLP<T, RB> &P, const SolveArgs &a, int64_t k)
 // basic Bland index), the entering column the smallest min(d_j, 0) / t_lj over
 // t_lj < -tol_piv (ties to the smallest Bland index) -- and the primal method
 // then removes any d_j > eps_opt left.  A start that is primal feasible but
-// not dual feasible goes straight to the primal method.  Returns the status,
-// or -1 when the start is neither (the caller then solves from the slack
-// basis).
-template <typename T, int RB>
-__device__ int dual_repair(WaveLP<T, RB> &P, T eps_opt, T tol_dual, T tol_p, const SolveParams &prm, int *enter)
+// not dual feasible goes straight to the primal method.  Returns kPrimal for
+// the caller to go on with the primal method, the status when the repair ends
+// otherwise, or -1 when the start is neither (the caller then solves from the
+// slack basis).
+constexpr int kPrimal = -2;
+template <typename T, int RB, int NG>
+__device__ __forceinline__ int dual_repair(WaveLP<T, RB> &P, Pending<T, RB, NG> &W, T tol_dual, T tol_p, const SolveParams &prm)
 {
     const int lane = threadIdx.x;
-    const int m = P.m, N = P.N, ldm = P.ldm, nm = P.n + P.m;
+    const int m = P.m, N = P.N, nm = P.n + P.m;
     const T tol_piv = T(prm.tol_piv);
-    if (__ballot(lane < N && P.d > tol_dual && P.nonb < nm)) {
+    if (ballot(lane < N && P.d > tol_dual && P.nonb < nm)) {
         bool infeas = false;
 #pragma unroll
         for (int r = 0; r < RB; ++r)
             infeas |= lane + 64 * r < m && !(P.rowf[r] & (kRowDead | kRowPad)) && P.rhs[r] < -tol_p;
-        if (__ballot(infeas)) return -1;
-        return simplex<T, RB, false>(P, eps_opt, prm, enter);
+        if (ballot(infeas)) return -1;
+        return kPrimal;
     }
     for (;;) {
         if (P.iters >= P.cap) return kIterLimit;
@@ -571,34 +677,34 @@ __device__ int dual_repair(WaveLP<T, RB> &P, T eps_opt, T tol_dual, T tol_p, con
                 vl = v; bl = P.basis[r]; rl = i;
             }
         }
-        if (!__ballot(rl >= 0)) break;  // primal feasible
+        const bool feasible = !ballot(rl >= 0);
+        if (feasible || W.full()) W.sweep(P);
+        if (feasible) return kPrimal;
         const T vmin = wave_min_f(vl);
-        const uint64_t tied = __ballot(rl >= 0 && vl == vmin);
+        const uint64_t tied = ballot(rl >= 0 && vl == vmin);
         int src = __builtin_ctzll(tied);
         if (__popcll(tied) > 1) {
             const bool in = (tied >> lane) & 1;
             const int bmin = wave_min_i(in ? bl : kBig);
-            src = __builtin_ctzll(__ballot(in && bl == bmin));
+            src = __builtin_ctzll(ballot(in && bl == bmin));
         }
         const int l = lane_get(rl, src);
-        T tlj = T(0);
-        if (lane < N) tlj = P.tab[lane * ldm + l];
+        const T tlj = W.load_row(P, l);
         const bool el = lane < N && P.nonb < nm && tlj < -tol_piv;
-        if (!__ballot(el)) return kInfeasible;  // row l cannot reach its bound
+        if (!ballot(el)) return kInfeasible;  // row l cannot reach its bound
         const T ratio = el ? (P.d < T(0) ? P.d : T(0)) / tlj : t_inf<T>();
         const T rmin = wave_min_f(ratio);
-        const uint64_t rt = __ballot(el && ratio == rmin);
+        const uint64_t rt = ballot(el && ratio == rmin);
         int e = __builtin_ctzll(rt);
         if (__popcll(rt) > 1) {
             const bool in = (rt >> lane) & 1;
             const int bmin = wave_min_i(in ? P.nonb : kBig);
-            e = __builtin_ctzll(__ballot(in && P.nonb == bmin));
+            e = __builtin_ctzll(ballot(in && P.nonb == bmin));
         }
-        load_pcol<T, RB>(P, e);
-        pivot<T, RB>(P, l, e);
+        W.load_pcol(P, e);
+        W.pivot(P, l, e, tlj);
         ++P.iters;
     }
-    return simplex<T, RB, false>(P, eps_opt, prm, enter);
 }
 
 // Bytes of LDS the wave kernel keeps in front of the tableau: the surplus
@@ -616,6 +722,16 @@ __host__ __device__ constexpr int64_t wave_aux_bytes(int rb, bool gather)
 // larger (or row-gathered) LPs use the instantiation without the prefetch
 // registers, which leaves room for more wavefronts per SIMD.
 constexpr int NPF = 40;
+
+// The launch's arguments, read again from the kernel's argument segment where
+// they are used: held in scalar registers from the start they spill.
+typedef const __attribute__((address_space(4))) SolveArgs *LateArgs;
+__device__ __forceinline__ LateArgs late_args()
+{
+    LateArgs p = (LateArgs)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    return p;
+}
 
 // An LP's geometry and input data, loaded into registers ahead of its solve.
 template <int RB, int PFD>
@@ -638,8 +754,9 @@ struct Fetch {
 // range check returns 0 past the LP's end, so no branch separates the loads and
 // nothing waits for them before their first use in the next LP's setup.
 template <int RB, int PFD>
-__device__ __forceinline__ void fetch(const SolveArgs &a, int64_t item, Fetch<RB, PFD> &F)
+__device__ __forceinline__ void fetch(int64_t item, Fetch<RB, PFD> &F)
 {
+    const auto &a = *late_args();
     const int lane = threadIdx.x;
     const int64_t k = a.ids ? int64_t(uniform(a.ids[item])) : item;
     F.k = k;
@@ -699,10 +816,18 @@ __device__ __forceinline__ void fetch(const SolveArgs &a, int64_t item, Fetch<RB
     }
 }
 
+// Whole groups of four pivots that a window holds besides the one being filled:
+// eight pivots per sweep.  Twelve and sixteen were slower, the longer chains
+// and the registers costing more than the sweeps they save (1e5 support LPs of
+// 120 x 40 FP64 7.95 / 8.14 / 8.70 ms; 1e5 screened FP32 1.57 / 1.72 / 1.95 ms;
+// 1e5 uniform 50 x 50 FP64 0.83 / 0.83 / 1.00 ms).
+constexpr int kGroups = 1;
+
 template <typename T, int RB, int PFD, bool WARM = false>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(PFD > 0 ? 2 : (sizeof(T) == 4 ? (RB == 1 ? 5 : 4) : 3)))) void simplex_wave_kernel(SolveArgs a)
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(PFD > 0 ? 2 : (sizeof(T) == 4 ? (RB == 1 ? 5 : 4) : (RB == 2 ? 2 : 3))))) void simplex_wave_kernel(SolveArgs a)
 {
     extern __shared__ __align__(16) char smem[];
+    constexpr int NG = kGroups;
     const int lane = threadIdx.x;
     int *colrow = reinterpret_cast<int *>(smem);
     int *rowid = reinterpret_cast<int *>(smem + align16(4 * 64 * RB));
@@ -713,7 +838,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(PFD > 0 ? 2 
     const QueuePlace queue(blockIdx.x, gridDim.x);
     int64_t cur = blockIdx.x, nxt = queue.second(blockIdx.x);
     Fetch<RB, PFD> F;
-    if (cur < total) fetch<RB, PFD>(a, cur, F);
+    if (cur < total) fetch<RB, PFD>(cur, F);
     while (cur < total) {
         int qv = 0;
         if (lane == 0 && a.queue) qv = queue.pop(a.queue);
@@ -754,9 +879,9 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(PFD > 0 ? 2 
             P.rowf[r] = f;
             P.rhs[r] = (i < m) ? T((f & kRowNeg) ? -bi : bi) : T(0);
             const int sen = (f >> 1) & 3;
-            const uint64_t ge = __ballot(i < m && sen == kGE);
-            const uint64_t ar = __ballot(i < m && sen != kLE);
-            const uint64_t eq = __ballot(i < m && sen == kEQ);
+            const uint64_t ge = ballot(i < m && sen == kGE);
+            const uint64_t ar = ballot(i < m && sen != kLE);
+            const uint64_t eq = ballot(i < m && sen == kEQ);
             sc[r] = -1;
             if (i < m && sen == kGE) {
                 const int g = ng + __popcll(ge & lanemask_lt(lane));
@@ -769,19 +894,23 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(PFD > 0 ? 2 
         }
         P.N = n + ng;
         P.C = P.N;
-        P.ldm = col_stride<T>(m);
+        P.ld = row_stride<T>(P.N);
         P.nart = nart;
-        const int64_t need = aux + int64_t(P.C) * P.ldm * int64_t(sizeof(T));
+        const int64_t need = aux + int64_t(m) * P.ld * int64_t(sizeof(T));
         const bool fits = P.C <= 64 && m <= 64 * RB && need <= a.lds_bytes;
         if (!fits && lane == 0) {
             const int slot = a.defer_base + atomicAdd(a.defer_count, 1);
             a.defer_ids[slot] = int32_t(k);
         }
-        const int N = P.N, C = P.C, ldm = P.ldm;
+        const int N = P.N, C = P.C, ld = P.ld;
         T *tab = reinterpret_cast<T *>(smem + aux);
         P.tab = tab;
 
-        // A2: index arrays and the tableau (column-major in LDS).
+#pragma unroll
+        for (int r = 0; r < RB; ++r) P.rowat[r] = min(lane + 64 * r, m - 1) * ld;
+        P.colat = min(lane, C - 1);
+
+        // A2: index arrays and the tableau (row-major in LDS).
         P.nonb = kBig;
         const double cj = fresh_copy(F.cv);
         if (fits) {
@@ -797,30 +926,36 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(PFD > 0 ? 2 
             P.basis[r] = (((P.rowf[r] >> 1) & 3) == kLE) ? n + i : n + m + i;
         }
         {
-            // A scattered from flat row-major order into the columns.  Element
-            // f = lane + 64 t sits at row f / n, column f % n; stepping t by one
+            // A in flat row-major order, which is the tableau's own when its row
+            // stride is n; otherwise element f = lane + 64 t, at row f / n and
+            // column f % n, moves on by (f / n) (ld - n).  Stepping t by one
             // advances the column by 64 % n and the row by 64 / n, plus one
             // when the column wraps.
             const int mn = m * n;
             const int dq = 64 / n, dr = 64 - dq * n;
             int ri = lane / n, cj2 = lane - (lane / n) * n;
             if (PFD > 0 && F.has_a) {
-                // The element's position cj2 * ldm + ri advances by
-                // dr * ldm + dq per step, and by 1 - n * ldm more when the
-                // column wraps; only the last, partial step needs a bounds test.
-                // (Prefetched elements past m * n read as 0, so every register
-                // can be checked for finiteness.)
+                // Only the last, partial step needs a bounds test.  (Prefetched
+                // elements past m * n read as 0, so every register can be checked
+                // for finiteness.)
                 const int full = mn >> 6;
-                const int step = dr * ldm + dq, wrap = 1 - n * ldm;
-                int pos = cj2 * ldm + ri;
 #pragma unroll
                 for (int t = 0; t < (PFD > 0 ? PFD : 1); ++t) bad |= !isfinite(F.av[t]);
+                if (ld == n) {
+                    T *at = tab + lane;
 #pragma unroll
-                for (int t = 0; t < (PFD > 0 ? PFD : 1); ++t) {
-                    if (t < full || (t == full && lane + 64 * t < mn)) tab[pos] = T(F.av[t]);
-                    cj2 += dr;
-                    pos += step;
-                    if (cj2 >= n) { cj2 -= n; pos += wrap; }
+                    for (int t = 0; t < (PFD > 0 ? PFD : 1); ++t)
+                        if (t < full || (t == full && lane + 64 * t < mn)) at[64 * t] = T(F.av[t]);
+                } else {
+                    const int gap = ld - n, step = 64 + gap * dq;
+                    int pos = lane + gap * ri;
+#pragma unroll
+                    for (int t = 0; t < (PFD > 0 ? PFD : 1); ++t) {
+                        if (t < full || (t == full && lane + 64 * t < mn)) tab[pos] = T(F.av[t]);
+                        cj2 += dr;
+                        pos += step;
+                        if (cj2 >= n) { cj2 -= n; pos += gap; }
+                    }
                 }
             } else {
                 // (Eight loads in flight for FP32 LPs of up to 64 rows keeps them
@@ -851,7 +986,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(PFD > 0 ? 2 
                     for (int u = 0; u < UB; ++u) {
                         if (f0 + 64 * u + lane < mn) {
                             bad |= !isfinite(av[u]);
-                            tab[cj2 * ldm + ri] = T(av[u]);
+                            tab[ri * ld + cj2] = T(av[u]);
                         }
                         ri += dq;
                         cj2 += dr;
@@ -862,11 +997,11 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(PFD > 0 ? 2 
             // Rows with b < 0 are negated (sign normalisation).
 #pragma unroll
             for (int r = 0; r < RB; ++r) {
-                uint64_t neg = __ballot(lane + 64 * r < m && (P.rowf[r] & kRowNeg));
+                uint64_t neg = ballot(lane + 64 * r < m && (P.rowf[r] & kRowNeg));
                 while (neg) {
                     const int i = 64 * r + __builtin_ctzll(neg);
                     neg &= neg - 1;
-                    if (lane < n) tab[lane * ldm + i] = -tab[lane * ldm + i];
+                    if (lane < n) tab[i * ld + lane] = -tab[i * ld + lane];
                 }
             }
             // Surplus columns, one row per lane.
@@ -874,7 +1009,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(PFD > 0 ? 2 
             for (int r = 0; r < RB; ++r) {
                 const int i = lane + 64 * r;
                 if (i < m)
-                    for (int g = 0; g < ng; ++g) tab[(n + g) * ldm + i] = (sc[r] == n + g) ? T(-1) : T(0);
+                    for (int g = 0; g < ng; ++g) tab[i * ld + n + g] = (sc[r] == n + g) ? T(-1) : T(0);
             }
         }
         }  // fits
@@ -886,13 +1021,13 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(PFD > 0 ? 2 
         // The registers of F are free again: start loading the next LP.  (The
         // last LP of a wavefront reloads itself, so the loads are unconditional
         // and land in the registers the current LP's came in.)
-        fetch<RB, PFD>(a, nxt < total ? nxt : cur, F);
+        fetch<RB, PFD>(nxt < total ? nxt : cur, F);
         if (!fits) {
             cur = nxt;
             nxt = queue.item(lane_get(qv, 0));
             continue;
         }
-        const bool invalid = __ballot(bad) != 0;
+        const bool invalid = ballot(bad) != 0;
         P.iters = 0; P.it1 = 0; P.degp = 0;
         P.cap = a.prm.max_iters > 0 ? a.prm.max_iters : 50 * (m + n + (m - neq) + nart);
         P.d = T(0);
@@ -904,95 +1039,102 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(PFD > 0 ? 2 
         // and only for all-<= LPs; any other LP is solved from the slack basis
         // right here.  An LP whose repair fails is deferred.
         bool warm_ok = false, warm_defer = false;
+        Pending<T, RB, WARM ? NG : 0> pend;
         if (invalid) {
             status = kInvalid;
         } else {
             if constexpr (WARM) {
                 warm_ok = nart == 0 && a.status[k] == kOptimal &&
                           !(a.warm_viol && a.warm_viol[k] > a.warm_max_viol);
-                if (warm_ok) warm_defer = !crash<T, RB>(P, a, k);
-            }
-            if (warm_defer) {
-                // nothing more here: the LP goes to the solve from the slack basis
-            } else if (nart > 0) {
-                // Phase I objective row: sum of the artificial rows in row order.
-                T acc = T(0), zacc = T(0);
-                for (int i = 0; i < m; ++i) {
-                    const int sen = (row_get<RB>(P.rowf, i) >> 1) & 3;
-                    if (sen != kLE) {
-                        if (lane < C) acc += tab[lane * ldm + i];
-                        zacc += row_get<RB>(P.rhs, i);
-                    }
+                if (warm_ok) {
+                    P.keep = true;
+                    pend.clear();
+                    warm_defer = !crash(P, pend, a, k);
                 }
-                P.d = acc;
-                P.z = zacc;
-                const double dmax = wave_max_f(lane < N ? fabs(double(acc)) : 0.0);
-                const double dscale = fmax(1.0, dmax);
-                const int r = simplex<T, RB, !WARM>(P, T(a.prm.tol_opt * dscale), a.prm, &enter);
+            }
+            // Phase I where some row needs an artificial, then Phase II.
+            for (int phase = nart > 0 ? 1 : 2; !warm_defer; phase = 2) {
+                T eps_opt;
+                int r = kPrimal;
+                P.keep = phase == 1;
+                if (phase == 1) {
+                    // Objective row: sum of the artificial rows in row order.
+                    T acc = T(0), zacc = T(0);
+                    for (int i = 0; i < m; ++i) {
+                        const int sen = (row_get<RB>(P.rowf, i) >> 1) & 3;
+                        if (sen != kLE) {
+                            if (lane < C) acc += tab[i * ld + lane];
+                            zacc += row_get<RB>(P.rhs, i);
+                        }
+                    }
+                    P.d = acc;
+                    P.z = zacc;
+                    const double dmax = wave_max_f(lane < N ? fabs(double(acc)) : 0.0);
+                    eps_opt = T(a.prm.tol_opt * fmax(1.0, dmax));
+                } else {
+                    // Objective row: c priced out over the basis, rows in order.
+                    T cb[RB];
+                    uint64_t nz[RB];
+#pragma unroll
+                    for (int r = 0; r < RB; ++r) {
+                        const int bvr = P.basis[r];
+                        const double cbv = __shfl(cj, bvr < n ? bvr : 0);  // c of the row's basic variable
+                        cb[r] = (!(P.rowf[r] & (kRowDead | kRowPad)) && bvr < n) ? T(cbv) : T(0);
+                        nz[r] = ballot(cb[r] != T(0));
+                    }
+                    const double cnb = __shfl(cj, (P.nonb >= 0 && P.nonb < n) ? P.nonb : 0);
+                    T acc = (lane < N && P.nonb < n) ? T(cnb) : T(0), zacc = T(0);
+#pragma unroll
+                    for (int r = 0; r < RB; ++r) {
+                        uint64_t mk = nz[r];
+                        while (mk) {
+                            const int bit = __builtin_ctzll(mk);
+                            mk &= mk - 1;
+                            const T f = lane_get(cb[r], bit);
+                            if (lane < C) acc = fma(-f, tab[(64 * r + bit) * ld + lane], acc);
+                            zacc = fma(-f, lane_get(P.rhs[r], bit), zacc);
+                        }
+                    }
+                    P.d = acc;
+                    P.z = zacc;
+                    eps_opt = T(a.prm.tol_opt * fmax(1.0, cnorm));
+                    // Single-precision level for the start's reduced costs.
+                    if (WARM && warm_ok)
+                        r = dual_repair(P, pend, T(1e-5 * fmax(1.0, cnorm)), T(a.prm.tol_feas * (1.0 + bnorm)), a.prm);
+                }
+                if (r == kPrimal) r = simplex<T, RB, NG>(P, eps_opt, a.prm, &enter);
+                if (phase == 2) {
+                    status = r;
+                    if (WARM && warm_ok) warm_defer = status != kOptimal;
+                    break;
+                }
                 P.it1 = P.iters;
                 enter = -1;
                 if (r == kIterLimit) status = kIterLimit;
                 else if (r == kUnbounded) status = kNumerical;
-                else {
-                    const double wstar = -double(P.z);
-                    if (wstar < -a.prm.tol_feas * (1.0 + bnorm)) status = kInfeasible;
-                }
-                if (status == kOptimal) {
-                    // Drive basic artificials out in row order; drop redundant rows.
-                    const T tol_piv = T(a.prm.tol_piv);
+                else if (-double(P.z) < -a.prm.tol_feas * (1.0 + bnorm)) status = kInfeasible;
+                if (status != kOptimal) break;
+                // Drive basic artificials out in row order; drop redundant rows.
+                const T tol_piv = T(a.prm.tol_piv);
 #pragma unroll
-                    for (int r = 0; r < RB; ++r) {
-                        uint64_t am = __ballot(lane + 64 * r < m && P.basis[r] >= n + m);
-                        while (am) {
-                            const int bit = __builtin_ctzll(am);
-                            am &= am - 1;
-                            const int i = 64 * r + bit;
-                            bool ok = false;
-                            if (lane < N && P.nonb < n + m) ok = fabs(tab[lane * ldm + i]) > tol_piv;
-                            const int e = price<T>(ok, T(0), P.nonb, true);
-                            if (e >= 0) {
-                                load_pcol<T, RB>(P, e);
-                                pivot<T, RB>(P, i, e);
-                            } else if (lane == bit) {
-                                P.rowf[r] |= kRowDead;
-                            }
+                for (int r = 0; r < RB; ++r) {
+                    uint64_t am = ballot(lane + 64 * r < m && P.basis[r] >= n + m);
+                    while (am) {
+                        const int bit = __builtin_ctzll(am);
+                        am &= am - 1;
+                        const int i = 64 * r + bit;
+                        bool ok = false;
+                        if (lane < N && P.nonb < n + m) ok = fabs(tab[i * ld + lane]) > tol_piv;
+                        const int e = price<T>(ok, T(0), P.nonb, true);
+                        if (e >= 0) {
+                            pend.clear();
+                            pend.load_pcol(P, e);
+                            pend.pivot(P, i, e, pend.load_row(P, i));
+                            pend.sweep(P);
+                        } else if (lane == bit) {
+                            P.rowf[r] |= kRowDead;
                         }
                     }
-                }
-            }
-            if (status == kOptimal && !warm_defer) {
-                // Phase II objective row: c priced out over the basis, rows in order.
-                T cb[RB];
-                uint64_t nz[RB];
-#pragma unroll
-                for (int r = 0; r < RB; ++r) {
-                    const int bvr = P.basis[r];
-                    const double cbv = __shfl(cj, bvr < n ? bvr : 0);  // c of the row's basic variable
-                    cb[r] = (!(P.rowf[r] & (kRowDead | kRowPad)) && bvr < n) ? T(cbv) : T(0);
-                    nz[r] = __ballot(cb[r] != T(0));
-                }
-                const double cnb = __shfl(cj, (P.nonb >= 0 && P.nonb < n) ? P.nonb : 0);
-                T acc = (lane < N && P.nonb < n) ? T(cnb) : T(0), zacc = T(0);
-#pragma unroll
-                for (int r = 0; r < RB; ++r) {
-                    uint64_t mk = nz[r];
-                    while (mk) {
-                        const int bit = __builtin_ctzll(mk);
-                        mk &= mk - 1;
-                        const T f = lane_get(cb[r], bit);
-                        if (lane < C) acc = fma(-f, tab[lane * ldm + 64 * r + bit], acc);
-                        zacc = fma(-f, lane_get(P.rhs[r], bit), zacc);
-                    }
-                }
-                P.d = acc;
-                P.z = zacc;
-                if (WARM && warm_ok) {
-                    // Single-precision level for the start's reduced costs.
-                    status = dual_repair<T, RB>(P, T(a.prm.tol_opt * fmax(1.0, cnorm)), T(1e-5 * fmax(1.0, cnorm)),
-                                                T(a.prm.tol_feas * (1.0 + bnorm)), a.prm, &enter);
-                    warm_defer = status != kOptimal;
-                } else {
-                    status = simplex<T, RB, !WARM>(P, T(a.prm.tol_opt * fmax(1.0, cnorm)), a.prm, &enter);
                 }
             }
         }
@@ -1010,8 +1152,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(PFD > 0 ? 2 
         }
 
         // A8: extraction through an LDS staging vector.
-        // The tableau's first columns are free now (the rhs column N is read
-        // below and lies past them): x is staged there.
+        const auto &out = *late_args();
+        // The tableau is free now: x is staged in its place.
         T *xv = tab;
         if (lane < n) xv[lane] = T(0);
         if (status == kOptimal) {
@@ -1023,7 +1165,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(PFD > 0 ? 2 
             }
         }
         const double xj = (lane < n) ? double(xv[lane]) : 0.0;
-        if (lane < n) a.x[P.co + lane] = (status == kOptimal) ? xj : __builtin_nan("");
+        if (lane < n) out.x[P.co + lane] = (status == kOptimal) ? xj : __builtin_nan("");
         double z = (lane < n) ? fma(cj, xj, 0.0) : 0.0;
         int nbs = (lane < n && xj != 0.0) ? 1 : 0;
 #pragma unroll
@@ -1035,12 +1177,12 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(PFD > 0 ? 2 
             double objv = z;
             if (status == kUnbounded) objv = __builtin_inf();
             else if (status != kOptimal) objv = __builtin_nan("");
-            a.obj[k] = objv;
-            a.status[k] = status;
-            if (a.enter_out) a.enter_out[k] = (status == kUnbounded) ? enter : -1;
-            if (a.stats) {
-                int32_t *st = a.stats + 8 * k;
-                if (a.refine_stats) {
+            out.obj[k] = objv;
+            out.status[k] = status;
+            if (out.enter_out) out.enter_out[k] = (status == kUnbounded) ? enter : -1;
+            if (out.stats) {
+                int32_t *st = out.stats + 8 * k;
+                if (out.refine_stats) {
                     st[3] = warm_ok ? 2 : 1;  // 2: started from the relaxation's basis
                     st[4] = P.iters;
                 } else {
@@ -1055,11 +1197,11 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(PFD > 0 ? 2 
                 st[7] = nbs;
             }
         }
-        if (a.basis_out) {
+        if (out.basis_out) {
 #pragma unroll
             for (int r = 0; r < RB; ++r) {
                 const int i = lane + 64 * r;
-                if (i < m) a.basis_out[P.ro + i] = (P.rowf[r] & kRowDead) ? -1 : P.basis[r];
+                if (i < m) out.basis_out[P.ro + i] = (P.rowf[r] & kRowDead) ? -1 : P.basis[r];
             }
         }
         cur = nxt;
@@ -1109,7 +1251,7 @@ int64_t wave_lds_aux_bytes(int rb, bool gather) { return wave_aux_bytes(rb, gath
 
 int64_t wave_tab_bytes(int m, int cols, bool fp32)
 {
-    return fp32 ? int64_t(cols) * col_stride<float>(m) * 4 : int64_t(cols) * col_stride<double>(m) * 8;
+    return fp32 ? int64_t(m) * row_stride<float>(cols) * 4 : int64_t(m) * row_stride<double>(cols) * 8;
 }
 
 int wave_prefetch_elems() { return 64 * NPF; }

@@ -1,0 +1,57 @@
+"""Deferred pivots of the one-wavefront kernel: sizes at the edges of its 16 x 16
+tiles and 64-row blocks, LPs of fewer and of many more pivots than one window
+holds, one and two phases.  Status and objective against the oracle; status,
+x, objective and pivot counts bit for bit against the workgroup kernel, whose
+sweeps are organised differently."""
+import numpy as np
+import pytest
+
+from paper_1802_08557_amd import workloads as W
+from helpers import assert_parity, oracle_solve
+
+pytestmark = pytest.mark.gpu
+
+SIZES = [(1, 1), (1, 64), (128, 1), (15, 17), (16, 16), (17, 15), (31, 48), (32, 49), (33, 33), (48, 20),
+         (49, 64), (63, 47), (64, 64), (65, 16), (80, 32), (96, 33), (113, 48), (127, 40), (128, 64)]
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    from paper_1802_08557_amd import lpbatch
+    c = lpbatch.Context(0)
+    yield c
+    c.close()
+
+
+def gaussian(N, m, n, seed):
+    """A ~ N(0,1), b ~ U[1,100], c ~ U[-1,10], all <=: tens to hundreds of pivots."""
+    rng = np.random.default_rng(seed)
+    return W.Batch(rng.standard_normal(N * m * n), rng.uniform(1.0, 100.0, N * m), rng.uniform(-1.0, 10.0, N * n),
+                   np.zeros(N * m, np.int8), np.full(N, m, np.int32), np.full(N, n, np.int32), f"gaussian_{m}x{n}")
+
+
+def solve(ctx, bt, **kw):
+    from paper_1802_08557_amd.lpbatch import DeviceBatch
+    print(f"[gpu] window {bt.name} {kw}", flush=True)
+    s = ctx.solve(DeviceBatch.from_host(bt), stats=True, sync=True, **kw)
+    return [v.cpu().numpy() for v in (s.status, s.obj, s.x, s.stats)]
+
+
+@pytest.mark.parametrize("pricing", [0, 1])
+@pytest.mark.parametrize("m,n", SIZES)
+def test_windows_match_workgroup_kernel(ctx, m, n, pricing):
+    for bt in (gaussian(24, m, n, 100 * m + n), W.uniform_batch(12, m, n, seed=m + n),
+               W.phase1_batch(12, m, n, seed=7 * m + n)):
+        ref = oracle_solve(bt, pricing=pricing)
+        st, obj, x, stats = solve(ctx, bt, pricing=pricing)
+        assert_parity(bt, st, obj, x, ref)
+        st2, obj2, x2, stats2 = solve(ctx, bt, pricing=pricing, block_threads=64)
+        assert np.array_equal(st, st2)
+        assert np.array_equal(obj, obj2, equal_nan=True) and np.array_equal(x, x2, equal_nan=True)
+        assert np.array_equal(stats[:, :3], stats2[:, :3])
+        if not bt.sense.any():
+            assert np.all(stats[:, 6] == 1)
+        st3, obj3, x3, _ = solve(ctx, bt, pricing=pricing, precision=1)
+        assert_parity(bt, st3, obj3, x3, ref)
