@@ -347,6 +347,16 @@ __device__ __forceinline__ void finish_launch(int32_t *queue, int32_t *extra)
     if (extra) atomicExch(extra, 0);
 }
 
+// A solve launch's arguments, read again from the kernel's argument segment where
+// they are used: held in scalar registers from the start they spill.
+typedef const __attribute__((address_space(4))) SolveArgs *LateArgs;
+__device__ __forceinline__ LateArgs late_args()
+{
+    LateArgs p = (LateArgs)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    return p;
+}
+
 __device__ __forceinline__ uint64_t lanemask_lt(int lane)
 {
     return (uint64_t(1) << lane) - 1;

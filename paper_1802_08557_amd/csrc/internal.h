@@ -243,43 +243,39 @@ int64_t wave_lds_aux_bytes(int rb, bool gather);
 int64_t wave_tab_bytes(int m, int cols, bool fp32);
 hipError_t simplex_wave_configure(int max_lds);
 
-// Size of the LDS control block + index arrays + pivot row/column buffers for an
-// LP with m rows and at most ncol_max non-basic columns, and the byte offset where
-// an LDS-resident tableau would start.  Host and device compute the same layout.
-
+// LDS of the workgroup kernel for an LP of m rows and N non-basic columns (byte
+// offsets): control block, index arrays, right-hand sides, reduced costs, then
+// the window of deferred pivots (a column of m and a row of N entries each),
+// then, where it fits, the tableau.  The offsets up to rhs do not depend on N.
 struct LdsLayout {
-    int64_t ctrl, basis, nonb, rowf, colrow, pcol, prow, pcol2, prow2, pcol3, prow3, tab, end_aux;
+    int64_t basis, rowf, colrow, rhs, nonb, obj, win, vec;
+    // End of a window of K pivots: where an LDS-resident tableau starts.
+    __host__ __device__ int64_t window(int64_t K) const { return align16(win + K * vec); }
 };
 
 // ctrl_bytes: size of the control block (type dependent, passed by the caller).
-__host__ __device__ inline LdsLayout lds_layout(int m, int ncol_max, int64_t tsize, int64_t ctrl_bytes)
+__host__ __device__ inline LdsLayout lds_layout(int m, int N, int64_t tsize, int64_t ctrl_bytes)
 {
     LdsLayout L;
-    L.ctrl = 0;
     L.basis = align16(ctrl_bytes);
-    L.nonb = align16(L.basis + 4 * (int64_t)m);
-    L.rowf = align16(L.nonb + 4 * (int64_t)ncol_max);
-    L.colrow = align16(L.rowf + 4 * (int64_t)m);
-    L.pcol = align16(L.colrow + 4 * (int64_t)m);
-    L.prow = align16(L.pcol + tsize * (int64_t)(m + 1));
-    L.pcol2 = align16(L.prow + tsize * (int64_t)(ncol_max + 1));
-    L.prow2 = align16(L.pcol2 + tsize * (int64_t)(m + 1));
-    L.pcol3 = align16(L.prow2 + tsize * (int64_t)(ncol_max + 1));
-    L.prow3 = align16(L.pcol3 + tsize * (int64_t)(m + 1));
-    L.tab = align16(L.prow3 + tsize * (int64_t)(ncol_max + 1));
-    L.end_aux = L.tab;
+    L.rowf = L.basis + 4 * int64_t(m);
+    L.colrow = L.rowf + 4 * int64_t(m);
+    L.rhs = align16(L.colrow + 4 * int64_t(m));
+    L.nonb = align16(L.rhs + tsize * int64_t(m));
+    L.obj = align16(L.nonb + 4 * int64_t(N));
+    L.win = align16(L.obj + tsize * int64_t(N));
+    L.vec = tsize * (int64_t(m) + N);
     return L;
 }
 
-// Row stride (elements) of a workgroup-kernel tableau with C = (non-basic
-// columns + 1) entries per row and tsize-byte entries: an odd number of
-// 16-byte units, so every row starts 16-byte aligned (the pivot sweep moves
-// 16 bytes per lane per access) and walking a column of an LDS-resident
-// tableau spreads over the banks.
-__host__ __device__ inline int tableau_ld(int C, int tsize)
+// Row stride (elements) of a workgroup-kernel tableau of N columns.  In LDS: no
+// multiple of four, so that walking a column spreads over the banks; in device
+// memory: whole cache lines of 128 bytes.
+__host__ __device__ inline int lds_tab_ld(int N) { return N & 3 ? N : N + 1; }
+__host__ __device__ inline int slot_tab_ld(int N, int tsize)
 {
-    const int R = 16 / tsize;
-    return R * (((C + R - 1) / R) | 1);
+    const int R = 128 / tsize;
+    return (N + R - 1) / R * R;
 }
 
 }  // namespace lpb

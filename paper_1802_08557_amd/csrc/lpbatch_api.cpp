@@ -88,15 +88,47 @@ int64_t lds_budget(const lp_ctx *ctx, int placement)
     return placement == LP_PLACE_LDS ? ctx->max_lds : ctx->max_lds / 3;
 }
 
-// LDS for one workgroup of the workgroup kernel that keeps per_cu of them
-// resident: when registers already cap a CU at per_cu workgroups, each may
-// take the CU's LDS / per_cu, and every LP whose tableau fits there next to
-// the index arrays is then solved from LDS instead of a device-memory slot.
-int64_t lds_share(const lp_ctx *ctx, bool fp32, int nt, int64_t lds, int per_cu)
+// LDS of one workgroup of the workgroup kernel and how many of them share a
+// CU, for LPs of at most m_max x n_max.
+struct BlockPlan {
+    int64_t lds, slot_bytes;
+    int per_cu;
+};
+
+// Pivots a launch wants its largest LP's window to hold.  Tableaux in device
+// memory are swept once per window, so a longer window is less traffic but
+// fewer workgroups per CU to hide each pivot's latency.
+constexpr int kWantWindow = 12, kWantWindowLds = 8;
+
+int plan_block(const lp_ctx *ctx, bool fp32, int nt, int m_max, int n_max, bool force_hbm, int placement,
+               BlockPlan &B)
 {
-    const int64_t share = std::min<int64_t>(ctx->max_lds, (int64_t(ctx->lds_per_cu) / per_cu) & ~int64_t(255));
-    if (share <= lds) return lds;
-    return lpb::simplex_blocks_per_cu(fp32, nt, int(share)) == per_cu ? share : lds;
+    const int64_t ts = fp32 ? 4 : 8, ctrl = lpb::simplex_ctrl_bytes(fp32);
+    const int ncol_worst = n_max + m_max;
+    // The launch must hold the index arrays and a window of two pivots for every
+    // LP whatever its surplus columns; budgets are for the common case of none.
+    const int64_t least = lpb::lds_layout(m_max, ncol_worst, ts, ctrl).window(2);
+    if (least > ctx->max_lds)
+        return fail(LP_ERR_ARG, "LP of %d rows x %d columns needs %lld bytes of LDS for its index arrays "
+                    "(device limit %d)", m_max, ncol_worst, (long long)least, ctx->max_lds);
+    const lpb::LdsLayout L = lpb::lds_layout(m_max, n_max, ts, ctrl);
+    const int64_t tab = int64_t(m_max) * lpb::lds_tab_ld(n_max) * ts;
+    const int64_t with_tab = std::max(least, L.window(kWantWindowLds) + tab + 16);
+    const bool want_lds = !force_hbm && with_tab <= lds_budget(ctx, placement);
+    int64_t lds = want_lds ? with_tab : std::max(least, std::min<int64_t>(ctx->max_lds, L.window(kWantWindow)));
+    B.per_cu = lpb::simplex_blocks_per_cu(fp32, nt, int(lds));
+    if (B.per_cu < 1) return fail(LP_ERR_HIP, "occupancy query failed for %d threads, %lld B LDS", nt, (long long)lds);
+    // Two wavefronts per SIMD: more of them hide more of each pivot's latency, but
+    // halve the LDS of each, which holds windows and tableaux (uneven 10..300
+    // FP64 66 ms with two, 95 ms with three; FP32 46 and 55 ms).  Each workgroup
+    // takes the CU's LDS / per_cu: longer windows, and every LP whose tableau
+    // fits there is solved from LDS instead of a device-memory slot.
+    B.per_cu = std::min(B.per_cu, 512 / nt);
+    const int64_t share = std::min<int64_t>(ctx->max_lds, (int64_t(ctx->lds_per_cu) / B.per_cu) & ~int64_t(255));
+    if (share > lds && lpb::simplex_blocks_per_cu(fp32, nt, int(share)) >= B.per_cu) lds = share;
+    B.lds = lds;
+    B.slot_bytes = lpb::align16(int64_t(m_max) * lpb::slot_tab_ld(ncol_worst, int(ts)) * ts);
+    return LP_OK;
 }
 
 // One persistent launch of the wavefront kernel over ids[0 .. num) (or the
@@ -148,52 +180,35 @@ int queue_pass(lp_ctx *ctx, const Plan &P, lpb::SolveArgs a, const lp_options &o
                char *slot_mem = nullptr, int64_t slot_cap = 0)
 {
     const bool fp32 = P.fp32;
-    const int64_t ts = P.ts;
     if (n_wave > 0) {
         int rc = launch_wave(ctx, fp32, a, pc, list_count ? list_ids : wave_ids, list_count ? P.num : n_wave,
                              list_count, wm_max, wn_max, defer_ids, int32_t(n_block), stream, timing, wname);
         if (rc != LP_OK) return rc;
     }
     // Workgroup kernel: the LPs given to it plus the ones the wavefront deferred.
-    const int ncol_worst = P.n_max + P.m_max;
-    lpb::LdsLayout L = lpb::lds_layout(P.m_max, ncol_worst, ts, lpb::simplex_ctrl_bytes(fp32));
-    // Tableau budget for the common case of no surplus columns (every row <= after
-    // normalisation); LPs with more columns than budgeted move to HBM by themselves.
-    const int64_t tab_common = int64_t(P.m_max + 1) * lpb::tableau_ld(P.n_max + 1, int(ts)) * ts;
-    const int64_t tab_worst = int64_t(P.m_max + 1) * lpb::tableau_ld(ncol_worst + 1, int(ts)) * ts;
     const int64_t cells = int64_t(P.m_max + 1) * (P.n_max + 1);
     int nt = opts.block_threads;
     if (!nt) nt = cells <= 64 * 64 ? 64 : (cells <= 256 * 256 ? 256 : 512);
-    int64_t lds = L.tab;
-    const bool want_lds = opts.placement != LP_PLACE_HBM && L.tab + tab_common <= lds_budget(ctx, opts.placement);
-    if (want_lds) lds = L.tab + tab_common;
-    if (lds > ctx->max_lds)
-        return fail(LP_ERR_ARG, "LP of %d rows x %d columns needs %lld bytes of LDS for its index "
-                    "arrays (device limit %d)", P.m_max, ncol_worst, (long long)lds, ctx->max_lds);
     a.force_hbm = opts.placement == LP_PLACE_HBM;
-    const int per_cu = lpb::simplex_blocks_per_cu(fp32, nt, int(lds));
-    if (per_cu < 1) return fail(LP_ERR_HIP, "occupancy query failed for %d threads, %lld B LDS", nt, (long long)lds);
-    if (!a.force_hbm) lds = lds_share(ctx, fp32, nt, lds, per_cu);
-    a.lds_bytes = int32_t(lds);
+    BlockPlan B;
+    if (int rc = plan_block(ctx, fp32, nt, P.m_max, P.n_max, a.force_hbm, opts.placement, B)) return rc;
+    a.lds_bytes = int32_t(B.lds);
+    a.slot_bytes = B.slot_bytes;
     // When the wavefront kernel was offered every LP, this launch only drains
     // the few it deferred: one workgroup per CU is plenty and keeps its end cheap.
-    const int64_t slots = n_wave > 0 && n_block == 0 ? ctx->num_cu : int64_t(per_cu) * ctx->num_cu;
+    const int64_t slots = n_wave > 0 && n_block == 0 ? ctx->num_cu : int64_t(B.per_cu) * ctx->num_cu;
     int64_t grid = std::min<int64_t>(P.num, slots);
-    const bool need_hbm = !want_lds || tab_worst > tab_common;
-    if (need_hbm) {
-        a.slot_bytes = lpb::align16(tab_worst);
-        if (slot_mem) {
-            const int64_t fit = slot_cap / a.slot_bytes;
-            if (fit < 1)
-                return fail(LP_ERR_ARG, "a %lld-byte tableau slot exceeds the %lld bytes available",
-                            (long long)a.slot_bytes, (long long)slot_cap);
-            grid = std::min(grid, fit);
-            a.scratch = slot_mem;
-        } else {
-            int rc = ctx->scratch.ensure(size_t(a.slot_bytes) * size_t(grid));
-            if (rc != LP_OK) return rc;
-            a.scratch = static_cast<char *>(ctx->scratch.p);
-        }
+    if (slot_mem) {
+        const int64_t fit = slot_cap / a.slot_bytes;
+        if (fit < 1)
+            return fail(LP_ERR_ARG, "a %lld-byte tableau slot exceeds the %lld bytes available",
+                        (long long)a.slot_bytes, (long long)slot_cap);
+        grid = std::min(grid, fit);
+        a.scratch = slot_mem;
+    } else {
+        int rc = ctx->scratch.ensure(size_t(a.slot_bytes) * size_t(grid));
+        if (rc != LP_OK) return rc;
+        a.scratch = static_cast<char *>(ctx->scratch.p);
     }
     a.queue = pc.bq;
     a.num = P.num;
@@ -237,9 +252,10 @@ int bin_of(int64_t m, int64_t n)
     return cells <= 64 * 64 ? 0 : cells <= 128 * 128 ? 1 : cells <= 256 * 256 ? 2 : 3;
 }
 
-// Untuned workgroup size: 512 threads for every bin (the autotuner picked 512 in
-// every bin of the 10..300 uneven batch on MI355X).
-int default_threads(int) { return 512; }
+// Untuned workgroup size: two workgroups of 256 threads per CU hide more of each
+// pivot's latency than one of 512 (uneven 10..300 batch FP64 66 against 79 ms,
+// FP32 46 against 70 ms).
+int default_threads(int) { return 256; }
 
 // FNV-1a over the batch's shapes and the planning flags (the plan cache key).
 uint64_t shape_hash(int64_t num, const int32_t *m, const int32_t *n, uint32_t flags)
@@ -274,31 +290,17 @@ int launch_block(lp_ctx *ctx, bool fp32, lpb::SolveArgs a, const BinLaunch &B, c
                  const int32_t *num_dev, int32_t id_base, int32_t *reset_extra, int64_t grid_cap, int32_t *q,
                  hipStream_t stream, bool timing, const char *name)
 {
-    const int64_t ts = fp32 ? 4 : 8;
-    const int ncol_worst = B.n_max + B.m_max;
-    lpb::LdsLayout L = lpb::lds_layout(B.m_max, ncol_worst, ts, lpb::simplex_ctrl_bytes(fp32));
-    const int64_t tab_common = int64_t(B.m_max + 1) * lpb::tableau_ld(B.n_max + 1, int(ts)) * ts;
-    const int64_t tab_worst = int64_t(B.m_max + 1) * lpb::tableau_ld(ncol_worst + 1, int(ts)) * ts;
-    int64_t lds = L.tab;
-    const bool want_lds = !B.force_hbm && L.tab + tab_common <= lds_budget(ctx, B.placement);
-    if (want_lds) lds = L.tab + tab_common;
-    if (lds > ctx->max_lds)
-        return fail(LP_ERR_ARG, "LP of %d rows x %d columns needs %lld bytes of LDS for its index arrays "
-                    "(device limit %d)", B.m_max, ncol_worst, (long long)lds, ctx->max_lds);
+    BlockPlan L;
+    if (int rc = plan_block(ctx, fp32, B.nt, B.m_max, B.n_max, B.force_hbm, B.placement, L)) return rc;
     a.force_hbm = B.force_hbm;
-    const int per_cu = lpb::simplex_blocks_per_cu(fp32, B.nt, int(lds));
-    if (per_cu < 1) return fail(LP_ERR_HIP, "occupancy query failed for %d threads, %lld B LDS", B.nt, (long long)lds);
-    if (!a.force_hbm) lds = lds_share(ctx, fp32, B.nt, lds, per_cu);
-    a.lds_bytes = int32_t(lds);
-    int64_t grid = std::min<int64_t>(num, int64_t(per_cu) * ctx->num_cu);
+    a.lds_bytes = int32_t(L.lds);
+    a.slot_bytes = L.slot_bytes;
+    int64_t grid = std::min<int64_t>(num, int64_t(L.per_cu) * ctx->num_cu);
     if (grid_cap > 0) grid = std::min(grid, grid_cap);
     if (grid < 1) return LP_OK;
-    if (!want_lds || tab_worst > tab_common) {
-        a.slot_bytes = lpb::align16(tab_worst);
-        int rc = ctx->scratch.ensure(size_t(a.slot_bytes) * size_t(grid));
-        if (rc != LP_OK) return rc;
-        a.scratch = static_cast<char *>(ctx->scratch.p);
-    }
+    int rc = ctx->scratch.ensure(size_t(a.slot_bytes) * size_t(grid));
+    if (rc != LP_OK) return rc;
+    a.scratch = static_cast<char *>(ctx->scratch.p);
     a.queue = q;
     a.ids = ids;
     a.num = num;
@@ -1019,7 +1021,7 @@ int lp_batch_solve_noalloc(lp_ctx *ctx, int64_t num_lps, const double *A, const 
                     hipGetErrorString(hipError_t(ctx->noalloc_err)));
     // A deferred LP (more columns than the wavefront holds once >= rows add
     // their surplus columns) needs one workgroup-kernel slot at least.
-    const int64_t slot = lpb::align16(int64_t(m + 1) * lpb::tableau_ld(n + m + 1, 8) * 8);
+    const int64_t slot = lpb::align16(int64_t(m) * lpb::slot_tab_ld(n + m, 8) * 8);
     if (slot > lpb::kNoAllocBytes - lpb::kNoAllocSlotsAt)
         return fail(LP_ERR_ARG, "lp_batch_solve_noalloc: LPs of %d x %d need a larger tableau slot", m, n);
     DeviceGuard g(ctx->device);

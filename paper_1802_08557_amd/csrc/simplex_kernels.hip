@@ -10,11 +10,11 @@
 //
 // The tableau is the condensed ("exchange") form of the paper's Sec. 4.1
 // tableau: the m basic columns are unit vectors and are not stored, so a row
-// holds the N non-basic columns and the right-hand side, and a pivot swaps the
-// entering and leaving variables' columns in place.  Rows 0..m-1 are the
-// constraints, row m the objective: reduced costs d_j (entering candidates
-// have d_j > 0) and, in the rhs cell, minus the current objective value.
-// basis[i] / nonb[j] hold the Bland index of the variable of row i / column j.
+// holds the N non-basic columns, and a pivot swaps the entering and leaving
+// variables' columns in place.  The right-hand sides, the reduced costs
+// (entering candidates have d_j > 0) and minus the objective value are kept
+// beside it, always current.  basis[i] / nonb[j] hold the Bland index of the
+// variable of row i / column j.
 //
 // Per iteration (Sec. 4.1):
 //   Step 1 (pricing): argmax of d_j > eps_opt over eligible columns, ties to
@@ -24,15 +24,14 @@
 //     ties to the smallest Bland index of the basic variable; none: unbounded.
 //     Wavefront DPP reductions and ballots on (key, Bland index), then one
 //     slot per wavefront in LDS, stand in for the paper's Data[]/Indices[]
-//     arrays, with +inf as the "MAX" sentinel.
+//     arrays.
 //   Step 3 (pivot): pivot row / PE; every other row (objective included) minus
 //     a_ie times the new pivot row (Listing 1); the entering column becomes the
 //     leaving variable's column: 1/PE in the pivot row, -a_ie/PE elsewhere.
-//     Every element is rewritten with one fma, the same expression wherever
-//     the tableau lives, so results do not depend on the placement or the
-//     workgroup size.  Up to three consecutive pivots whose Steps 1-2 can be
-//     taken from the earlier pivots' vectors share one sweep (each element
-//     takes their rules in order, so results are those of separate sweeps).
+//     Every element takes one fma per pivot, the same expression wherever the
+//     tableau lives, so results do not depend on the placement or the
+//     workgroup size.  The updates of up to 32 pivots wait in a window of
+//     vectors and reach the tableau in one sweep on the matrix cores (flush).
 // Phase I (Sec. 4) maximises -(sum of artificials) when some row needs one;
 // basic artificials at zero are driven out and redundant rows dropped, then
 // Phase II prices c out over the basis and continues.
@@ -56,35 +55,15 @@ struct Ctrl {
     int next;
     int cnt;  // scratch tally (warm start)
     int pad[2];
-    double bnorm, cnorm;
-    T rv[16];
-    int ri[16];
-    int rp[16];
+    T rv[2][8];  // block_pick: one slot per wavefront, two sets used in turn
+    int ri[2][8];
+    int rp[2][8];
     double rd[16];
 };
 
 __device__ __forceinline__ int row_sense(int f) { return (f >> 1) & 3; }
 
 // ---- reductions ------------------------------------------------------------
-
-template <typename T, int NT>
-__device__ __forceinline__ void block_argmin(T &k1, int &k2, int &p, Ctrl<T> *sh)
-{
-    wave_argmin_dpp(k1, k2, p);
-    if constexpr (NT > 64) {
-        const int w = threadIdx.x >> 6;
-        if ((threadIdx.x & 63) == 0) { sh->rv[w] = k1; sh->ri[w] = k2; sh->rp[w] = p; }
-        __syncthreads();
-        k1 = sh->rv[0]; k2 = sh->ri[0]; p = sh->rp[0];
-#pragma unroll
-        for (int q = 1; q < NT / 64; ++q) {
-            T o1 = sh->rv[q];
-            int o2 = sh->ri[q];
-            if (o1 < k1 || (o1 == k1 && o2 < k2)) { k1 = o1; k2 = o2; p = sh->rp[q]; }
-        }
-        __syncthreads();
-    }
-}
 
 template <typename T, int NT>
 __device__ __forceinline__ double block_max(double v, Ctrl<T> *sh)
@@ -103,12 +82,44 @@ __device__ __forceinline__ double block_max(double v, Ctrl<T> *sh)
     return v;
 }
 
+// The lane of the wavefront with the largest (MAX) or least value among `on`
+// lanes, ties to the smallest `tie`; -1 when no lane is on.  Values are >= +0
+// and not NaN.
+template <bool MAX, typename T>
+__device__ __forceinline__ int wave_pick(bool on, T v, int tie)
+{
+    uint64_t mask = MAX ? wave_max_nonneg(on, v) : wave_min_nonneg(on, v);
+    if (!mask) return -1;
+    if (__builtin_expect(__popcll(mask) > 1, 0)) {
+        const bool in = (mask >> (threadIdx.x & 63)) & 1;
+        const int least = wave_min_i(in ? tie : BIG);
+        mask = ballot(in && tie == least);
+    }
+    return __builtin_ctzll(mask);
+}
+
+// A thread's own best candidate over the items it looks at.
+template <bool MAX, typename T>
+struct Best {
+    bool on = false;
+    T v = T(0);
+    int tie = BIG, idx = -1;
+    __device__ __forceinline__ void offer(bool ok, T x, int t, int i)
+    {
+        const bool take = ok && (!on || (MAX ? x > v : x < v) || (x == v && t < tie));
+        v = take ? x : v;
+        tie = take ? t : tie;
+        idx = take ? i : idx;
+        on |= ok;
+    }
+};
+
 // ---- one LP ------------------------------------------------------------------
 
 template <typename T, int NT>
 struct LP {
     // geometry
-    int m, n, N, C, ld, nart;
+    int m, n, N, ld, nart;
     int64_t k, ro, co;
     const double *A, *b, *c;
     const int32_t *rows;  // screened LP: row i is constraint rows[i] of the shared LP
@@ -123,196 +134,232 @@ struct LP {
     // LDS arrays
     Ctrl<T> *sh;
     int *basis, *nonb, *rowf, *colrow;
-    T *pcol, *prow;    // pivot column and (scaled) pivot row of a pivot
-    T *pcol2, *prow2;  // the same for the second pivot of a fused pair
-    T *pcol3, *prow3;  // and for the third of a fused triple
-    T *tab;  // LDS or HBM
+    T *rhs, *obj;  // current right-hand sides and reduced costs
+    T *np, *pr;    // window: negated pivot columns [K][m], scaled pivot rows [K][N]
+    int K, p;      // pivots the window holds at most, and now
+    T *tab;        // m x N in LDS or device memory, row stride ld, without the window's pivots
+    T z;           // right-hand side of the objective row (minus its value)
+    int turn;      // set of block_pick's slots
     // counters (uniform across the workgroup)
     int iters, it1, degp, cap;
 };
 
-// Step 3's vectors for a pivot on (l, e) of the current tableau: the scaled
-// pivot row prow_j = t_lj / PE (1 / PE in column e) and the pivot column
-// pcol_i = t_ie (0 for dropped rows; row m is the objective row).  No barrier.
+// The workgroup's best candidate (see wave_pick): its idx and, in `best`, its
+// value; -1 when there is none.  One barrier: the slots of consecutive calls
+// alternate.
+template <bool MAX, typename T, int NT>
+__device__ __forceinline__ int block_pick(LP<T, NT> &P, const Best<MAX, T> &c, T &best)
+{
+    const int lane = threadIdx.x & 63;
+    int src = wave_pick<MAX>(c.on, c.v, c.tie);
+    if constexpr (NT == 64) {
+        if (src < 0) return -1;
+        best = lane_get(c.v, src);
+        return lane_get(c.idx, src);
+    } else {
+        Ctrl<T> *sh = P.sh;
+        const int w = uniform(threadIdx.x >> 6), t = P.turn;
+        P.turn ^= 1;
+        if (lane == max(src, 0)) {
+            sh->rv[t][w] = c.v;
+            sh->ri[t][w] = c.tie;
+            sh->rp[t][w] = src < 0 ? -1 : c.idx;
+        }
+        __syncthreads();
+        const int q = lane & (NT / 64 - 1);
+        const T v = sh->rv[t][q];
+        const int tie = sh->ri[t][q], idx = sh->rp[t][q];
+        src = wave_pick<MAX>(lane < NT / 64 && idx >= 0, v, tie);
+        if (src < 0) return -1;
+        best = lane_get(v, src);
+        return lane_get(idx, src);
+    }
+}
+
+// The current tableau is
+//     t_ij = fma(np[p-1]_i, pr[p-1]_j, ... fma(np[0]_i, pr[0]_j, tab_ij) ...)
+// over the pivots of the window, oldest first.  A pivot's own row and column,
+// which it replaces rather than updates, go to tab at once and the window's
+// entries of that row and column become 0 (push), so that every entry takes
+// the operations of one sweep per pivot in their order, and the sweep (flush)
+// comes once per K pivots.
+//
+// Why a window: the sweep reads and writes the whole tableau, which for the
+// large LPs of a batch lives in device memory and bounds the kernel by the
+// rate of the memory behind the CU, while Steps 1 and 2 need the reduced costs
+// and right-hand sides (kept current in LDS), one column and one row.  K is
+// what the LP's LDS leaves (LdsLayout), at most kMaxWindow.  Measured against
+// three pivots per sweep on the vector units: 1,000 LPs of 500 x 500 FP64 23.5 ->
+// 7.3 ms (sixteen pivots per sweep; a sweep still takes half of an LP's time,
+// at the HBM copy rate), 10,000 uneven LPs of 10..300 FP64 140 -> 60 ms and FP32
+// 86 -> 40 ms (42 % sweeps, 37 % the device-memory latency of the one column and
+// row, 14 % the reductions), 2,000 LPs of 117 x 150 FP32 1.14 -> 0.63 ms.
+constexpr int kMaxWindow = 32;
+
+// f(i, a) for every live row i of this thread with its entry a of column e of
+// the current tableau; the negated column becomes slot p of np (0 in dropped
+// rows).  No barrier.
+template <typename T, int NT, typename F>
+__device__ __forceinline__ void column(LP<T, NT> &P, int e, F f)
+{
+    const int m = P.m, N = P.N, p = P.p;
+    T *np = P.np;
+    const T *pe = P.pr + e;
+    // Two rows a turn: their loads from the tableau are in flight together.
+    for (int i = threadIdx.x; i < m; i += 2 * NT) {
+        const int i1 = i + NT;
+        const bool two = i1 < m;
+        const int ib = two ? i1 : i;
+        T a0 = P.tab[int64_t(i) * P.ld + e], a1 = P.tab[int64_t(ib) * P.ld + e];
+#pragma unroll 4
+        for (int k = 0; k < p; ++k) {
+            const T s = pe[k * N];
+            a0 = fma(np[k * m + i], s, a0);
+            a1 = fma(np[k * m + ib], s, a1);
+        }
+        const bool l0 = !(P.rowf[i] & ROW_DEAD), l1 = two && !(P.rowf[ib] & ROW_DEAD);
+        np[p * m + i] = l0 ? -a0 : T(0);
+        if (two) np[p * m + i1] = l1 ? -a1 : T(0);
+        if (l0) f(i, a0);
+        if (l1) f(i1, a1);
+    }
+}
+
+// f(j, t) for every column j of this thread with its entry t of row l of the
+// current tableau.  No barrier.
+template <typename T, int NT, typename F>
+__device__ __forceinline__ void row(LP<T, NT> &P, int l, F f)
+{
+    const int m = P.m, N = P.N, p = P.p;
+    const T *pr = P.pr, *nl = P.np + l;
+    const T *tl = P.tab + int64_t(l) * P.ld;
+    for (int j = threadIdx.x; j < N; j += 2 * NT) {
+        const int j1 = j + NT;
+        const bool two = j1 < N;
+        const int jb = two ? j1 : j;
+        T t0 = tl[j], t1 = tl[jb];
+#pragma unroll 4
+        for (int k = 0; k < p; ++k) {
+            const T s = nl[k * m];
+            t0 = fma(s, pr[k * N + j], t0);
+            t1 = fma(s, pr[k * N + jb], t1);
+        }
+        f(j, t0);
+        if (two) f(j1, t1);
+    }
+}
+
+// Step 3 for the pivot on (l, e), whose negated column is slot p of np with
+// a barrier since: it becomes slot p of the window.  de, ne: the entering
+// column's reduced cost and variable.  Ends with a barrier only when the
+// workgroup is one wavefront; otherwise the next block_pick's or flush's
+// barrier comes before anything written here is read by another thread.
 template <typename T, int NT>
-__device__ __forceinline__ void pivot_vectors(LP<T, NT> &P, int l, int e, bool have_col = false)
+__device__ __forceinline__ void push(LP<T, NT> &P, int l, int e, T de, int ne)
 {
     const int tid = threadIdx.x;
-    const T *tab = P.tab;
-    const int ld = P.ld, C = P.C, m = P.m;
-    const T pe = tab[(int64_t)l * ld + e];
-    for (int j = tid; j < C; j += NT)
-        P.prow[j] = (j == e) ? T(1) / pe : tab[(int64_t)l * ld + j] / pe;
-    // have_col: Step 2 already stored rows 0..m-1 of the column (same thread
-    // per row), so only the objective row's entry is read here.
-    if (have_col) {
-        if (tid == 0) P.pcol[m] = tab[(int64_t)m * ld + e];
-    } else {
-        for (int i = tid; i <= m; i += NT)
-            P.pcol[i] = (i < m && (P.rowf[i] & ROW_DEAD)) ? T(0) : tab[(int64_t)i * ld + e];
+    const int m = P.m, N = P.N, p = P.p;
+    T *np = P.np + p * m, *pr = P.pr + p * N;
+    T *tl = P.tab + int64_t(l) * P.ld;
+    const T pe = -np[l];
+    const T prhs = P.rhs[l] / pe, pre = T(1) / pe;
+    const int bl = uniform(P.basis[l]);
+    row(P, l, [&](int j, T t) {
+        const T w = j == e ? pre : t / pe;
+        P.obj[j] = fma(-de, w, j == e ? T(0) : P.obj[j]);
+        pr[j] = w;
+        tl[j] = w;
+    });
+    P.z = fma(-de, prhs, P.z);
+    __syncthreads();  // row l and column e of the window have been read
+    for (int i = tid; i < m; i += NT) {
+        if (i == l) {
+            P.rhs[i] = prhs;
+            P.basis[i] = ne;
+        } else {
+            const T na = np[i];
+            P.rhs[i] = fma(na, prhs, P.rhs[i]);
+            P.tab[int64_t(i) * P.ld + e] = fma(na, pre, T(0));
+        }
     }
+    for (int k = tid; k <= p; k += NT) {
+        P.np[k * m + l] = T(0);
+        P.pr[k * N + e] = T(0);
+    }
+    if (tid == e % NT) P.nonb[e] = bl;
+    ++P.p;
+    if constexpr (NT == 64) __syncthreads();
 }
 
-// Step 3's sweep: every tableau entry t_ij becomes fma(-pcol_i, prow_j, t_ij)
-// -- with 0 in place of t_ij in the pivot column e, and prow_j itself in the
-// pivot row l -- for the pivot whose vectors are in P.prow / P.pcol; with
-// PAIR, the result then takes the second pivot's rule the same way (vectors
-// in P.prow2 / P.pcol2, row l2, column e2).  Lanes move 16 bytes (R entries)
-// per access, U accesses in flight -- all loads, then the fmas, then all
-// stores.  Rows start 16-byte aligned (tableau_ld); the entries past C up to
-// the row stride are padding, updated with whatever they hold and never read
-// back (the pivot-row buffers are padded the same way).
-//   * Wide rows (more than 64 U / 2 vectors): each wavefront takes whole rows.
-//   * Narrow rows: each wavefront takes RW = 64 U / nv rows at a time, its
-//     lanes spread over those rows' vectors (item q = lane + 64 u is vector
-//     q % nv of row q / nv), so a narrow tableau still keeps every lane busy
-//     and many accesses in flight -- with a tableau in device memory the
-//     sweep is bound by the accesses in flight, not by the bytes.
-// No barrier.
-template <typename T, int NT, int NP>
-__device__ __forceinline__ void sweep_impl(LP<T, NT> &P, int l1, int e1, int l2, int e2, int l3, int e3)
+// The sweep: tab takes the window's pivots.  Wavefront w takes row tiles w,
+// w + W, ... of sixteen rows, CT column tiles of sixteen a step, the next
+// step's loads in flight during this one's products and stores (a tableau in
+// device memory is bound by the bytes in flight): one 16 x 16 x 4 matrix
+// product per tile and four pivots, whose accumulation is the chain of fmas in
+// pivot order.  Operand A holds row 16 rt + lane % 16 and operand B column
+// 16 ct + lane % 16 of pivot 4 g + lane / 16.  Rows past m - 1 and columns past
+// N - 1 of the last tiles read the last row or column and are not written.
+// Starts and ends with a barrier.
+template <typename T, int NT>
+__device__ __forceinline__ void flush(LP<T, NT> &P)
 {
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    constexpr int W = NT / 64;
-    T *tab = P.tab;
-    const int ld = P.ld, C = P.C, m = P.m;
-    using V = T __attribute__((ext_vector_type(16 / sizeof(T))));
-    constexpr int R = 16 / int(sizeof(T));
-    constexpr int U = 4;
-    const int nv = (C + R - 1) / R;
-    const V *pr1 = reinterpret_cast<const V *>(P.prow);
-    const V *pr2 = reinterpret_cast<const V *>(P.prow2);
-    const V *pr3 = reinterpret_cast<const V *>(P.prow3);
-    // One entry's update: the first pivot's rule, then the second's and the
-    // third's (NP pivots).
-    auto upd = [&](int i, int j, T v, T w1, T f1, T w2, T f2, T w3, T f3) {
-        T t = (i == l1) ? w1 : fma(-f1, w1, (j == e1) ? T(0) : v);
-        if constexpr (NP >= 2) t = (i == l2) ? w2 : fma(-f2, w2, (j == e2) ? T(0) : t);
-        if constexpr (NP >= 3) t = (i == l3) ? w3 : fma(-f3, w3, (j == e3) ? T(0) : t);
-        return t;
+    constexpr int W = NT / 64, CT = 4, GMAX = kMaxWindow / 4;
+    const int lane = threadIdx.x & 63, wave = uniform(threadIdx.x >> 6), q = lane >> 4, c16 = lane & 15;
+    const int m = P.m, N = P.N, ld = P.ld, p = P.p, G = (p + 3) >> 2;
+    __syncthreads();
+    if (p == 0) return;
+    using Row = typename Tile<T>::V[CT];
+    auto place = [&](int rt, int v) { return P.tab + int64_t(min(16 * rt + mfma_row<T>(q, v), m - 1)) * ld; };
+    auto load = [&](int rt, int j0, Row &c) {
+        static_for<0, 4>([&](auto v) {
+            const T *at = place(rt, v);
+            static_for<0, CT>([&](auto t) {
+                if (j0 + 16 * t < N) c[t][int(v)] = at[min(j0 + 16 * t + c16, N - 1)];
+            });
+        });
     };
-    const int rw = (64 * U) / nv;  // rows per wavefront step on the narrow path
-    if (rw < 2) {
-        for (int i = wave; i <= m; i += W) {
-            V *row = reinterpret_cast<V *>(tab + (int64_t)i * ld);
-            const T f1 = P.pcol[i];
-            const T f2 = NP >= 2 ? P.pcol2[i] : T(0);
-            const T f3 = NP >= 3 ? P.pcol3[i] : T(0);
-            for (int k0 = lane; k0 < nv; k0 += 64 * U) {
-                V v[U], w1[U], w2[U], w3[U];
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    const int k = k0 + 64 * u;
-                    if (k < nv) {
-                        v[u] = row[k];
-                        w1[u] = pr1[k];
-                        if constexpr (NP >= 2) w2[u] = pr2[k];
-                        if constexpr (NP >= 3) w3[u] = pr3[k];
-                    }
+    int rt = wave, j0 = 0;
+    Row c;
+    T a[GMAX];
+    if (16 * rt < m) load(rt, j0, c);
+    while (16 * rt < m) {
+        int nrt = rt, nj0 = j0 + 16 * CT;
+        if (nj0 >= N) { nj0 = 0; nrt += W; }
+        Row cn;
+        if (16 * nrt < m) load(nrt, nj0, cn);
+        if (j0 == 0) {
+            const int ia = min(16 * rt + c16, m - 1);
+            static_for<0, GMAX>([&](auto g) {
+                const int k = 4 * g + q;
+                a[g] = T(0);
+                if (g < G) {
+                    const T x = P.np[min(k, p - 1) * m + ia];
+                    a[g] = k < p ? x : T(0);
                 }
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    const int k = k0 + 64 * u;
-#pragma unroll
-                    for (int r = 0; r < R; ++r)
-                        v[u][r] = upd(i, k * R + r, v[u][r], w1[u][r], f1, NP >= 2 ? w2[u][r] : T(0), f2,
-                                      NP >= 3 ? w3[u][r] : T(0), f3);
-                }
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    const int k = k0 + 64 * u;
-                    if (k < nv) row[k] = v[u];
-                }
-            }
+            });
         }
-        return;
+        static_for<0, GMAX>([&](auto g) {
+            if (g >= G) return;
+            const T *pk = P.pr + min(4 * g + q, p - 1) * N;
+            static_for<0, CT>([&](auto t) {
+                if (j0 + 16 * t < N) c[t] = Tile<T>::mma(a[g], pk[min(j0 + 16 * t + c16, N - 1)], c[t]);
+            });
+        });
+        static_for<0, 4>([&](auto v) {
+            const int i = 16 * rt + mfma_row<T>(q, v);
+            T *at = place(rt, v);
+            if (i < m)
+                static_for<0, CT>([&](auto t) {
+                    const int j = j0 + 16 * t + c16;
+                    if (j < N) at[j] = c[t][int(v)];
+                });
+        });
+        static_for<0, CT>([&](auto t) { c[t] = cn[t]; });
+        rt = nrt;
+        j0 = nj0;
     }
-    // Narrow rows: this lane's items, as (row offset, vector) pairs.
-    int ro[U], kv[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-        const int q = lane + 64 * u;
-        ro[u] = q / nv;
-        kv[u] = q - ro[u] * nv;
-        if (ro[u] >= rw) ro[u] = m + 1;  // past the last row: no item
-    }
-    for (int i0 = wave * rw; i0 <= m; i0 += W * rw) {
-        V v[U], w1[U], w2[U], w3[U];
-        T f1[U], f2[U], f3[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int i = i0 + ro[u];
-            if (i <= m) {
-                v[u] = reinterpret_cast<const V *>(tab + (int64_t)i * ld)[kv[u]];
-                w1[u] = pr1[kv[u]];
-                f1[u] = P.pcol[i];
-                if constexpr (NP >= 2) {
-                    w2[u] = pr2[kv[u]];
-                    f2[u] = P.pcol2[i];
-                }
-                if constexpr (NP >= 3) {
-                    w3[u] = pr3[kv[u]];
-                    f3[u] = P.pcol3[i];
-                }
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int i = i0 + ro[u];
-#pragma unroll
-            for (int r = 0; r < R; ++r)
-                v[u][r] = upd(i, kv[u] * R + r, v[u][r], w1[u][r], f1[u], NP >= 2 ? w2[u][r] : T(0),
-                              NP >= 2 ? f2[u] : T(0), NP >= 3 ? w3[u][r] : T(0), NP >= 3 ? f3[u] : T(0));
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int i = i0 + ro[u];
-            if (i <= m) reinterpret_cast<V *>(tab + (int64_t)i * ld)[kv[u]] = v[u];
-        }
-    }
-}
-
-template <typename T, int NT>
-__device__ __forceinline__ void sweep1(LP<T, NT> &P, int l, int e)
-{
-    sweep_impl<T, NT, 1>(P, l, e, -1, -1, -1, -1);
-}
-
-// Step 3: pivot on (l, e).  Every thread takes part; ends with a barrier.
-template <typename T, int NT>
-__device__ __forceinline__ void pivot(LP<T, NT> &P, int l, int e)
-{
-    pivot_vectors<T, NT>(P, l, e);
+    P.p = 0;
     __syncthreads();
-    sweep1<T, NT>(P, l, e);
-    if (threadIdx.x == 0) {
-        const int t = P.basis[l];
-        P.basis[l] = P.nonb[e];
-        P.nonb[e] = t;
-    }
-    __syncthreads();
-}
-
-// Two consecutive pivots, (l1, e1) and then (l2, e2) of the tableau that the
-// first leaves, in ONE pass over the tableau: every entry is read once,
-// updated by the first pivot's rule and then by the second's -- the same
-// operations in the same order as two separate sweeps, so the result is the
-// same bit for bit -- and written once, which halves the tableau traffic of
-// the pair.  P.prow / P.pcol hold the first pivot's vectors, P.prow2 / P.pcol2
-// the second's (computed from the first's without the tableau being swept).
-// No barrier.
-template <typename T, int NT>
-__device__ __forceinline__ void sweep2(LP<T, NT> &P, int l1, int e1, int l2, int e2)
-{
-    sweep_impl<T, NT, 2>(P, l1, e1, l2, e2, -1, -1);
-}
-
-// Three consecutive pivots in one pass (vectors in P.prow3 / P.pcol3 for the
-// third), the same operations in the same order as three sweeps.  No barrier.
-template <typename T, int NT>
-__device__ __forceinline__ void sweep3(LP<T, NT> &P, int l1, int e1, int l2, int e2, int l3, int e3)
-{
-    sweep_impl<T, NT, 3>(P, l1, e1, l2, e2, l3, e3);
 }
 
 // Steps 1-3 until a halt condition.  Returns ST_OPTIMAL, ST_UNBOUNDED or ST_ITER;
@@ -321,291 +368,155 @@ template <typename T, int NT>
 __device__ __forceinline__ int simplex(LP<T, NT> &P, T eps_opt, const SolveParams &prm, int *enter)
 {
     const int tid = threadIdx.x;
-    const int m = P.m, N = P.N, C = P.C, ld = P.ld, nm = P.n + P.m;
+    const int N = P.N, nm = P.n + P.m;
     const T tol_piv = T(prm.tol_piv);
-    T *tab = P.tab;
     int deg_run = 0;
     for (;;) {
         if (P.iters >= P.cap) return ST_ITER;
         const bool bland = prm.k_deg > 0 && deg_run >= prm.k_deg;
         // Step 1: entering column.
-        T k1 = t_inf<T>();
-        int k2 = BIG, p = -1;
-        const T *obj = tab + (int64_t)m * ld;
+        Best<true, T> in;
         const bool steep = prm.pricing == 1 && !bland;
         for (int j = tid; j < N; j += NT) {
-            const T d = obj[j];
+            const T d = P.obj[j];
             const int bj = P.nonb[j];
-            if (d > eps_opt && bj < nm) {
-                T key = bland ? T(0) : -d;
-                if (steep) {
-                    // Steepest edge: d_j^2 / (1 + sum of column j's squares
-                    // over the live rows); threads walk down their columns,
-                    // rows i summed into partial sum i mod R, the partial sums
-                    // then added in order -- the wavefront kernel's order, so
-                    // both kernels choose the same column.
-                    constexpr int R = 16 / int(sizeof(T));
-                    T acc[R];
+            const bool ok = d > eps_opt && bj < nm;
+            if (steep) {
+                if (!ok) continue;
+                // Steepest edge: d_j^2 / (1 + sum of column j's squares
+                // over the live rows); threads walk down their columns,
+                // rows i summed into partial sum i mod R, the partial sums
+                // then added in order -- the wavefront kernel's order, so
+                // both kernels choose the same column.
+                constexpr int R = 16 / int(sizeof(T));
+                T acc[R];
 #pragma unroll
-                    for (int q = 0; q < R; ++q) acc[q] = T(0);
-                    for (int i0 = 0; i0 < m; i0 += R) {
+                for (int q = 0; q < R; ++q) acc[q] = T(0);
+                for (int i0 = 0; i0 < P.m; i0 += R) {
 #pragma unroll
-                        for (int q = 0; q < R; ++q) {
-                            const int i = i0 + q;
-                            if (i < m && !(P.rowf[i] & ROW_DEAD)) {
-                                const T t = tab[(int64_t)i * ld + j];
-                                acc[q] = fma(t, t, acc[q]);
-                            }
+                    for (int q = 0; q < R; ++q) {
+                        const int i = i0 + q;
+                        if (i < P.m && !(P.rowf[i] & ROW_DEAD)) {
+                            const T t = P.tab[int64_t(i) * P.ld + j];
+                            acc[q] = fma(t, t, acc[q]);
                         }
                     }
-                    T w = T(1);
+                }
+                T w = T(1);
 #pragma unroll
-                    for (int q = 0; q < R; ++q) w += acc[q];
-                    key = -(d * d / w);
-                }
-                if (key < k1 || (key == k1 && bj < k2)) { k1 = key; k2 = bj; p = j; }
+                for (int q = 0; q < R; ++q) w += acc[q];
+                const T key = d * d / w;
+                in.offer(key == key, key, bj, j);
+            } else {
+                in.offer(ok, bland ? T(0) : d, bj, j);
             }
         }
-        block_argmin<T, NT>(k1, k2, p, P.sh);
-        if (p < 0) return ST_OPTIMAL;
-        const int e = p;
+        T key = T(0);
+        const int e = block_pick(P, in, key);
+        if (e < 0) return ST_OPTIMAL;
+        const T de = P.obj[e];
+        const int ne = uniform(P.nonb[e]);
         // Step 2: leaving row.
-        k1 = t_inf<T>(); k2 = BIG; p = -1;
-        const bool keep_col = prm.pricing != 1 && P.iters + 1 < P.cap;  // the look-ahead path reuses it
-        for (int i = tid; i < m; i += NT) {
-            if (P.rowf[i] & ROW_DEAD) {
-                if (keep_col) P.pcol[i] = T(0);
-                continue;
-            }
-            const T a = tab[(int64_t)i * ld + e];
-            if (keep_col) P.pcol[i] = a;
+        Best<false, T> out;
+        column(P, e, [&](int i, T a) {
             if (a > tol_piv) {
-                const T bi = tab[(int64_t)i * ld + N];
+                const T bi = P.rhs[i];
                 const T th = (bi > T(0) ? bi : T(0)) / a;
-                const int bb = P.basis[i];
-                if (th < k1 || (th == k1 && bb < k2)) { k1 = th; k2 = bb; p = i; }
+                out.offer(th == th, th, P.basis[i], i);
             }
-        }
-        block_argmin<T, NT>(k1, k2, p, P.sh);
-        if (p < 0) { *enter = P.nonb[e]; return ST_UNBOUNDED; }
-        if (k1 == T(0)) { ++deg_run; ++P.degp; } else deg_run = 0;
-        const int l = p;
-        if (prm.pricing == 1 || P.iters + 1 >= P.cap) {
-            pivot<T, NT>(P, l, e);
-            ++P.iters;
-            continue;
-        }
-        // Look one pivot ahead.  The tableau the pivot on (l, e) leaves is
-        // t'_ij = fma(-pcol_i, prow_j, t_ij) (0 for t_ij in column e; prow_j
-        // in row l), so Steps 1 and 2 of the next iteration need only the
-        // objective row, one column and the right-hand sides of it, computed
-        // here from the pivot's vectors without sweeping the tableau.  When
-        // they find a second pivot both go through one sweep (sweep2), or,
-        // when a third is found the same way, all three (sweep3).
-        pivot_vectors<T, NT>(P, l, e, true);
-        if (tid == 0) {
-            const int t = P.basis[l];
-            P.basis[l] = P.nonb[e];
-            P.nonb[e] = t;
-        }
-        __syncthreads();
-        // Step 1 of the next iteration (column e now holds the variable that
-        // left; its reduced cost -d_e / PE is negative, so e2 != e).
-        const bool bland2 = prm.k_deg > 0 && deg_run >= prm.k_deg;
-        const T fm = P.pcol[m];
-        k1 = t_inf<T>(); k2 = BIG; p = -1;
-        for (int j = tid; j < N; j += NT) {
-            const T d = fma(-fm, P.prow[j], (j == e) ? T(0) : obj[j]);
-            const int bj = P.nonb[j];
-            if (d > eps_opt && bj < nm) {
-                const T key = bland2 ? T(0) : -d;
-                if (key < k1 || (key == k1 && bj < k2)) { k1 = key; k2 = bj; p = j; }
-            }
-        }
-        block_argmin<T, NT>(k1, k2, p, P.sh);
-        const int e2 = p;
-        int l2 = -1;
-        if (e2 >= 0) {
-            // Step 2 of the next iteration.
-            k1 = t_inf<T>(); k2 = BIG; p = -1;
-            const T pc2 = P.prow[e2], prhs = P.prow[N];
-            for (int i = tid; i < m; i += NT) {
-                if (P.rowf[i] & ROW_DEAD) {
-                    P.pcol2[i] = T(0);
-                    continue;
-                }
-                const T a = (i == l) ? pc2 : fma(-P.pcol[i], pc2, tab[(int64_t)i * ld + e2]);
-                P.pcol2[i] = a;  // the second pivot's column, if this step finds a row
-                if (a > tol_piv) {
-                    const T bi = (i == l) ? prhs : fma(-P.pcol[i], prhs, tab[(int64_t)i * ld + N]);
-                    const T th = (bi > T(0) ? bi : T(0)) / a;
-                    const int bb = P.basis[i];
-                    if (th < k1 || (th == k1 && bb < k2)) { k1 = th; k2 = bb; p = i; }
-                }
-            }
-            block_argmin<T, NT>(k1, k2, p, P.sh);
-            l2 = p;
-        }
-        if (l2 < 0) {
-            // Optimal or unbounded after this pivot: it goes alone, and the
-            // next iteration reaches the same outcome.
-            sweep1<T, NT>(P, l, e);
-            __syncthreads();
-            ++P.iters;
-            continue;
-        }
-        if (k1 == T(0)) { ++deg_run; ++P.degp; } else deg_run = 0;
-        // The second pivot's vectors, entry by entry as pivot_vectors would
-        // compute them from the swept tableau.
-        {
-            const T pc2 = P.prow[e2];
-            const T pe2 = (l2 == l) ? pc2 : fma(-P.pcol[l2], pc2, tab[(int64_t)l2 * ld + e2]);
-            const T f2 = P.pcol[l2];
-            for (int j = tid; j < C; j += NT) {
-                const T t = (l2 == l) ? P.prow[j]
-                                      : fma(-f2, P.prow[j], (j == e) ? T(0) : tab[(int64_t)l2 * ld + j]);
-                P.prow2[j] = (j == e2) ? T(1) / pe2 : t / pe2;
-            }
-            // Rows 0..m-1 of the column were stored by Step 2 above.
-            if (tid == 0) {
-                const int i = m;
-                P.pcol2[i] = fma(-P.pcol[i], pc2, tab[(int64_t)i * ld + e2]);
-                const int t = P.basis[l2];
-                P.basis[l2] = P.nonb[e2];
-                P.nonb[e2] = t;
-            }
-        }
-        __syncthreads();
-        // Look a third pivot ahead the same way, from both pivots' vectors:
-        // entry (i, j) after the two pivots is
-        //   t'_ij  = (i == l ) ? prow_j  : fma(-pcol_i,  prow_j,  j == e  ? 0 : t_ij)
-        //   t''_ij = (i == l2) ? prow2_j : fma(-pcol2_i, prow2_j, j == e2 ? 0 : t'_ij).
-        int e3 = -1, l3 = -1;
-        if (P.iters + 2 < P.cap) {
-            const bool bland3 = prm.k_deg > 0 && deg_run >= prm.k_deg;
-            const T fm2 = P.pcol2[m];
-            k1 = t_inf<T>(); k2 = BIG; p = -1;
-            for (int j = tid; j < N; j += NT) {
-                const T d1 = fma(-fm, P.prow[j], (j == e) ? T(0) : obj[j]);
-                const T d = fma(-fm2, P.prow2[j], (j == e2) ? T(0) : d1);
-                const int bj = P.nonb[j];
-                if (d > eps_opt && bj < nm) {
-                    const T key = bland3 ? T(0) : -d;
-                    if (key < k1 || (key == k1 && bj < k2)) { k1 = key; k2 = bj; p = j; }
-                }
-            }
-            block_argmin<T, NT>(k1, k2, p, P.sh);
-            e3 = p;
-            if (e3 >= 0) {
-                k1 = t_inf<T>(); k2 = BIG; p = -1;
-                const T pc1 = P.prow[e3], pc2b = P.prow2[e3], prhs1 = P.prow[N], prhs2 = P.prow2[N];
-                for (int i = tid; i < m; i += NT) {
-                    if (P.rowf[i] & ROW_DEAD) {
-                        P.pcol3[i] = T(0);
-                        continue;
-                    }
-                    const T a1 = (i == l) ? pc1 : fma(-P.pcol[i], pc1, (e3 == e) ? T(0) : tab[(int64_t)i * ld + e3]);
-                    const T a = (i == l2) ? pc2b : fma(-P.pcol2[i], pc2b, (e3 == e2) ? T(0) : a1);
-                    P.pcol3[i] = a;
-                    if (a > tol_piv) {
-                        const T b1 = (i == l) ? prhs1 : fma(-P.pcol[i], prhs1, tab[(int64_t)i * ld + N]);
-                        const T bi = (i == l2) ? prhs2 : fma(-P.pcol2[i], prhs2, b1);
-                        const T th = (bi > T(0) ? bi : T(0)) / a;
-                        const int bb = P.basis[i];
-                        if (th < k1 || (th == k1 && bb < k2)) { k1 = th; k2 = bb; p = i; }
-                    }
-                }
-                block_argmin<T, NT>(k1, k2, p, P.sh);
-                l3 = p;
-            }
-        }
-        if (l3 < 0) {
-            sweep2<T, NT>(P, l, e, l2, e2);
-            __syncthreads();
-            P.iters += 2;
-            continue;
-        }
-        if (k1 == T(0)) { ++deg_run; ++P.degp; } else deg_run = 0;
-        // The third pivot's vectors.
-        {
-            const T pe3 = P.pcol3[l3];
-            for (int j = tid; j < C; j += NT) {
-                const T t1 = (l3 == l) ? P.prow[j]
-                                       : fma(-P.pcol[l3], P.prow[j], (j == e) ? T(0) : tab[(int64_t)l3 * ld + j]);
-                const T t = (l3 == l2) ? P.prow2[j] : fma(-P.pcol2[l3], P.prow2[j], (j == e2) ? T(0) : t1);
-                P.prow3[j] = (j == e3) ? T(1) / pe3 : t / pe3;
-            }
-            if (tid == 0) {
-                const int i = m;
-                const T a1 = fma(-P.pcol[i], P.prow[e3], (e3 == e) ? T(0) : tab[(int64_t)i * ld + e3]);
-                P.pcol3[i] = fma(-P.pcol2[i], P.prow2[e3], (e3 == e2) ? T(0) : a1);
-                const int t = P.basis[l3];
-                P.basis[l3] = P.nonb[e3];
-                P.nonb[e3] = t;
-            }
-        }
-        __syncthreads();
-        sweep3<T, NT>(P, l, e, l2, e2, l3, e3);
-        __syncthreads();
-        P.iters += 3;
+        });
+        T th = T(0);
+        const int l = block_pick(P, out, th);
+        if (l < 0) { *enter = ne; return ST_UNBOUNDED; }
+        if (th == T(0)) { ++deg_run; ++P.degp; } else deg_run = 0;
+        push(P, l, e, de, ne);
+        ++P.iters;
+        if (P.p == P.K || prm.pricing == 1) flush(P);
     }
 }
 
-// A1/A2: non-basic and basic index arrays, then the tableau rows
-// (sign-normalised so every rhs is >= 0, with a -1 surplus entry per >= row).
-// Returns whether this thread saw a non-finite entry of A or b.
+// A1/A2: non-basic and basic index arrays, then the tableau rows and right-hand
+// sides (sign-normalised so every rhs is >= 0, with a -1 surplus entry per >=
+// row).  Returns whether this thread saw a non-finite entry of A.
 template <typename T, int NT>
 __device__ __forceinline__ bool fill_tableau(LP<T, NT> &P)
 {
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = uniform(tid >> 6);
     constexpr int W = NT / 64;
-    const int m = P.m, n = P.n, N = P.N, C = P.C, ld = P.ld;
+    const int m = P.m, n = P.n, N = P.N, ld = P.ld;
     T *tab = P.tab;
+    P.p = 0;
     for (int j = tid; j < N; j += NT) P.nonb[j] = (j < n) ? j : n + P.colrow[j - n];
-    for (int i = tid; i < m; i += NT)
+    for (int i = tid; i < m; i += NT) {
         P.basis[i] = (row_sense(P.rowf[i]) == LE) ? n + i : n + m + i;
+        const double bi = P.b[P.row_of(i)];
+        P.rhs[i] = T((P.rowf[i] & ROW_NEG) ? -bi : bi);
+    }
     bool bad = false;
+    if (!P.rows) {
+        // A in flat order, eight loads a thread in flight; stepping by NT
+        // elements advances the row by NT / n and the column by NT % n.
+        constexpr int U = 8;
+        const int mn = m * n, dq = NT / n, dr = NT - dq * n;
+        int i = tid / n, j = tid - i * n;
+        for (int f0 = tid; f0 < mn; f0 += U * NT) {
+            double v[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) v[u] = f0 + u * NT < mn ? P.A[f0 + u * NT] : 0.0;
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (f0 + u * NT < mn) {
+                    bad |= !isfinite(v[u]);
+                    tab[int64_t(i) * ld + j] = T((P.rowf[i] & ROW_NEG) ? -v[u] : v[u]);
+                }
+                i += dq;
+                j += dr;
+                if (j >= n) { j -= n; ++i; }
+            }
+        }
+    }
     for (int i = wave; i < m; i += W) {
         const double sg = (P.rowf[i] & ROW_NEG) ? -1.0 : 1.0;
         const double *Ai = P.A + (int64_t)P.row_of(i) * n;
         T *row = tab + (int64_t)i * ld;
-        for (int j = lane; j < C; j += 64) {
-            double v;
-            if (j < n) {
+        if (P.rows)
+            for (int j = lane; j < n; j += 64) {
                 const double aij = Ai[j];
                 bad |= !isfinite(aij);
-                v = sg * aij;
-            } else if (j < N) {
-                v = (P.colrow[j - n] == i) ? -1.0 : 0.0;
-            } else {
-                v = sg * P.b[P.row_of(i)];
+                row[j] = T(sg * aij);
             }
-            row[j] = T(v);
-        }
+        for (int j = n + lane; j < N; j += 64) row[j] = (P.colrow[j - n] == i) ? T(-1) : T(0);
     }
     return bad;
 }
 
-// Phase II objective row: c priced out over the current basis, rows in order.
+// Phase II objective row: c priced out over the current basis, rows in order
+// (the window must be empty; slot 0 of np holds the basic costs meanwhile).
 template <typename T, int NT>
 __device__ __forceinline__ void price_out(LP<T, NT> &P)
 {
     const int tid = threadIdx.x;
-    const int m = P.m, n = P.n, N = P.N, C = P.C, ld = P.ld;
-    T *tab = P.tab;
+    const int m = P.m, n = P.n, N = P.N, ld = P.ld;
+    const T *tab = P.tab;
+    T *cbv = P.np;
     for (int i = tid; i < m; i += NT) {
         const int bv = P.basis[i];
-        P.pcol[i] = ((P.rowf[i] & ROW_DEAD) || bv >= n) ? T(0) : T(P.c[bv]);
+        cbv[i] = ((P.rowf[i] & ROW_DEAD) || bv >= n) ? T(0) : T(P.c[bv]);
     }
     __syncthreads();
-    for (int j = tid; j < C; j += NT) {
-        const int bj = (j < N) ? P.nonb[j] : BIG;
+    for (int j = tid; j < N; j += NT) {
+        const int bj = P.nonb[j];
         T acc = (bj < n) ? T(P.c[bj]) : T(0);
         for (int i = 0; i < m; ++i) {
-            const T cb = P.pcol[i];
+            const T cb = cbv[i];
             if (cb != T(0)) acc = fma(-cb, tab[(int64_t)i * ld + j], acc);
         }
-        tab[(int64_t)m * ld + j] = acc;
+        P.obj[j] = acc;
+    }
+    P.z = T(0);
+    for (int i = 0; i < m; ++i) {
+        const T cb = cbv[i];
+        if (cb != T(0)) P.z = fma(-cb, P.rhs[i], P.z);
     }
     __syncthreads();
 }
@@ -618,17 +529,18 @@ __device__ __forceinline__ void price_out(LP<T, NT> &P)
 // column not yet used (ties to the lower row).  Returns false -- the tableau
 // then holds some mix and must be rebuilt -- when the start basis is not square
 // on its tight rows or a pivot entry falls below tol_piv.  P.colrow (unused
-// without surplus columns) holds the tight-row flags.
+// without surplus columns) holds the tight-row flags; the objective row is
+// priced out afterwards.
 template <typename T, int NT>
 __device__ __forceinline__ bool crash(LP<T, NT> &P, const SolveArgs &a)
 {
     const int tid = threadIdx.x;
-    const int m = P.m, n = P.n, N = P.N, ld = P.ld;
-    const T *tab = P.tab;
+    const int m = P.m, n = P.n, N = P.N;
     const int32_t *wb = a.warm_basis + P.ro;
     Ctrl<T> *sh = P.sh;
     int *tight = P.colrow;
     for (int i = tid; i < m; i += NT) tight[i] = 1;
+    for (int j = tid; j < N; j += NT) P.obj[j] = T(0);
     if (tid == 0) { sh->bad = 0; sh->cnt = 0; }
     __syncthreads();
     int cnt = 0;  // basic structurals minus tight rows, this thread's share
@@ -642,33 +554,28 @@ __device__ __forceinline__ bool crash(LP<T, NT> &P, const SolveArgs &a)
     for (int i = tid; i < m; i += NT) cnt -= tight[i];
     if (cnt) atomicAdd(&sh->cnt, cnt);
     __syncthreads();
-    if (sh->bad || sh->cnt != 0) return false;
+    if (uniform(sh->bad) || uniform(sh->cnt) != 0) return false;
     const T tol_piv = T(a.prm.tol_piv);
-    for (int r = 0; r < m; ++r) {
-        const int v = wb[r];
+    for (int r = 0;; ++r) {
+        const int v = r < m ? uniform(wb[r]) : 0;
+        if (r == m || P.p == P.K) flush(P);
+        if (r == m) return true;
         if (v >= n) continue;
         // The structural's column (it must still be non-basic).
-        T k1 = T(0);
-        int k2 = BIG, p = -1;
-        for (int j = tid; j < N; j += NT)
-            if (P.nonb[j] == v) { k2 = j; p = j; }
-        block_argmin<T, NT>(k1, k2, p, sh);
-        if (p < 0) return false;
-        const int c = p;
+        T best = T(0);
+        Best<false, T> at;
+        for (int j = tid; j < N; j += NT) at.offer(P.nonb[j] == v, T(0), j, j);
+        const int c = block_pick(P, at, best);
+        if (c < 0) return false;
         // The unused tight row of largest |entry| (ties to the lower row).
-        k1 = t_inf<T>(); k2 = BIG; p = -1;
-        for (int i = tid; i < m; i += NT) {
-            if (!tight[i]) continue;
-            const T t = -fabs(tab[(int64_t)i * ld + c]);
-            if (t < k1 || (t == k1 && i < k2)) { k1 = t; k2 = i; p = i; }
-        }
-        block_argmin<T, NT>(k1, k2, p, sh);
-        if (p < 0 || !(-k1 > tol_piv)) return false;
-        if (tid == 0) tight[p] = 0;
-        pivot<T, NT>(P, p, c);
+        Best<true, T> big;
+        column(P, c, [&](int i, T t) { big.offer(tight[i] && t == t, T(fabs(t)), i, i); });
+        const int l = block_pick(P, big, best);
+        if (l < 0 || !(best > tol_piv)) return false;
+        push(P, l, c, T(0), v);
+        if (tid == l % NT) tight[l] = 0;
         ++P.iters;
     }
-    return true;
 }
 
 // Repair of the crashed start (objective row priced out): the dual simplex
@@ -678,54 +585,55 @@ __device__ __forceinline__ bool crash(LP<T, NT> &P, const SolveArgs &a)
 // basic Bland index); entering column: the smallest min(d_j, 0) / t_lj over
 // t_lj < -tol_piv (ties to the smallest Bland index) -- then the primal method
 // removes any d_j > eps_opt left.  A primal feasible start that is not dual
-// feasible goes straight to the primal method.  Returns the status, or -1
-// when the start is neither.
+// feasible goes straight to the primal method.  Returns kPrimal for the caller
+// to go on with the primal method, the status when the repair ends otherwise,
+// or -1 when the start is neither.
+constexpr int kPrimal = -2;
 template <typename T, int NT>
-__device__ __forceinline__ int dual_repair(LP<T, NT> &P, T eps_opt, T tol_dual, T tol_p, const SolveParams &prm, int *enter)
+__device__ __forceinline__ int dual_repair(LP<T, NT> &P, T tol_dual, T tol_p, const SolveParams &prm)
 {
     const int tid = threadIdx.x;
-    const int m = P.m, N = P.N, ld = P.ld, nm = P.n + P.m;
-    T *tab = P.tab;
+    const int m = P.m, N = P.N, nm = P.n + P.m;
     const T tol_piv = T(prm.tol_piv);
     Ctrl<T> *sh = P.sh;
     // Dual and primal feasibility of the start.
     double dmax = -1.0, pinf = -1.0;
     for (int j = tid; j < N; j += NT)
-        if (P.nonb[j] < nm && tab[(int64_t)m * ld + j] > tol_dual) dmax = 1.0;
+        if (P.nonb[j] < nm && P.obj[j] > tol_dual) dmax = 1.0;
     for (int i = tid; i < m; i += NT)
-        if (!(P.rowf[i] & ROW_DEAD) && tab[(int64_t)i * ld + N] < -tol_p) pinf = 1.0;
+        if (!(P.rowf[i] & ROW_DEAD) && P.rhs[i] < -tol_p) pinf = 1.0;
     const bool dual_bad = block_max<T, NT>(dmax, sh) > 0.0;
     const bool primal_bad = block_max<T, NT>(pinf, sh) > 0.0;
-    if (dual_bad) return primal_bad ? -1 : simplex<T, NT>(P, eps_opt, prm, enter);
+    if (dual_bad) return primal_bad ? -1 : kPrimal;
     for (;;) {
         if (P.iters >= P.cap) return ST_ITER;
-        T k1 = t_inf<T>();
-        int k2 = BIG, p = -1;
+        T best = T(0);
+        Best<true, T> out;
         for (int i = tid; i < m; i += NT) {
-            if (P.rowf[i] & ROW_DEAD) continue;
-            const T v = tab[(int64_t)i * ld + N];
-            const int bb = P.basis[i];
-            if (v < -tol_p && (v < k1 || (v == k1 && bb < k2))) { k1 = v; k2 = bb; p = i; }
+            const T v = P.rhs[i];
+            out.offer(!(P.rowf[i] & ROW_DEAD) && v < -tol_p, -v, P.basis[i], i);
         }
-        block_argmin<T, NT>(k1, k2, p, sh);
-        if (p < 0) break;  // primal feasible
-        const int l = p;
-        k1 = t_inf<T>(); k2 = BIG; p = -1;
-        for (int j = tid; j < N; j += NT) {
+        const int l = block_pick(P, out, best);
+        if (l < 0 || P.p == P.K) flush(P);
+        if (l < 0) return kPrimal;  // primal feasible
+        Best<false, T> in;
+        row(P, l, [&](int j, T t) {
             const int bj = P.nonb[j];
-            const T t = tab[(int64_t)l * ld + j];
             if (bj < nm && t < -tol_piv) {
-                const T d = tab[(int64_t)m * ld + j];
-                const T ratio = (d < T(0) ? d : T(0)) / t;
-                if (ratio < k1 || (ratio == k1 && bj < k2)) { k1 = ratio; k2 = bj; p = j; }
+                const T d = P.obj[j];
+                const T ratio = (d < T(0) ? d : T(0)) / t + T(0);  // +0 for -0
+                in.offer(ratio == ratio, ratio, bj, j);
             }
-        }
-        block_argmin<T, NT>(k1, k2, p, sh);
-        if (p < 0) return ST_INFEASIBLE;  // row l cannot reach its bound
-        pivot<T, NT>(P, l, p);
+        });
+        const int e = block_pick(P, in, best);
+        if (e < 0) return ST_INFEASIBLE;  // row l cannot reach its bound
+        const T de = P.obj[e];
+        const int ne = uniform(P.nonb[e]);
+        column(P, e, [](int, T) {});
+        __syncthreads();
+        push(P, l, e, de, ne);
         ++P.iters;
     }
-    return simplex<T, NT>(P, eps_opt, prm, enter);
 }
 
 // Solve LP k with the tableau at P.tab (LDS or HBM).  Row classification
@@ -733,9 +641,9 @@ __device__ __forceinline__ int dual_repair(LP<T, NT> &P, T eps_opt, T tol_dual, 
 template <typename T, int NT>
 __device__ __forceinline__ void solve_lp(LP<T, NT> &P, const SolveArgs &a, int placement)
 {
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = uniform(tid >> 6);
     constexpr int W = NT / 64;
-    const int m = P.m, n = P.n, N = P.N, C = P.C, ld = P.ld;
+    const int m = P.m, n = P.n, N = P.N, ld = P.ld;
     Ctrl<T> *sh = P.sh;
     T *tab = P.tab;
 
@@ -753,18 +661,19 @@ __device__ __forceinline__ void solve_lp(LP<T, NT> &P, const SolveArgs &a, int p
     const double cnorm = block_max<T, NT>(cmax, sh);
     const double bnorm = block_max<T, NT>(bmax, sh);
     int status = ST_OPTIMAL, enter = -1;
-    const bool invalid = sh->bad != 0;
+    const bool invalid = uniform(sh->bad) != 0;
     P.iters = 0; P.it1 = 0; P.degp = 0;
     P.cap = a.prm.max_iters > 0 ? a.prm.max_iters
-                                : 50 * (m + n + (m - sh->neq) + P.nart);
+                                : 50 * (m + n + (m - uniform(sh->neq)) + P.nart);
 
     // Warm start of an FP64 re-solve from the single-precision solve's final
     // basis of this LP (not for screened solves, whose repair the wavefront
     // kernel does): only when that solve ended optimal -- its status is still
     // in status[k] -- with few violated rows, and only for all-<= LPs.
-    bool warm = !invalid && a.warm_basis && !a.warm_rows && P.nart == 0 && a.status[P.k] == ST_OPTIMAL &&
-                !(a.warm_viol && a.warm_viol[P.k] > a.warm_max_viol);
-    if (warm && !crash<T, NT>(P, a)) {
+    // (FP64 only: single-precision solves start from the slack basis.)
+    bool warm = sizeof(T) == 8 && !invalid && a.warm_basis && !a.warm_rows && P.nart == 0 && uniform(a.status[P.k]) == ST_OPTIMAL &&
+                !(a.warm_viol && uniform(a.warm_viol[P.k]) > a.warm_max_viol);
+    if (sizeof(T) == 8 && warm && !crash<T, NT>(P, a)) {
         // The crash stopped part-way: rebuild the slack-basis tableau.
         warm = false;
         __syncthreads();
@@ -772,62 +681,33 @@ __device__ __forceinline__ void solve_lp(LP<T, NT> &P, const SolveArgs &a, int p
         P.iters = 0;
         __syncthreads();
     }
-    if (invalid) {
-        status = ST_INVALID;
-    } else {
-        if (P.nart > 0) {
-            // Phase I objective row: the sum of the artificial rows (in row order).
+    if (invalid) status = ST_INVALID;
+    // Phase I where some row needs an artificial, then Phase II.
+    for (int phase = P.nart > 0 ? 1 : 2; status == ST_OPTIMAL; phase = 2) {
+        T eps_opt;
+        if (phase == 1) {
+            // Objective row: the sum of the artificial rows (in row order).
             double dmax = 0.0;
-            for (int j = tid; j < C; j += NT) {
+            for (int j = tid; j < N; j += NT) {
                 T acc = T(0);
                 for (int i = 0; i < m; ++i)
                     if (row_sense(P.rowf[i]) != LE) acc += tab[(int64_t)i * ld + j];
-                tab[(int64_t)m * ld + j] = acc;
-                if (j < N) dmax = fmax(dmax, fabs(double(acc)));
+                P.obj[j] = acc;
+                dmax = fmax(dmax, fabs(double(acc)));
             }
+            P.z = T(0);
+            for (int i = 0; i < m; ++i)
+                if (row_sense(P.rowf[i]) != LE) P.z += P.rhs[i];
             __syncthreads();
-            const double dscale = fmax(1.0, block_max<T, NT>(dmax, sh));
-            const int r = simplex<T, NT>(P, T(a.prm.tol_opt * dscale), a.prm, &enter);
-            P.it1 = P.iters;
-            enter = -1;
-            if (r == ST_ITER) status = ST_ITER;
-            else if (r == ST_UNBOUNDED) status = ST_NUMERICAL;
-            else {
-                const double wstar = -double(tab[(int64_t)m * ld + N]);
-                if (wstar < -a.prm.tol_feas * (1.0 + bnorm)) status = ST_INFEASIBLE;
-            }
-            if (status == ST_OPTIMAL) {
-                // Drive basic artificials out, in row order; drop redundant rows.
-                const T tol_piv = T(a.prm.tol_piv);
-                for (int i = 0; i < m; ++i) {
-                    if (P.basis[i] < n + m) continue;
-                    T k1 = T(0);
-                    int k2 = BIG, p = -1;
-                    for (int j = tid; j < N; j += NT) {
-                        const int bj = P.nonb[j];
-                        if (bj < n + m && fabs(tab[(int64_t)i * ld + j]) > tol_piv && bj < k2) {
-                            k2 = bj; p = j;
-                        }
-                    }
-                    block_argmin<T, NT>(k1, k2, p, sh);
-                    if (p >= 0) {
-                        pivot<T, NT>(P, i, p);
-                    } else {
-                        if (tid == 0) P.rowf[i] |= ROW_DEAD;
-                        __syncthreads();
-                    }
-                }
-            }
-        }
-        if (status == ST_OPTIMAL) {
-            // Phase II objective row: c priced out over the current basis.
+            eps_opt = T(a.prm.tol_opt * fmax(1.0, block_max<T, NT>(dmax, sh)));
+        } else {
             price_out<T, NT>(P);
-            const T eps_opt = T(a.prm.tol_opt * fmax(1.0, cnorm));
-            if (warm) {
+            eps_opt = T(a.prm.tol_opt * fmax(1.0, cnorm));
+            if (sizeof(T) == 8 && warm) {
                 // Single-precision level for the start's reduced costs.
-                status = dual_repair<T, NT>(P, eps_opt, T(1e-5 * fmax(1.0, cnorm)),
-                                            T(a.prm.tol_feas * (1.0 + bnorm)), a.prm, &enter);
-                if (status < 0) {
+                const int r = dual_repair<T, NT>(P, T(1e-5 * fmax(1.0, cnorm)), T(a.prm.tol_feas * (1.0 + bnorm)),
+                                                 a.prm);
+                if (r == -1) {
                     // Neither primal nor dual feasible: solve from the slack basis.
                     warm = false;
                     __syncthreads();
@@ -835,28 +715,65 @@ __device__ __forceinline__ void solve_lp(LP<T, NT> &P, const SolveArgs &a, int p
                     P.iters = 0;
                     __syncthreads();
                     price_out<T, NT>(P);
-                    status = simplex<T, NT>(P, eps_opt, a.prm, &enter);
+                } else if (r != kPrimal) {
+                    status = r;
+                    break;
                 }
-            } else {
-                status = simplex<T, NT>(P, eps_opt, a.prm, &enter);
+            }
+        }
+        const int r = simplex<T, NT>(P, eps_opt, a.prm, &enter);
+        if (phase == 2) {
+            status = r;
+            break;
+        }
+        P.it1 = P.iters;
+        enter = -1;
+        if (r == ST_ITER) status = ST_ITER;
+        else if (r == ST_UNBOUNDED) status = ST_NUMERICAL;
+        else if (-double(P.z) < -a.prm.tol_feas * (1.0 + bnorm)) status = ST_INFEASIBLE;
+        if (status != ST_OPTIMAL) break;
+        // Drive basic artificials out, in row order; drop redundant rows.
+        const T tol_piv = T(a.prm.tol_piv);
+        for (int i = 0;; ++i) {
+            if (i == m || P.p == P.K) flush(P);
+            if (i == m) break;
+            __syncthreads();
+            if (uniform(P.basis[i]) < n + m) continue;
+            T best = T(0);
+            Best<false, T> at;
+            row(P, i, [&](int j, T t) {
+                const int bj = P.nonb[j];
+                at.offer(bj < n + m && fabs(t) > tol_piv, T(0), bj, j);
+            });
+            const int e = block_pick(P, at, best);
+            if (e >= 0) {
+                const T de = P.obj[e];
+                const int ne = uniform(P.nonb[e]);
+                column(P, e, [](int, T) {});
+                __syncthreads();
+                push(P, i, e, de, ne);
+            } else if (tid == i % NT) {
+                P.rowf[i] |= ROW_DEAD;
             }
         }
     }
 
     // A8: extraction.  x_j = rhs of the row where j is basic, else 0;
     // objective recomputed in FP64 from the input c by wavefront 0 in a fixed order.
-    T *xv = P.prow;  // reuse as an n-vector
+    __syncthreads();
+    T *xv = P.obj;  // reuse as an n-vector
     for (int j = tid; j < n; j += NT) xv[j] = T(0);
     __syncthreads();
     int nbs = 0;
     if (status == ST_OPTIMAL) {
         for (int i = tid; i < m; i += NT) {
             const int bv = P.basis[i];
-            if (bv < n && !(P.rowf[i] & ROW_DEAD)) xv[bv] = tab[(int64_t)i * ld + N];
+            if (bv < n && !(P.rowf[i] & ROW_DEAD)) xv[bv] = P.rhs[i];
         }
     }
     __syncthreads();
-    double *x = a.x + P.co;
+    const auto &out = *late_args();
+    double *x = out.x + P.co;
     if (status == ST_OPTIMAL) {
         for (int j = tid; j < n; j += NT) x[j] = double(xv[j]);
     } else {
@@ -878,12 +795,12 @@ __device__ __forceinline__ void solve_lp(LP<T, NT> &P, const SolveArgs &a, int p
             double objv = z;
             if (status == ST_UNBOUNDED) objv = __builtin_inf();
             else if (status != ST_OPTIMAL) objv = __builtin_nan("");
-            a.obj[P.k] = objv;
-            a.status[P.k] = status;
-            if (a.enter_out) a.enter_out[P.k] = (status == ST_UNBOUNDED) ? enter : -1;
-            if (a.stats) {
-                int32_t *st = a.stats + 8 * P.k;
-                if (a.refine_stats) {
+            out.obj[P.k] = objv;
+            out.status[P.k] = status;
+            if (out.enter_out) out.enter_out[P.k] = (status == ST_UNBOUNDED) ? enter : -1;
+            if (out.stats) {
+                int32_t *st = out.stats + 8 * P.k;
+                if (out.refine_stats) {
                     st[3] = warm ? 2 : 1;  // 2: started from the single-precision basis
                     st[4] = P.iters;
                 } else {
@@ -899,9 +816,9 @@ __device__ __forceinline__ void solve_lp(LP<T, NT> &P, const SolveArgs &a, int p
             }
         }
     }
-    if (a.basis_out)
+    if (out.basis_out)
         for (int i = tid; i < m; i += NT)
-            a.basis_out[P.ro + i] = (P.rowf[i] & ROW_DEAD) ? -1 : P.basis[i];
+            out.basis_out[P.ro + i] = (P.rowf[i] & ROW_DEAD) ? -1 : P.basis[i];
     __syncthreads();
 }
 
@@ -932,16 +849,18 @@ __device__ __forceinline__ void reject_lp(const LP<T, NT> &P, const SolveArgs &a
 }
 
 template <typename T, int NT>
-__global__ __launch_bounds__(NT) void simplex_kernel(SolveArgs a)
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void simplex_kernel(SolveArgs a)
 {
     extern __shared__ __align__(16) char smem[];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = uniform(tid >> 6);
     Ctrl<T> *sh = reinterpret_cast<Ctrl<T> *>(smem);
     const int64_t total = a.num_dev ? int64_t(a.id_base) + *a.num_dev : a.num;
+    // (Values every thread reads alike are made scalar: the loop bounds, strides
+    // and addresses built from them then cost no vector registers.)
     int64_t item = blockIdx.x;
     while (item < total) {
         if (tid == 0) sh->next = gridDim.x + (a.queue ? atomicAdd(a.queue, 1) : 0);
-        const int64_t k = a.ids ? int64_t(a.ids[item]) : item;
+        const int64_t k = a.ids ? int64_t(uniform(a.ids[item])) : item;
         LP<T, NT> P;
         P.k = k;
         if (a.um > 0) {
@@ -950,10 +869,10 @@ __global__ __launch_bounds__(NT) void simplex_kernel(SolveArgs a)
             P.ro = k * a.um;
             P.co = k * a.un;
         } else {
-            P.m = a.m[k]; P.n = a.n[k];
-            P.A = a.A + a.aoff[k];
-            P.ro = a.roff[k];
-            P.co = a.coff[k];
+            P.m = uniform(a.m[k]); P.n = uniform(a.n[k]);
+            P.A = a.A + uniform64(a.aoff[k]);
+            P.ro = uniform64(a.roff[k]);
+            P.co = uniform64(a.coff[k]);
         }
         P.b = a.b + P.ro;
         P.c = a.c + P.co;
@@ -969,22 +888,19 @@ __global__ __launch_bounds__(NT) void simplex_kernel(SolveArgs a)
             P.rows = a.row_subset ? a.row_subset + k * int64_t(P.m) : nullptr;
         }
         const int m = P.m, n = P.n;
-        LdsLayout L = lds_layout(m, n + m, sizeof(T), sizeof(Ctrl<T>));
+        // The arrays that row classification fills; the rest follow once the
+        // number of columns is known.
+        LdsLayout L = lds_layout(m, n, sizeof(T), sizeof(Ctrl<T>));
         P.sh = sh;
+        P.turn = 0;
         P.basis = reinterpret_cast<int *>(smem + L.basis);
-        P.nonb = reinterpret_cast<int *>(smem + L.nonb);
         P.rowf = reinterpret_cast<int *>(smem + L.rowf);
         P.colrow = reinterpret_cast<int *>(smem + L.colrow);
-        P.pcol = reinterpret_cast<T *>(smem + L.pcol);
-        P.prow = reinterpret_cast<T *>(smem + L.prow);
-        P.pcol2 = reinterpret_cast<T *>(smem + L.pcol2);
-        P.prow2 = reinterpret_cast<T *>(smem + L.prow2);
-        P.pcol3 = reinterpret_cast<T *>(smem + L.pcol3);
-        P.prow3 = reinterpret_cast<T *>(smem + L.prow3);
-        if (L.tab > int64_t(a.lds_bytes)) {
+        P.rhs = reinterpret_cast<T *>(smem + L.rhs);
+        if (L.window(2) > int64_t(a.lds_bytes)) {
             reject_lp<T, NT>(P, a);
             __syncthreads();
-            item = sh->next;
+            item = uniform(sh->next);
             __syncthreads();
             continue;
         }
@@ -1024,22 +940,33 @@ __global__ __launch_bounds__(NT) void simplex_kernel(SolveArgs a)
             if (lane == 0) { sh->ng = ng; sh->nart = nart; sh->neq = neq; }
         }
         __syncthreads();
-        P.N = n + sh->ng;
-        P.C = P.N + 1;
-        P.ld = tableau_ld(P.C, int(sizeof(T)));
-        P.nart = sh->nart;
-        const int64_t tab_bytes = int64_t(m + 1) * P.ld * int64_t(sizeof(T));
-        const bool in_lds = !a.force_hbm && L.tab + tab_bytes <= int64_t(a.lds_bytes);
-        if (!in_lds && (!a.scratch || tab_bytes > a.slot_bytes)) {
+        P.N = n + uniform(sh->ng);
+        P.nart = uniform(sh->nart);
+        L = lds_layout(m, P.N, sizeof(T), sizeof(Ctrl<T>));
+        P.nonb = reinterpret_cast<int *>(smem + L.nonb);
+        P.obj = reinterpret_cast<T *>(smem + L.obj);
+        P.pr = reinterpret_cast<T *>(smem + L.win);
+        // The tableau in LDS when it fits beside a window of at least two
+        // pivots; the window takes what is left, in whole groups of four.
+        const int64_t lds = a.lds_bytes, vec = int64_t(sizeof(T)) * (m + P.N);
+        const int64_t in_lds_bytes = int64_t(sizeof(T)) * m * lds_tab_ld(P.N);
+        const bool in_lds = !a.force_hbm && L.window(2) + in_lds_bytes <= lds;
+        P.ld = in_lds ? lds_tab_ld(P.N) : slot_tab_ld(P.N, int(sizeof(T)));
+        const int64_t room = (lds - L.win - (in_lds ? in_lds_bytes + 16 : 0)) / vec;
+        P.K = int(room >= kMaxWindow ? kMaxWindow : room >= 4 ? room & ~int64_t(3) : room < 1 ? 1 : room);
+        P.np = P.pr + int64_t(P.K) * P.N;
+        P.p = 0;
+        const int64_t slot_need = int64_t(sizeof(T)) * m * P.ld;
+        if (L.window(2) > lds || (!in_lds && (!a.scratch || slot_need > a.slot_bytes))) {
             reject_lp<T, NT>(P, a);
         } else if (in_lds) {
-            P.tab = reinterpret_cast<T *>(smem + L.tab);
+            P.tab = reinterpret_cast<T *>(smem + L.window(P.K));
             solve_lp<T, NT>(P, a, 3);
         } else {
             P.tab = reinterpret_cast<T *>(a.scratch + int64_t(blockIdx.x) * a.slot_bytes);
             solve_lp<T, NT>(P, a, 2);
         }
-        item = sh->next;
+        item = uniform(sh->next);
         __syncthreads();
     }
     drain_memory();

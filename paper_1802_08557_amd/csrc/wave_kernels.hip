@@ -723,16 +723,6 @@ __host__ __device__ constexpr int64_t wave_aux_bytes(int rb, bool gather)
 // registers, which leaves room for more wavefronts per SIMD.
 constexpr int NPF = 40;
 
-// The launch's arguments, read again from the kernel's argument segment where
-// they are used: held in scalar registers from the start they spill.
-typedef const __attribute__((address_space(4))) SolveArgs *LateArgs;
-__device__ __forceinline__ LateArgs late_args()
-{
-    LateArgs p = (LateArgs)__builtin_amdgcn_kernarg_segment_ptr();
-    asm volatile("" : "+s"(p));
-    return p;
-}
-
 // An LP's geometry and input data, loaded into registers ahead of its solve.
 template <int RB, int PFD>
 struct Fetch {

@@ -1,8 +1,11 @@
-"""Deferred pivots of the one-wavefront kernel: sizes at the edges of its 16 x 16
+"""Deferred pivots.  The one-wavefront kernel: sizes at the edges of its 16 x 16
 tiles and 64-row blocks, LPs of fewer and of many more pivots than one window
 holds, one and two phases.  Status and objective against the oracle; status,
 x, objective and pivot counts bit for bit against the workgroup kernel, whose
-sweeps are organised differently."""
+sweeps are organised differently.  The workgroup kernel: sizes at the edges of
+its tiles, wavefronts and thread counts, windows from three pivots (an LP whose
+vectors nearly fill LDS) to thirty-two, tableaux in LDS and in device memory,
+against the oracle and bit for bit against each other."""
 import numpy as np
 import pytest
 
@@ -55,3 +58,33 @@ def test_windows_match_workgroup_kernel(ctx, m, n, pricing):
             assert np.all(stats[:, 6] == 1)
         st3, obj3, x3, _ = solve(ctx, bt, pricing=pricing, precision=1)
         assert_parity(bt, st3, obj3, x3, ref)
+
+
+BLOCK_SIZES = [(1, 65), (130, 1), (15, 66), (65, 64), (129, 17), (97, 255), (256, 100), (128, 129), (257, 70)]
+
+
+@pytest.mark.parametrize("m,n", BLOCK_SIZES)
+def test_workgroup_windows(ctx, m, n):
+    for bt in (gaussian(6, m, n, 10 * m + n), W.phase1_batch(6, m, n, seed=3 * m + n)):
+        ref = oracle_solve(bt)
+        first = None
+        for kw in (dict(), dict(placement=2), dict(block_threads=64), dict(block_threads=128, placement=1),
+                   dict(block_threads=512, placement=2), dict(block_threads=256)):
+            st, obj, x, stats = solve(ctx, bt, **kw)
+            assert_parity(bt, st, obj, x, ref)
+            if first is None:
+                first = (st, obj, x, stats)
+            assert np.array_equal(st, first[0])
+            assert np.array_equal(obj, first[1], equal_nan=True) and np.array_equal(x, first[2], equal_nan=True)
+            assert np.array_equal(stats[:, :3], first[3][:, :3])
+        st, obj, x, _ = solve(ctx, bt, precision=1)
+        assert_parity(bt, st, obj, x, ref)
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+def test_workgroup_window_of_three(ctx, precision):
+    bt = W.uniform_batch(1, 1700, 1700, seed=5)
+    ref = oracle_solve(bt)
+    st, obj, x, stats = solve(ctx, bt, precision=precision)
+    assert_parity(bt, st, obj, x, ref)
+    assert np.all(stats[:, 6] == 2)
