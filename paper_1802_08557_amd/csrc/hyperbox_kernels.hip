@@ -3,9 +3,17 @@
 // For the box [lo_1, hi_1] x ... x [lo_n, hi_n] and a direction l, the maximum
 // of l.x over the box is sum_i l_i h_i with h_i = lo_i where l_i < 0 and
 // h_i = hi_i otherwise (paper, "Solving a Special Case of LP", Eq. (7)).  No
-// simplex is needed; the kernel is a streaming pass over the directions and is
-// bound by HBM bandwidth: one thread per direction, whose n-element rows are
-// read through the caches in full lines, summed in index order.
+// simplex is needed; the kernel is a streaming pass over the directions, bound
+// by HBM bandwidth.
+//
+// One wavefront takes 64 directions.  A thread that walked its own row would
+// read 64 rows' lines at once and evict them from L1 before their next element
+// is due; instead the wavefront reads the rows' elements in consecutive order,
+// every lane of a load next to the one before it, chooses h (and writes x) there
+// and stages l and h in LDS, from which lane k sums row k in index order.  Rows
+// of more than 32 elements go in equal chunks of at most 32 columns.  1e6 boxes
+// of n = 20 (480 MB read): 688 us with a thread per row, 130 us so -- 3.7 TB/s
+// against 4.8 TB/s for a copy.
 #include <stdint.h>
 
 #include "internal.h"
@@ -13,24 +21,63 @@
 namespace lpb {
 namespace {
 
-__global__ __launch_bounds__(256) void hyperbox_kernel(int64_t num, int n, const double *lo, const double *hi,
-                                                       const double *l, int shared_box, double *value,
-                                                       double *x)
+constexpr int kRows = 64;      // directions of a wavefront
+constexpr int kMaxCols = 32;   // columns staged at once
+constexpr int kInFlight = 10;  // elements of each array a lane loads ahead
+
+// LDS row stride: odd, so that 64 lanes reading one column meet at most two to a bank.
+__host__ __device__ constexpr int stage_ld(int cols) { return cols | 1; }
+
+__global__ __launch_bounds__(64) void hyperbox_kernel(int64_t num, int n, int cols, const double *lo,
+                                                      const double *hi, const double *l, int shared_box,
+                                                      double *value, double *x)
 {
-    const int64_t k = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (k >= num) return;
-    const double *lk = l + k * n;
-    const double *lok = shared_box ? lo : lo + k * n;
-    const double *hik = shared_box ? hi : hi + k * n;
-    double *xk = x ? x + k * n : nullptr;
+    extern __shared__ __align__(16) char smem[];
+    const int lane = threadIdx.x;
+    const int S = stage_ld(cols);
+    double *ls = reinterpret_cast<double *>(smem), *hs = ls + kRows * S;
+    const int64_t r0 = int64_t(blockIdx.x) * kRows;
+    const int rows = int(num - r0 < kRows ? num - r0 : kRows);
     double v = 0.0;
-    for (int i = 0; i < n; ++i) {
-        const double li = lk[i];
-        const double h = (li < 0.0) ? lok[i] : hik[i];
-        v = fma(li, h, v);
-        if (xk) xk[i] = h;
+    for (int c0 = 0; c0 < n; c0 += cols) {
+        const int cl = n - c0 < cols ? n - c0 : cols;
+        // Element e of the chunk is column e % cl of row e / cl; stepping by 64
+        // moves on 64 / cl rows and 64 % cl columns.
+        const int count = rows * cl, dq = 64 / cl, dr = 64 - dq * cl;
+        int r = lane / cl, c = lane - r * cl;
+        for (int e0 = lane; e0 < count; e0 += 64 * kInFlight) {
+            double lv[kInFlight], lov[kInFlight], hiv[kInFlight];
+            int at[kInFlight];
+            int64_t g[kInFlight];
+#pragma unroll
+            for (int u = 0; u < kInFlight; ++u) {
+                at[u] = e0 + 64 * u < count ? r * S + c : -1;
+                g[u] = (r0 + r) * n + c0 + c;
+                if (at[u] >= 0) {
+                    const int64_t b = shared_box ? c0 + c : g[u];
+                    lv[u] = l[g[u]];
+                    lov[u] = lo[b];
+                    hiv[u] = hi[b];
+                }
+                r += dq;
+                c += dr;
+                if (c >= cl) { c -= cl; ++r; }
+            }
+#pragma unroll
+            for (int u = 0; u < kInFlight; ++u) {
+                if (at[u] < 0) continue;
+                const double h = lv[u] < 0.0 ? lov[u] : hiv[u];
+                ls[at[u]] = lv[u];
+                hs[at[u]] = h;
+                if (x) x[g[u]] = h;
+            }
+        }
+        __syncthreads();
+        if (lane < rows)
+            for (int i = 0; i < cl; ++i) v = fma(ls[lane * S + i], hs[lane * S + i], v);
+        __syncthreads();
     }
-    value[k] = v;
+    if (lane < rows) value[r0 + lane] = v;
 }
 
 }  // namespace
@@ -39,8 +86,11 @@ hipError_t launch_hyperbox(int64_t num, int n, const double *lo, const double *h
                            int shared_box, double *value, double *x, hipStream_t s)
 {
     if (num <= 0) return hipSuccess;
-    hipLaunchKernelGGL(hyperbox_kernel, dim3(unsigned((num + 255) / 256)), dim3(256), 0, s, num, n, lo, hi, l,
-                       shared_box, value, x);
+    const int chunks = (n + kMaxCols - 1) / kMaxCols, cols = (n + chunks - 1) / chunks;
+    const int64_t blocks = (num + kRows - 1) / kRows;
+    if (blocks > INT32_MAX) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(hyperbox_kernel, dim3(unsigned(blocks)), dim3(64), 2 * kRows * stage_ld(cols) * sizeof(double),
+                       s, num, n, cols, lo, hi, l, shared_box, value, x);
     return hipGetLastError();
 }
 
