@@ -155,30 +155,26 @@ int certify_blocks_per_cu(int nt, int lds_bytes);
 int64_t certify_lds_bytes(int m, int n, bool with_matrix);
 hipError_t certify_configure(int max_lds);
 
-// Warm-start network (mlp_kernels.hip).  One strided BF16 GEMM with a fused
-// epilogue: C[i][j] = sum_k a[i*sai + k*sak] * b[k*sbk + j*sbj] (+ bias[j]);
-// zeroed where mask[i*ldc + j] <= 0 when mask is set; stored as FP32 (c32)
-// and/or rounded to BF16 (c16, after a ReLU when relu is set).
-struct MlpGemm {
-    int M, N, K;
-    const uint16_t *a, *b;
-    int64_t sai, sak, sbk, sbj;
-    const float *bias, *mask;
-    float *c32;
-    uint16_t *c16;
-    int64_t ldc;
-    int relu;
+// Warm-start network (mlp_kernels.hip).  The gradients of B labelled rows: FP32
+// parameters w32 and their BF16 copy w16 in, grad [LP_MLP_NUM_PARAMS] and
+// loss[0] out; the rest is scratch: dS, dZ2, dZ1 and the row losses in FP32
+// ([B][...]), and the BF16 operands of the dW products transposed, [columns][ldt]
+// with ldt >= B rounded up to 16.
+struct MlpTrain {
+    int64_t B, ldt;
+    const float *dirs, *w32;
+    const uint8_t *tight;
+    const uint16_t *w16;
+    float *ds, *dz2, *dz1, *row_loss;
+    uint16_t *xt, *h1t, *h2t, *dst, *dz2t, *dz1t;
+    float *grad, *loss;
 };
+hipError_t launch_mlp_grads(const MlpTrain &g, hipStream_t s);
 
 struct MlpAdam {
     float lr, wd, beta1, beta2, eps, bc1, bc2;  // bc = 1 - beta^t
 };
 
-hipError_t launch_mlp_gemm(const MlpGemm &g, hipStream_t s);
-hipError_t launch_to_bf16(const float *x, uint16_t *y, int64_t count, hipStream_t s);
-hipError_t launch_bce(const float *S, const uint8_t *Y, int64_t B, int O, float *dS, uint16_t *dS16,
-                      float *row_loss, float *loss, hipStream_t s);
-hipError_t launch_colsum(const float *dZ, int64_t B, int N, float *db, hipStream_t s);
 hipError_t launch_adamw(float *w, const float *g, float *m, float *v, uint16_t *w16, int64_t count,
                         const MlpAdam &h, const int64_t (&decay)[6], hipStream_t s);
 hipError_t launch_cast_params(const float *w, uint16_t *w16, int64_t count, hipStream_t s);

@@ -29,31 +29,30 @@ constexpr int64_t OW1 = 0, OB1 = OW1 + int64_t(H) * IN, OW2 = OB1 + H, OB2 = OW2
                   OW3 = OB2 + H, OB3 = OW3 + int64_t(OUT) * H;
 static_assert(OB3 + OUT == NP, "parameter layout");
 
-// Activation buffers of a batch of B rows (byte offsets into MlpState::act).
+// Scratch of a batch of B rows (byte offsets into MlpState::act; see MlpTrain).
 struct Act {
-    size_t x16, z1, h1, z2, h2, s, ds, ds16, dz2, dz216, dz1, dz116, rowloss, total;
+    size_t ds, dz2, dz1, rowloss, xt, h1t, h2t, dst, dz2t, dz1t, total;
 };
 
-Act act_layout(int64_t B, bool train)
+Act act_layout(int64_t B, int64_t ldt)
 {
-    auto al = [](size_t v) { return (v + 255) & ~size_t(255); };
     Act a{};
     size_t o = 0;
-    a.x16 = o; o += al(size_t(B) * IN * 2);
-    a.h1 = o; o += al(size_t(B) * H * 2);
-    a.h2 = o; o += al(size_t(B) * H * 2);
-    a.s = o; o += al(size_t(B) * OUT * 4);
-    if (train) {
-        a.z1 = o; o += al(size_t(B) * H * 4);
-        a.z2 = o; o += al(size_t(B) * H * 4);
-        a.ds = o; o += al(size_t(B) * OUT * 4);
-        a.ds16 = o; o += al(size_t(B) * OUT * 2);
-        a.dz2 = o; o += al(size_t(B) * H * 4);
-        a.dz216 = o; o += al(size_t(B) * H * 2);
-        a.dz1 = o; o += al(size_t(B) * H * 4);
-        a.dz116 = o; o += al(size_t(B) * H * 2);
-        a.rowloss = o; o += al(size_t(B) * 4);
-    }
+    auto take = [&o](size_t bytes) {
+        const size_t at = o;
+        o += (bytes + 255) & ~size_t(255);
+        return at;
+    };
+    a.ds = take(size_t(B) * OUT * 4);
+    a.dz2 = take(size_t(B) * H * 4);
+    a.dz1 = take(size_t(B) * H * 4);
+    a.rowloss = take(size_t(B) * 4);
+    a.xt = take(size_t(ldt) * IN * 2);
+    a.h1t = take(size_t(ldt) * H * 2);
+    a.h2t = take(size_t(ldt) * H * 2);
+    a.dst = take(size_t(ldt) * OUT * 2);
+    a.dz2t = take(size_t(ldt) * H * 2);
+    a.dz1t = take(size_t(ldt) * H * 2);
     a.total = o;
     return a;
 }
@@ -89,92 +88,37 @@ int reset_state(lp_ctx *ctx, hipStream_t s)
     return LP_OK;
 }
 
-lpb::MlpGemm gemm(int M, int N, int K, const uint16_t *a, int64_t sai, int64_t sak, const uint16_t *b,
-                  int64_t sbk, int64_t sbj)
-{
-    lpb::MlpGemm g;
-    std::memset(&g, 0, sizeof g);
-    g.M = M; g.N = N; g.K = K;
-    g.a = a; g.sai = sai; g.sak = sak;
-    g.b = b; g.sbk = sbk; g.sbj = sbj;
-    g.ldc = N;
-    return g;
-}
-
-// Forward pass of B rows; training keeps Z1, Z2 for the backward pass.
-int forward(lp_ctx *ctx, int64_t B, const float *dirs, const Act &L, bool train, hipStream_t s)
+// Gradients of B labelled rows into grad and the mean loss into loss[0].
+int loss_grads(lp_ctx *ctx, int64_t B, const float *dirs, const uint8_t *tight, float *grad, float *loss,
+               hipStream_t s)
 {
     lpb::MlpState &M = ctx->mlp;
-    char *act = M.act.as<char>();
-    const uint16_t *w16 = M.params16.as<uint16_t>();
-    const float *w = M.params.as<float>();
-    uint16_t *x16 = reinterpret_cast<uint16_t *>(act + L.x16);
-    uint16_t *h1 = reinterpret_cast<uint16_t *>(act + L.h1);
-    uint16_t *h2 = reinterpret_cast<uint16_t *>(act + L.h2);
-    HIP_TRY(lpb::launch_to_bf16(dirs, x16, B * IN, s));
-    const int Bi = int(B);
-    lpb::MlpGemm g = gemm(Bi, H, IN, x16, IN, 1, w16 + OW1, 1, IN);
-    g.bias = w + OB1;
-    g.c32 = train ? reinterpret_cast<float *>(act + L.z1) : nullptr;
-    g.c16 = h1;
-    g.relu = 1;
-    HIP_TRY(lpb::launch_mlp_gemm(g, s));
-    g = gemm(Bi, H, H, h1, H, 1, w16 + OW2, 1, H);
-    g.bias = w + OB2;
-    g.c32 = train ? reinterpret_cast<float *>(act + L.z2) : nullptr;
-    g.c16 = h2;
-    g.relu = 1;
-    HIP_TRY(lpb::launch_mlp_gemm(g, s));
-    g = gemm(Bi, OUT, H, h2, H, 1, w16 + OW3, 1, H);
-    g.bias = w + OB3;
-    g.c32 = reinterpret_cast<float *>(act + L.s);
-    HIP_TRY(lpb::launch_mlp_gemm(g, s));
-    return LP_OK;
-}
-
-// Loss and gradients of B labelled rows into M.grads and M.misc[0].
-int loss_grads(lp_ctx *ctx, int64_t B, const float *dirs, const uint8_t *tight, hipStream_t s)
-{
-    lpb::MlpState &M = ctx->mlp;
-    const Act L = act_layout(B, true);
+    const int64_t ldt = (B + 15) & ~int64_t(15);
+    const Act L = act_layout(B, ldt);
     int rc = M.act.ensure(L.total);
     if (rc != LP_OK) return rc;
-    rc = forward(ctx, B, dirs, L, true, s);
-    if (rc != LP_OK) return rc;
-    char *act = M.act.as<char>();
-    auto f32 = [&](size_t o) { return reinterpret_cast<float *>(act + o); };
-    auto b16 = [&](size_t o) { return reinterpret_cast<uint16_t *>(act + o); };
-    const uint16_t *w16 = M.params16.as<uint16_t>();
-    float *gr = M.grads.as<float>();
-    const int Bi = int(B);
-    HIP_TRY(lpb::launch_bce(f32(L.s), tight, B, OUT, f32(L.ds), b16(L.ds16), f32(L.rowloss), M.misc.as<float>(), s));
-    // dW3 = q(dS)^T H2, db3 = column sums of dS.
-    lpb::MlpGemm g = gemm(OUT, H, Bi, b16(L.ds16), 1, OUT, b16(L.h2), H, 1);
-    g.c32 = gr + OW3;
-    HIP_TRY(lpb::launch_mlp_gemm(g, s));
-    HIP_TRY(lpb::launch_colsum(f32(L.ds), B, OUT, gr + OB3, s));
-    // dZ2 = (q(dS) q(W3)) * [Z2 > 0].
-    g = gemm(Bi, H, OUT, b16(L.ds16), OUT, 1, w16 + OW3, H, 1);
-    g.mask = f32(L.z2);
-    g.c32 = f32(L.dz2);
-    g.c16 = b16(L.dz216);
-    HIP_TRY(lpb::launch_mlp_gemm(g, s));
-    // dW2 = q(dZ2)^T H1, db2.
-    g = gemm(H, H, Bi, b16(L.dz216), 1, H, b16(L.h1), H, 1);
-    g.c32 = gr + OW2;
-    HIP_TRY(lpb::launch_mlp_gemm(g, s));
-    HIP_TRY(lpb::launch_colsum(f32(L.dz2), B, H, gr + OB2, s));
-    // dZ1 = (q(dZ2) q(W2)) * [Z1 > 0].
-    g = gemm(Bi, H, H, b16(L.dz216), H, 1, w16 + OW2, H, 1);
-    g.mask = f32(L.z1);
-    g.c32 = f32(L.dz1);
-    g.c16 = b16(L.dz116);
-    HIP_TRY(lpb::launch_mlp_gemm(g, s));
-    // dW1 = q(dZ1)^T X, db1.
-    g = gemm(H, IN, Bi, b16(L.dz116), 1, H, b16(L.x16), IN, 1);
-    g.c32 = gr + OW1;
-    HIP_TRY(lpb::launch_mlp_gemm(g, s));
-    HIP_TRY(lpb::launch_colsum(f32(L.dz1), B, H, gr + OB1, s));
+    auto f32 = [&](size_t o) { return M.act.as<float>(o); };
+    auto b16 = [&](size_t o) { return M.act.as<uint16_t>(o); };
+    lpb::MlpTrain g;
+    g.B = B;
+    g.ldt = ldt;
+    g.dirs = dirs;
+    g.w32 = M.params.as<float>();
+    g.tight = tight;
+    g.w16 = M.params16.as<uint16_t>();
+    g.ds = f32(L.ds);
+    g.dz2 = f32(L.dz2);
+    g.dz1 = f32(L.dz1);
+    g.row_loss = f32(L.rowloss);
+    g.xt = b16(L.xt);
+    g.h1t = b16(L.h1t);
+    g.h2t = b16(L.h2t);
+    g.dst = b16(L.dst);
+    g.dz2t = b16(L.dz2t);
+    g.dz1t = b16(L.dz1t);
+    g.grad = grad;
+    g.loss = loss;
+    HIP_TRY(lpb::launch_mlp_grads(g, s));
     return LP_OK;
 }
 
@@ -275,11 +219,8 @@ int lp_mlp_grads(lp_ctx *ctx, int64_t B, const float *dirs, const uint8_t *tight
     if (!tight) return fail(LP_ERR_ARG, "tight is NULL");
     DeviceGuard dg(ctx->device);
     hipStream_t s = static_cast<hipStream_t>(stream);
-    rc = loss_grads(ctx, B, dirs, tight, s);
-    if (rc != LP_OK) return rc;
-    if (grad_out) HIP_TRY(hipMemcpyAsync(grad_out, ctx->mlp.grads.p, size_t(NP) * 4, hipMemcpyDeviceToDevice, s));
-    if (loss_out) HIP_TRY(hipMemcpyAsync(loss_out, ctx->mlp.misc.p, 4, hipMemcpyDeviceToDevice, s));
-    return LP_OK;
+    return loss_grads(ctx, B, dirs, tight, grad_out ? grad_out : ctx->mlp.grads.as<float>(),
+                      loss_out ? loss_out : ctx->mlp.misc.as<float>(), s);
 }
 
 int lp_mlp_train_step(lp_ctx *ctx, int64_t B, const float *dirs, const uint8_t *tight, float lr,
@@ -293,9 +234,9 @@ int lp_mlp_train_step(lp_ctx *ctx, int64_t B, const float *dirs, const uint8_t *
     if (!(lr >= 0.f) || !(weight_decay >= 0.f)) return fail(LP_ERR_ARG, "lr and weight_decay must be >= 0");
     DeviceGuard dg(ctx->device);
     hipStream_t s = static_cast<hipStream_t>(stream);
-    rc = loss_grads(ctx, B, dirs, tight, s);
-    if (rc != LP_OK) return rc;
     lpb::MlpState &M = ctx->mlp;
+    rc = loss_grads(ctx, B, dirs, tight, M.grads.as<float>(), loss_out ? loss_out : M.misc.as<float>(), s);
+    if (rc != LP_OK) return rc;
     M.step += 1;
     lpb::MlpAdam h;
     h.lr = lr;
@@ -308,7 +249,6 @@ int lp_mlp_train_step(lp_ctx *ctx, int64_t B, const float *dirs, const uint8_t *
     const int64_t decay[6] = {OW1, OB1, OW2, OB2, OW3, OB3};
     HIP_TRY(lpb::launch_adamw(M.params.as<float>(), M.grads.as<float>(), M.adam_m.as<float>(),
                               M.adam_v.as<float>(), M.params16.as<uint16_t>(), NP, h, decay, s));
-    if (loss_out) HIP_TRY(hipMemcpyAsync(loss_out, M.misc.p, 4, hipMemcpyDeviceToDevice, s));
     return LP_OK;
 }
 

@@ -1,20 +1,16 @@
 // mlp_kernels.hip -- the warm-start scoring network (20 -> 256 -> 256 -> 120,
 // ReLU) on the matrix cores: BF16 operands, FP32 accumulation.
 //
-// Every layer, forward and backward, is one launch of a strided GEMM
-//     C[i][j] = sum_k A(i, k) B(k, j),  A(i, k) = a[i*sai + k*sak],
-//                                        B(k, j) = b[k*sbk + j*sbj]
-// on v_mfma_f32_16x16x16_bf16 tiles, one wavefront per 32 x 32 block of C,
-// followed by a fused epilogue (bias, ReLU mask of the forward activation,
-// FP32 and/or rounded BF16 stores).  The products are small (the widest is
-// 256 x 256), so one strided kernel serves the six backward shapes too; the
-// forward reads both operands along k with 8-byte loads.
+// All products run on v_mfma_f32_16x16x16_bf16 tiles.  Inference is one kernel
+// (all layers and the top-k of a tile of 64 directions).  A training step's
+// gradients are two: everything that is local to a row of the batch -- forward
+// pass, loss, dS, dZ2, dZ1 -- for a tile of sixteen rows in one workgroup with
+// the activations in LDS (mlp_rows_kernel), and everything that sums over the
+// batch -- dW, bias gradients, mean loss (mlp_sums_kernel).  Every reduction
+// runs in a fixed order, so a training step is deterministic.
 //
-// The remaining kernels are elementwise or row-wise: FP32 -> BF16 input
-// conversion, the logistic loss and its gradient, bias gradients (column sums
-// in a fixed order), AdamW on the FP32 master weights with a fresh BF16 copy,
-// and the per-direction top-k of the scores.  Every reduction runs in a fixed
-// order, so a training step is deterministic.
+// The remaining kernels: AdamW on the FP32 master weights with a fresh BF16
+// copy, and a standalone per-direction top-k.
 #include <math.h>
 #include <stdint.h>
 
@@ -32,144 +28,6 @@ __device__ __forceinline__ uint16_t to_bf16(float f)
     uint32_t u = __float_as_uint(f);
     u += 0x7FFFu + ((u >> 16) & 1u);
     return uint16_t(u >> 16);
-}
-
-// Four consecutive-k operand values of row (or column) r, k = k0 .. k0 + 3;
-// zero outside [0, R) x [0, K).
-__device__ __forceinline__ s16x4 load_frag(const uint16_t *p, int r, int R, int64_t sr, int k0, int K,
-                                           int64_t sk)
-{
-    s16x4 v = {0, 0, 0, 0};
-    if (r >= R) return v;
-    const uint16_t *q = p + int64_t(r) * sr;
-    if (sk == 1 && k0 + 3 < K && ((int64_t(r) * sr + k0) & 3) == 0) {
-        const uint2 w = *reinterpret_cast<const uint2 *>(q + k0);
-        v[0] = short(w.x & 0xFFFF);
-        v[1] = short(w.x >> 16);
-        v[2] = short(w.y & 0xFFFF);
-        v[3] = short(w.y >> 16);
-        return v;
-    }
-#pragma unroll
-    for (int t = 0; t < 4; ++t)
-        if (k0 + t < K) v[t] = short(q[int64_t(k0 + t) * sk]);
-    return v;
-}
-
-__global__ __launch_bounds__(64) void gemm_bf16_kernel(MlpGemm g)
-{
-    const int lane = threadIdx.x;
-    const int i0 = blockIdx.x * 32, j0 = blockIdx.y * 32;
-    const int r16 = lane & 15, kq = (lane >> 4) * 4;
-    f32x4 acc[2][2];
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int b = 0; b < 2; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
-    for (int k0 = 0; k0 < g.K; k0 += 16) {
-        // A fragment: row i0 + 16 a + (lane % 16), k = k0 + 4 (lane / 16) + t;
-        // B fragment: column j0 + 16 b + (lane % 16), same k.
-        s16x4 fa[2], fb[2];
-#pragma unroll
-        for (int a = 0; a < 2; ++a) fa[a] = load_frag(g.a, i0 + 16 * a + r16, g.M, g.sai, k0 + kq, g.K, g.sak);
-#pragma unroll
-        for (int b = 0; b < 2; ++b) fb[b] = load_frag(g.b, j0 + 16 * b + r16, g.N, g.sbj, k0 + kq, g.K, g.sbk);
-#pragma unroll
-        for (int a = 0; a < 2; ++a)
-#pragma unroll
-            for (int b = 0; b < 2; ++b)
-                acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(fa[a], fb[b], acc[a][b], 0, 0, 0);
-    }
-    // D layout: lane holds column (lane % 16), rows 4 (lane / 16) + t.
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int b = 0; b < 2; ++b) {
-            const int j = j0 + 16 * b + r16;
-            if (j >= g.N) continue;
-            const float bj = g.bias ? g.bias[j] : 0.f;
-#pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                const int i = i0 + 16 * a + kq + t;
-                if (i >= g.M) continue;
-                float v = acc[a][b][t] + bj;
-                const int64_t o = int64_t(i) * g.ldc + j;
-                if (g.mask && !(g.mask[o] > 0.f)) v = 0.f;
-                if (g.c32) g.c32[o] = v;
-                if (g.c16) g.c16[o] = to_bf16(g.relu ? fmaxf(v, 0.f) : v);
-            }
-        }
-}
-
-__global__ void to_bf16_kernel(const float *x, uint16_t *y, int64_t count)
-{
-    const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (i < count) y[i] = to_bf16(x[i]);
-}
-
-// dS = (sigmoid(S) - Y) / (B * O) in FP32 and BF16; row_loss[b] = sum over the
-// row of softplus(S) - Y S (summed in column order).
-__global__ __launch_bounds__(256) void bce_kernel(const float *S, const uint8_t *Y, int64_t B, int O, float *dS,
-                                                  uint16_t *dS16, float *row_loss)
-{
-    // One wavefront per row: lane j takes outputs j, j + 64, ...; the row's
-    // loss is reduced over the lanes by a fixed butterfly.
-    const int lane = threadIdx.x & 63;
-    const int64_t b = int64_t(blockIdx.x) * (blockDim.x >> 6) + (threadIdx.x >> 6);
-    if (b >= B) return;
-    const float inv = 1.0f / (float(B) * float(O));
-    float acc = 0.f;
-    for (int j = lane; j < O; j += 64) {
-        const int64_t o = b * O + j;
-        const float s = S[o];
-        const float y = Y[o] ? 1.f : 0.f;
-        const float sp = fmaxf(s, 0.f) + log1pf(expf(-fabsf(s)));
-        acc += sp - y * s;
-        const float sg = 1.f / (1.f + expf(-s));
-        const float d = (sg - y) * inv;
-        dS[o] = d;
-        dS16[o] = to_bf16(d);
-    }
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
-    if (lane == 0) row_loss[b] = acc;
-}
-
-// Mean of the row losses, one workgroup, fixed order: each thread sums a
-// strided slice, then a tree over the threads.
-__global__ __launch_bounds__(256) void mean_kernel(const float *row_loss, int64_t B, int O, float *out)
-{
-    __shared__ double part[256];
-    double s = 0.0;
-    for (int64_t b = threadIdx.x; b < B; b += 256) s += double(row_loss[b]);
-    part[threadIdx.x] = s;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if (int(threadIdx.x) < w) part[threadIdx.x] += part[threadIdx.x + w];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) *out = float(part[0] / (double(B) * O));
-}
-
-// db[j] = sum_b dZ[b][j]: 64 columns per workgroup; thread (c, p) sums rows
-// p, p + 16, ... of column c in order, then the sixteen partial sums are added
-// in order of p.
-__global__ __launch_bounds__(1024) void colsum_kernel(const float *dZ, int64_t B, int N, float *db)
-{
-    __shared__ float part[16][64];
-    const int c = threadIdx.x & 63, p = threadIdx.x >> 6;
-    const int j = blockIdx.x * 64 + c;
-    float s = 0.f;
-    if (j < N)
-        for (int64_t b = p; b < B; b += 16) s += dZ[b * N + j];
-    part[p][c] = s;
-    __syncthreads();
-    if (p == 0 && j < N) {
-        float t = part[0][c];
-#pragma unroll
-        for (int q = 1; q < 16; ++q) t += part[q][c];
-        db[j] = t;
-    }
 }
 
 // AdamW on the FP32 master copy; decay[i] = 1 for weights, 0 for biases.
@@ -227,8 +85,8 @@ __global__ __launch_bounds__(64) void topk_kernel(const float *S, int64_t B, int
 // All three layers and the top-k for a tile of 64 directions in one workgroup
 // of four wavefronts: the input tile and both hidden activations stay in LDS
 // (BF16), the weights stream from L2 as MFMA fragments.  The products, their
-// k order and the epilogues are those of gemm_bf16_kernel, so the scores are
-// the same bits as the layer-by-layer path.
+// k order and the epilogues are those of the training forward pass, so the
+// scores are the same bits.
 
 // ---- Top-k by a bitonic sort over the wavefront ------------------------------
 // Key of entry t with score v: the score's bits mapped to an order-preserving
@@ -468,36 +326,307 @@ __global__ __launch_bounds__(256) void mlp_infer_kernel(const float *dirs, int64
     }
 }
 
+// ---- Training: gradients of a batch ---------------------------------------------
+// What limited the layer-by-layer form (one launch per product, elementwise step
+// and column sum, fifteen in all) was latency: the dW products ran on 8 to 64
+// wavefronts whose lanes gathered every operand two bytes at a time, 100 us
+// each for 512 rows.  The row kernel writes the BF16 operands of the dW
+// products transposed (the rows of a tile are neighbours in a lane's
+// accumulators, so that is one 8-byte store), and both kernels load several k
+// steps ahead.  512 rows: 410 us before, 37 us now (26 and 9 us and the launches).
+
+// Weight fragment of a product that contracts over a weight matrix's rows:
+// column j of a [K][cols] BF16 matrix, k = k0 .. k0+3 (zero past K).
+__device__ __forceinline__ s16x4 wfrag_t(const uint16_t *w, int j, int cols, int K, int k0)
+{
+    s16x4 v = {0, 0, 0, 0};
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+        if (k0 + t < K) v[t] = short(w[int64_t(k0 + t) * cols + j]);
+    return v;
+}
+
+constexpr int kRowsT = 16;  // batch rows of a workgroup
+constexpr int kWavesT = 8;  // wavefronts of a workgroup
+constexpr int kNT = kHid / 16 / kWavesT;  // column tiles of a hidden layer per wavefront
+static_assert(16 * kWavesT >= kOut, "one column tile of the scores per wavefront");
+constexpr int kLdo = 136;   // row stride of the dS tile: 120 columns, 0 up to 128
+
+// acc[j] = the wavefront's NT column tiles of act[16][K] * W, fragments by
+// frag(column tile, k0), eight k steps loaded ahead.
+template <int NT, int K, typename F>
+__device__ __forceinline__ void rows_product(const uint16_t *act, int lda, F frag, f32x4 (&acc)[NT])
+{
+    constexpr int STEPS = (K + 15) / 16, U = 8;
+    const int lane = threadIdx.x & 63, r16 = lane & 15, kq = (lane >> 4) * 4;
+#pragma unroll
+    for (int j = 0; j < NT; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int s0 = 0; s0 < STEPS; s0 += U) {
+        s16x4 fb[U][NT];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int j = 0; j < NT; ++j)
+                if (s0 + u < STEPS) fb[u][j] = frag(j, 16 * (s0 + u) + kq);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (s0 + u >= STEPS) continue;
+            const s16x4 fa = *reinterpret_cast<const s16x4 *>(act + r16 * lda + 16 * (s0 + u) + kq);
+#pragma unroll
+            for (int j = 0; j < NT; ++j)
+                acc[j] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(fa, fb[u][j], acc[j], 0, 0, 0);
+        }
+    }
+}
+
+__device__ __forceinline__ s16x4 pack4(const float (&v)[4])
+{
+    return s16x4{short(to_bf16(v[0])), short(to_bf16(v[1])), short(to_bf16(v[2])), short(to_bf16(v[3]))};
+}
+
+// Rows b0 .. b0 + 15 of the batch.  D layout of a tile: lane holds column
+// lane % 16 and rows 4 (lane / 16) + t, so the masks of the backward pass stay
+// in the lanes that computed Z1 and Z2.
+__global__ __launch_bounds__(64 * kWavesT) void mlp_rows_kernel(MlpTrain g)
+{
+    __shared__ __align__(16) uint16_t x16[kRowsT * kLdx];
+    __shared__ __align__(16) uint16_t ha[kRowsT * kLdh];   // H1, then dZ2
+    __shared__ __align__(16) uint16_t hb[kRowsT * kLdh];   // H2
+    __shared__ __align__(16) uint16_t d16[kRowsT * kLdo];  // dS
+    __shared__ __align__(16) float sc[kRowsT * 128];       // S
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int r16 = lane & 15, kq = (lane >> 4) * 4;
+    const int64_t B = g.B, b0 = int64_t(blockIdx.x) * kRowsT;
+    const uint16_t *w16 = g.w16;
+    const float *w32 = g.w32;
+    for (int e = tid; e < kRowsT * 32; e += 64 * kWavesT) {
+        const int r = e >> 5, k = e & 31;
+        x16[r * kLdx + k] = to_bf16((b0 + r < B && k < kIn) ? g.dirs[(b0 + r) * kIn + k] : 0.f);
+    }
+    for (int e = tid; e < kRowsT * kLdo; e += 64 * kWavesT) d16[e] = 0;
+    __syncthreads();
+    // Four rows of column c of a BF16 tile into the transposed array (rows past
+    // the batch stay within its padding and are not read).
+    const int64_t bt = b0 + kq;
+    auto put_t = [&](uint16_t *t, int c, s16x4 v) { *reinterpret_cast<s16x4 *>(t + c * g.ldt + bt) = v; };
+    if (tid < 4 * kIn) {
+        const int c = tid >> 2, q = (tid & 3) * 4;
+        s16x4 v;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) v[t] = short(x16[(q + t) * kLdx + c]);
+        *reinterpret_cast<s16x4 *>(g.xt + c * g.ldt + b0 + q) = v;
+    }
+    // A hidden layer's epilogue: bias, ReLU, BF16; returns which values pass.
+    auto hidden = [&](const f32x4 (&acc)[kNT], const float *bias, uint16_t *h, uint16_t *ht) {
+        uint32_t pass = 0;
+#pragma unroll
+        for (int j = 0; j < kNT; ++j) {
+            const int c = (kNT * wave + j) * 16 + r16;
+            float v[4];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const float z = acc[j][t] + bias[c];
+                pass |= uint32_t(z > 0.f) << (4 * j + t);
+                v[t] = fmaxf(z, 0.f);
+                h[(kq + t) * kLdh + c] = to_bf16(v[t]);
+            }
+            put_t(ht, c, pack4(v));
+        }
+        return pass;
+    };
+    f32x4 acc[kNT];
+    rows_product<kNT, kIn>(x16, kLdx, [&](int j, int k0) { return wfrag(w16 + kOW1, (kNT * wave + j) * 16 + r16, kHid, kIn, k0); }, acc);
+    const uint32_t pass1 = hidden(acc, w32 + kOB1, ha, g.h1t);
+    __syncthreads();
+    rows_product<kNT, kHid>(ha, kLdh, [&](int j, int k0) { return wfrag(w16 + kOW2, (kNT * wave + j) * 16 + r16, kHid, kHid, k0); }, acc);
+    const uint32_t pass2 = hidden(acc, w32 + kOB2, hb, g.h2t);
+    __syncthreads();
+    {
+        f32x4 s[1];
+        rows_product<1, kHid>(hb, kLdh, [&](int j, int k0) { return wfrag(w16 + kOW3, (wave + j) * 16 + r16, kOut, kHid, k0); }, s);
+        const int c = wave * 16 + r16;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) sc[(kq + t) * 128 + c] = s[0][t] + (c < kOut ? w32[kOB3 + c] : 0.f);
+    }
+    __syncthreads();
+    // Loss and dS = (sigmoid(S) - Y) / (B * O): one wavefront per row, lane j
+    // takes outputs j and j + 64, the row's loss by a fixed butterfly.
+    const float inv = 1.0f / (float(B) * float(kOut));
+    for (int r = wave; r < kRowsT; r += kWavesT) {
+        const int64_t b = b0 + r;
+        if (b >= B) break;
+        float loss = 0.f;
+        for (int j = lane; j < kOut; j += 64) {
+            const float s = sc[r * 128 + j];
+            const float y = g.tight[b * kOut + j] ? 1.f : 0.f;
+            const float sp = fmaxf(s, 0.f) + log1pf(expf(-fabsf(s)));
+            loss += sp - y * s;
+            const float sg = 1.f / (1.f + expf(-s));
+            const float d = (sg - y) * inv;
+            g.ds[b * kOut + j] = d;
+            d16[r * kLdo + j] = to_bf16(d);
+        }
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) loss += __shfl_xor(loss, off);
+        if (lane == 0) g.row_loss[b] = loss;
+    }
+    __syncthreads();
+    for (int e = tid; e < 4 * kOut; e += 64 * kWavesT) {
+        const int c = e >> 2, q = (e & 3) * 4;
+        s16x4 v;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) v[t] = short(d16[(q + t) * kLdo + c]);
+        *reinterpret_cast<s16x4 *>(g.dst + c * g.ldt + b0 + q) = v;
+    }
+    // dZ = (upstream * W) where the ReLU passed: FP32 for the bias gradient,
+    // BF16 for the products.
+    auto masked = [&](const f32x4 (&a)[kNT], uint32_t pass, float *z32, uint16_t *z, uint16_t *zt) {
+#pragma unroll
+        for (int j = 0; j < kNT; ++j) {
+            const int c = (kNT * wave + j) * 16 + r16;
+            float v[4];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                v[t] = (pass >> (4 * j + t)) & 1 ? a[j][t] + 0.f : 0.f;
+                if (bt + t < B) z32[(bt + t) * kHid + c] = v[t];
+                if (z) z[(kq + t) * kLdh + c] = to_bf16(v[t]);
+            }
+            put_t(zt, c, pack4(v));
+        }
+    };
+    rows_product<kNT, kOut>(d16, kLdo, [&](int j, int k0) { return wfrag_t(w16 + kOW3, (kNT * wave + j) * 16 + r16, kHid, kOut, k0); }, acc);
+    masked(acc, pass2, g.dz2, ha, g.dz2t);
+    __syncthreads();
+    rows_product<kNT, kHid>(ha, kLdh, [&](int j, int k0) { return wfrag_t(w16 + kOW2, (kNT * wave + j) * 16 + r16, kHid, kHid, k0); }, acc);
+    masked(acc, pass1, g.dz1, nullptr, g.dz1t);
+}
+
+// One 16 x 16 tile of a dW product over the batch: C[i][j] = sum_b a[i][b] w[j][b]
+// with both operands transposed ([rows][ldt], b contiguous), in order of b.
+__device__ __forceinline__ void dw_tile(const uint16_t *a, int M, const uint16_t *w, int N, int64_t ldt, int64_t B,
+                                        int ti, int tj, float *C)
+{
+    const int lane = threadIdx.x & 63, r16 = lane & 15, kq = (lane >> 4) * 4;
+    const int i = 16 * ti + r16, j = 16 * tj + r16;
+    const uint16_t *pa = a + int64_t(i < M ? i : M - 1) * ldt, *pw = w + int64_t(j < N ? j : N - 1) * ldt;
+    // Past the batch: whole groups of four are skipped, a last partial one masked.
+    auto frag = [&](const uint16_t *p, int64_t k) {
+        s16x4 v = {0, 0, 0, 0};
+        if (k < B) v = *reinterpret_cast<const s16x4 *>(p + k);
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+            if (k + t >= B) v[t] = 0;
+        return v;
+    };
+    constexpr int U = 8;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    for (int64_t k0 = 0; k0 < B; k0 += 16 * U) {
+        s16x4 fa[U], fw[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            fa[u] = frag(pa, k0 + 16 * u + kq);
+            fw[u] = frag(pw, k0 + 16 * u + kq);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (k0 + 16 * u < B) acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(fa[u], fw[u], acc, 0, 0, 0);
+    }
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+        const int row = 16 * ti + kq + t;
+        if (row < M && j < N) C[int64_t(row) * N + j] = acc[t] + 0.f;
+    }
+}
+
+// db[j] = sum_b dZ[b][j] for 64 columns: sixteen partial sums over rows p, p + 16,
+// ... in order, then the partial sums in order of p.
+__device__ __forceinline__ void column_sums(const float *dZ, int64_t B, int N, int j0, float *db, float (&part)[16][64])
+{
+    const int c = threadIdx.x & 63, j = j0 + c;
+    float s[4] = {0.f, 0.f, 0.f, 0.f};
+    const int p0 = (threadIdx.x >> 6) * 4;
+    constexpr int U = 8;  // sixteen-row steps loaded ahead
+    if (j < N)
+        for (int64_t b0 = p0; b0 < B; b0 += 16 * U) {
+            float v[U][4];
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const int64_t b = b0 + 16 * u + q;
+                    v[u][q] = dZ[(b < B ? b : B - 1) * N + j];
+                }
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    if (b0 + 16 * u + q < B) s[q] += v[u][q];
+        }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) part[p0 + q][c] = s[q];
+    __syncthreads();
+    if (threadIdx.x < 64 && j < N) {
+        float t = part[0][c];
+#pragma unroll
+        for (int q = 1; q < 16; ++q) t += part[q][c];
+        db[j] = t;
+    }
+}
+
+// Tiles of the three dW products (four wavefronts to a workgroup), then the bias
+// gradients (64 columns to a workgroup), then the mean loss.
+constexpr int kTilesH = kHid / 16, kTilesO = (kOut + 15) / 16, kTilesI = (kIn + 15) / 16;
+constexpr int kDw2 = kTilesH * kTilesH, kDw3 = kTilesO * kTilesH, kDw1 = kTilesH * kTilesI;
+constexpr int kDwBlocks = (kDw2 + kDw3 + kDw1) / 4;
+constexpr int kColsH = kHid / 64, kColsO = (kOut + 63) / 64;
+static_assert((kDw2 + kDw3 + kDw1) % 4 == 0 && kHid % 64 == 0, "whole workgroups of tiles");
+
+__global__ __launch_bounds__(256) void mlp_sums_kernel(MlpTrain g)
+{
+    __shared__ union {
+        float cols[16][64];
+        double mean[256];
+    } sh;
+    const int tid = threadIdx.x;
+    int blk = blockIdx.x;
+    if (blk < kDwBlocks) {
+        int t = 4 * blk + (tid >> 6);
+        if (t < kDw2) dw_tile(g.dz2t, kHid, g.h1t, kHid, g.ldt, g.B, t / kTilesH, t % kTilesH, g.grad + kOW2);
+        else if ((t -= kDw2) < kDw3) dw_tile(g.dst, kOut, g.h2t, kHid, g.ldt, g.B, t / kTilesH, t % kTilesH, g.grad + kOW3);
+        else {
+            t -= kDw3;
+            dw_tile(g.dz1t, kHid, g.xt, kIn, g.ldt, g.B, t / kTilesI, t % kTilesI, g.grad + kOW1);
+        }
+        return;
+    }
+    blk -= kDwBlocks;
+    if (blk < kColsH) return column_sums(g.dz2, g.B, kHid, 64 * blk, g.grad + kOB2, sh.cols);
+    blk -= kColsH;
+    if (blk < kColsH) return column_sums(g.dz1, g.B, kHid, 64 * blk, g.grad + kOB1, sh.cols);
+    blk -= kColsH;
+    if (blk < kColsO) return column_sums(g.ds, g.B, kOut, 64 * blk, g.grad + kOB3, sh.cols);
+    // Mean of the row losses: each thread sums a strided slice, then a tree.
+    double s = 0.0;
+    for (int64_t b = tid; b < g.B; b += 256) s += double(g.row_loss[b]);
+    sh.mean[tid] = s;
+    __syncthreads();
+    for (int w = 128; w > 0; w >>= 1) {
+        if (tid < w) sh.mean[tid] += sh.mean[tid + w];
+        __syncthreads();
+    }
+    if (tid == 0) *g.loss = float(sh.mean[0] / (double(g.B) * kOut));
+}
+
 }  // namespace
 
-hipError_t launch_mlp_gemm(const MlpGemm &g, hipStream_t s)
+hipError_t launch_mlp_grads(const MlpTrain &g, hipStream_t s)
 {
-    if (g.M <= 0 || g.N <= 0) return hipSuccess;
-    dim3 grid((g.M + 31) / 32, (g.N + 31) / 32);
-    hipLaunchKernelGGL(gemm_bf16_kernel, grid, dim3(64), 0, s, g);
-    return hipGetLastError();
-}
-
-hipError_t launch_to_bf16(const float *x, uint16_t *y, int64_t count, hipStream_t s)
-{
-    if (count <= 0) return hipSuccess;
-    hipLaunchKernelGGL(to_bf16_kernel, dim3(unsigned((count + 255) / 256)), dim3(256), 0, s, x, y, count);
-    return hipGetLastError();
-}
-
-hipError_t launch_bce(const float *S, const uint8_t *Y, int64_t B, int O, float *dS, uint16_t *dS16,
-                      float *row_loss, float *loss, hipStream_t s)
-{
-    hipLaunchKernelGGL(bce_kernel, dim3(unsigned((B + 3) / 4)), dim3(256), 0, s, S, Y, B, O, dS, dS16, row_loss);
+    hipLaunchKernelGGL(mlp_rows_kernel, dim3(unsigned((g.B + kRowsT - 1) / kRowsT)), dim3(64 * kWavesT), 0, s,
+                       g);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(mean_kernel, dim3(1), dim3(256), 0, s, row_loss, B, O, loss);
-    return hipGetLastError();
-}
-
-hipError_t launch_colsum(const float *dZ, int64_t B, int N, float *db, hipStream_t s)
-{
-    hipLaunchKernelGGL(colsum_kernel, dim3(unsigned((N + 63) / 64)), dim3(1024), 0, s, dZ, B, N, db);
+    hipLaunchKernelGGL(mlp_sums_kernel, dim3(kDwBlocks + 2 * kColsH + kColsO + 1), dim3(256), 0, s, g);
     return hipGetLastError();
 }
 
