@@ -288,6 +288,7 @@ __global__ __launch_bounds__(NT) void certify_kernel(CertArgs a)
                     yt[t] = ct;
                     perm[t] = t;
                 }
+                __syncthreads();  // the block is complete
                 double am = 0.0;
                 for (int e = tid; e < K * K; e += NT) am = fmax(am, fabs(M[e]));
                 __syncthreads();

@@ -929,12 +929,21 @@ int lp_batch_solve_ex(lp_ctx *ctx, int64_t num_lps, const double *A, const doubl
             HIP_TRY(lpb::launch_certify_wave(W, ca, int(cgrid), stream));
             t.done();
         } else {
-            // One workgroup of 64 threads per LP; LU blocks up to 32 x 32 in LDS,
-            // larger ones in the workgroup's device-memory slot.
-            const int cnt_nt = 64;
+            // One workgroup per LP.  A batch of one size wants many LPs in
+            // flight: 64 threads, LU blocks up to 32 x 32 in LDS, larger ones in the
+            // workgroup's device-memory slot (2,000 of 117 x 150: 103 us against
+            // 195 us with 256 threads; 3,000 of 300 x 200: 365 against 495 us).  A
+            // batch of mixed sizes is bound by its large LPs, whose blocks of up
+            // to 160 x 160 pay a device-memory round trip per LU step: 256 threads
+            // and blocks of up to 80 KB less the vectors in LDS (10,000 of 10..300:
+            // 12.3 -> 9.0 ms, 400 of 20..300: 3.8 -> 1.8 ms).
+            const int cnt_nt = P.uniform ? 64 : 256;
+            const int64_t base = lpb::certify_lds_bytes(P_full.m_max, P_full.n_max, false);
             const int64_t kl = std::min(kmax, 32);
-            const int64_t clds = lpb::certify_lds_bytes(P_full.m_max, P_full.n_max, false) + 8 * kl * kl;
-            if (clds > ctx->max_lds) return fail(LP_ERR_ARG, "LP too large for the certificate kernel");
+            const int64_t least = base + 8 * kl * kl;
+            if (least > ctx->max_lds) return fail(LP_ERR_ARG, "LP too large for the certificate kernel");
+            const int64_t most = std::min<int64_t>(base + 8 * int64_t(kmax) * kmax, ctx->max_lds / 2);
+            const int64_t clds = P.uniform ? least : std::max(least, most);
             ca.lds_bytes = int32_t(clds);
             const int per_cu = lpb::certify_blocks_per_cu(cnt_nt, int(clds));
             if (per_cu < 1) return fail(LP_ERR_HIP, "occupancy query failed for the certificate kernel");
