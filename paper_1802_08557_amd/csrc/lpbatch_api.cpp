@@ -97,11 +97,48 @@ struct BlockPlan {
 
 // Pivots a launch wants its largest LP's window to hold.  Tableaux in device
 // memory are swept once per window, so a longer window is less traffic but
-// fewer workgroups per CU to hide each pivot's latency.
-constexpr int kWantWindow = 12, kWantWindowLds = 8;
+// fewer workgroups per CU to hide each pivot's latency.  In LDS a sweep is
+// cheap: a short window does where a longer one would cost workgroups, and a
+// tableau of few rows or columns sees few pivots.
+constexpr int kWantWindow = 12, kWantWindowLds = 8, kLeastWindowLds = 4;
+
+int want_window_lds(int m_max, int n_max)
+{
+    return std::max(2, std::min(kWantWindowLds, std::min(m_max, n_max) / 2));
+}
+
+// LDS of a workgroup that holds the tableau and a window of K pivots beside it.
+int64_t lds_with_tableau(const lpb::LdsLayout &L, bool fp32, int m_max, int n_max, int K)
+{
+    return L.window(K) + int64_t(m_max) * lpb::lds_tab_ld(n_max) * (fp32 ? 4 : 8) + 16;
+}
+
+// Workgroups of nt threads that a CU gets of a launch over num LPs when nothing
+// else limits them: two wavefronts per SIMD.  More of them hide more of each
+// pivot's latency, but halve the LDS of each, which holds windows and tableaux
+// (uneven 10..300 FP64 66 ms with two, 95 ms with three; FP32 46 and 55 ms).
+int want_per_cu(const lp_ctx *ctx, int nt, int64_t num)
+{
+    return int(std::max<int64_t>(1, std::min<int64_t>(512 / nt, (num + ctx->num_cu - 1) / ctx->num_cu)));
+}
+
+// Threads per workgroup for num LPs of at most m_max x n_max in one launch.  Tableaux
+// in LDS: the eight wavefronts of a CU are shared out over the LPs it holds at
+// once, which its LDS or the batch limits (FP64, 64 against 128 against 256
+// threads: 20,000 LPs of 3 x 100 0.29, 0.47, 0.88 ms; of 30 x 100 1.12, 1.03,
+// 1.87 ms; of 12 x 300 2.95, 2.63, 2.15 ms; 30 LPs of 200 x 10 139, 93, 77 us).
+int block_threads(const lp_ctx *ctx, bool fp32, int m_max, int n_max, bool force_hbm, int placement, int64_t num)
+{
+    const int64_t cells = int64_t(m_max + 1) * (n_max + 1);
+    const lpb::LdsLayout L = lpb::lds_layout(m_max, n_max, fp32 ? 4 : 8, lpb::simplex_ctrl_bytes(fp32));
+    const int64_t lds = lds_with_tableau(L, fp32, m_max, n_max, std::min(kLeastWindowLds, want_window_lds(m_max, n_max)));
+    if (force_hbm || lds > lds_budget(ctx, placement)) return cells <= 64 * 64 ? 64 : cells <= 256 * 256 ? 256 : 512;
+    const int64_t per_cu = std::min<int64_t>(ctx->lds_per_cu / lds, want_per_cu(ctx, 64, num));
+    return cells <= 512 || per_cu >= 7 ? 64 : per_cu >= 4 ? 128 : 256;
+}
 
 int plan_block(const lp_ctx *ctx, bool fp32, int nt, int m_max, int n_max, bool force_hbm, int placement,
-               BlockPlan &B)
+               int64_t num, BlockPlan &B)
 {
     const int64_t ts = fp32 ? 4 : 8, ctrl = lpb::simplex_ctrl_bytes(fp32);
     const int ncol_worst = n_max + m_max;
@@ -112,20 +149,21 @@ int plan_block(const lp_ctx *ctx, bool fp32, int nt, int m_max, int n_max, bool 
         return fail(LP_ERR_ARG, "LP of %d rows x %d columns needs %lld bytes of LDS for its index arrays "
                     "(device limit %d)", m_max, ncol_worst, (long long)least, ctx->max_lds);
     const lpb::LdsLayout L = lpb::lds_layout(m_max, n_max, ts, ctrl);
-    const int64_t tab = int64_t(m_max) * lpb::lds_tab_ld(n_max) * ts;
-    const int64_t with_tab = std::max(least, L.window(kWantWindowLds) + tab + 16);
-    const bool want_lds = !force_hbm && with_tab <= lds_budget(ctx, placement);
-    int64_t lds = want_lds ? with_tab : std::max(least, std::min<int64_t>(ctx->max_lds, L.window(kWantWindow)));
-    B.per_cu = lpb::simplex_blocks_per_cu(fp32, nt, int(lds));
+    const int want = want_per_cu(ctx, nt, num), budget = int(lds_budget(ctx, placement));
+    auto with_tab = [&](int K) { return std::max(least, lds_with_tableau(L, fp32, m_max, n_max, K)); };
+    auto per_cu = [&](int64_t lds) { return lpb::simplex_blocks_per_cu(fp32, nt, int(lds)); };
+    const int K = want_window_lds(m_max, n_max), K_least = std::min(K, kLeastWindowLds);
+    int64_t lds = std::max(least, std::min<int64_t>(ctx->max_lds, L.window(kWantWindow)));
+    if (!force_hbm && with_tab(K_least) <= budget) {
+        lds = with_tab(K);
+        if (lds > budget || per_cu(lds) < want) lds = with_tab(K_least);
+    }
+    B.per_cu = std::min(per_cu(lds), want);
     if (B.per_cu < 1) return fail(LP_ERR_HIP, "occupancy query failed for %d threads, %lld B LDS", nt, (long long)lds);
-    // Two wavefronts per SIMD: more of them hide more of each pivot's latency, but
-    // halve the LDS of each, which holds windows and tableaux (uneven 10..300
-    // FP64 66 ms with two, 95 ms with three; FP32 46 and 55 ms).  Each workgroup
-    // takes the CU's LDS / per_cu: longer windows, and every LP whose tableau
-    // fits there is solved from LDS instead of a device-memory slot.
-    B.per_cu = std::min(B.per_cu, 512 / nt);
+    // Each workgroup takes the CU's LDS / per_cu: longer windows, and every LP
+    // whose tableau fits there is solved from LDS instead of a device-memory slot.
     const int64_t share = std::min<int64_t>(ctx->max_lds, (int64_t(ctx->lds_per_cu) / B.per_cu) & ~int64_t(255));
-    if (share > lds && lpb::simplex_blocks_per_cu(fp32, nt, int(share)) >= B.per_cu) lds = share;
+    if (share > lds && per_cu(share) >= B.per_cu) lds = share;
     B.lds = lds;
     B.slot_bytes = lpb::align16(int64_t(m_max) * lpb::slot_tab_ld(ncol_worst, int(ts)) * ts);
     return LP_OK;
@@ -219,12 +257,11 @@ int queue_pass(lp_ctx *ctx, const Plan &P, lpb::SolveArgs a, const lp_options &o
         if (no_defer) return LP_OK;
     }
     // Workgroup kernel: the LPs given to it plus the ones the wavefront deferred.
-    const int64_t cells = int64_t(P.m_max + 1) * (P.n_max + 1);
-    int nt = opts.block_threads;
-    if (!nt) nt = cells <= 64 * 64 ? 64 : (cells <= 256 * 256 ? 256 : 512);
     a.force_hbm = opts.placement == LP_PLACE_HBM;
+    int nt = opts.block_threads;
+    if (!nt) nt = block_threads(ctx, fp32, P.m_max, P.n_max, a.force_hbm, opts.placement, P.num);
     BlockPlan B;
-    if (int rc = plan_block(ctx, fp32, nt, P.m_max, P.n_max, a.force_hbm, opts.placement, B)) return rc;
+    if (int rc = plan_block(ctx, fp32, nt, P.m_max, P.n_max, a.force_hbm, opts.placement, P.num, B)) return rc;
     a.lds_bytes = int32_t(B.lds);
     a.slot_bytes = B.slot_bytes;
     // When the wavefront kernel was offered every LP, this launch only drains
@@ -324,7 +361,7 @@ int launch_block(lp_ctx *ctx, bool fp32, lpb::SolveArgs a, const BinLaunch &B, c
                  hipStream_t stream, bool timing, const char *name)
 {
     BlockPlan L;
-    if (int rc = plan_block(ctx, fp32, B.nt, B.m_max, B.n_max, B.force_hbm, B.placement, L)) return rc;
+    if (int rc = plan_block(ctx, fp32, B.nt, B.m_max, B.n_max, B.force_hbm, B.placement, num, L)) return rc;
     a.force_hbm = B.force_hbm;
     a.lds_bytes = int32_t(L.lds);
     a.slot_bytes = L.slot_bytes;

@@ -65,11 +65,11 @@ __device__ __forceinline__ int row_sense(int f) { return (f >> 1) & 3; }
 
 // ---- reductions ------------------------------------------------------------
 
+// The workgroup's largest of values >= +0 (not NaN).
 template <typename T, int NT>
 __device__ __forceinline__ double block_max(double v, Ctrl<T> *sh)
 {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v = fmax(v, __shfl_xor(v, off));
+    v = lane_get(v, __builtin_ctzll(wave_max_nonneg(true, v)));
     if constexpr (NT > 64) {
         const int w = threadIdx.x >> 6;
         if ((threadIdx.x & 63) == 0) sh->rd[w] = v;
@@ -137,6 +137,7 @@ struct LP {
     T *rhs, *obj;  // current right-hand sides and reduced costs
     T *np, *pr;    // window: negated pivot columns [K][m], scaled pivot rows [K][N]
     int K, p;      // pivots the window holds at most, and now
+    bool direct;   // each pivot updates the tableau at once; the window stays empty
     T *tab;        // m x N in LDS or device memory, row stride ld, without the window's pivots
     T z;           // right-hand side of the objective row (minus its value)
     int turn;      // set of block_pick's slots
@@ -194,7 +195,17 @@ __device__ __forceinline__ int block_pick(LP<T, NT> &P, const Best<MAX, T> &c, T
 // at the HBM copy rate), 10,000 uneven LPs of 10..300 FP64 140 -> 60 ms and FP32
 // 86 -> 40 ms (42 % sweeps, 37 % the device-memory latency of the one column and
 // row, 14 % the reductions), 2,000 LPs of 117 x 150 FP32 1.14 -> 0.63 ms.
+//
+// A tableau in LDS is swept at LDS speed, so sixteen pivots a window do: each pivot
+// reads half as many vectors of it as of thirty-two (1,000 LPs FP64, 32 / 16 pivots:
+// 100 x 100 344 / 335 us, 200 x 60 FP32 322 / 316 us).  Of at most kDirectRows rows
+// each pivot updates every entry at once (push), three or four operations a
+// column against walks over the window for the column and the row: 1,000 LPs
+// FP64 of 3 x 500 98 -> 77 us, of 6 x 80 80 -> 63 us, of 16 x 250 FP32 154 ->
+// 176 us, hence the line at eight.
 constexpr int kMaxWindow = 32;
+constexpr int kMaxWindowLds = 16;
+constexpr int kDirectRows = 8;
 
 // f(i, a) for every live row i of this thread with its entry a of column e of
 // the current tableau; the negated column becomes slot p of np (0 in dropped
@@ -250,12 +261,14 @@ __device__ __forceinline__ void row(LP<T, NT> &P, int l, F f)
 }
 
 // Step 3 for the pivot on (l, e), whose negated column is slot p of np with
-// a barrier since: it becomes slot p of the window.  de, ne: the entering
-// column's reduced cost and variable.  Ends with a barrier only when the
-// workgroup is one wavefront; otherwise the next block_pick's or flush's
-// barrier comes before anything written here is read by another thread.
-template <typename T, int NT>
-__device__ __forceinline__ void push(LP<T, NT> &P, int l, int e, T de, int ne)
+// a barrier since: it becomes slot p of the window, or (P.direct) updates the
+// tableau.  de, ne: the entering column's reduced cost and variable.
+// f(j, d, b) receives every column j of this thread with its new reduced cost and
+// variable.  Ends with a barrier only when the workgroup is one wavefront;
+// otherwise the next block_pick's or flush's barrier comes before anything
+// written here is read by another thread.
+template <typename T, int NT, typename F>
+__device__ __forceinline__ void push(LP<T, NT> &P, int l, int e, T de, int ne, F f)
 {
     const int tid = threadIdx.x;
     const int m = P.m, N = P.N, p = P.p;
@@ -266,9 +279,27 @@ __device__ __forceinline__ void push(LP<T, NT> &P, int l, int e, T de, int ne)
     const int bl = uniform(P.basis[l]);
     row(P, l, [&](int j, T t) {
         const T w = j == e ? pre : t / pe;
-        P.obj[j] = fma(-de, w, j == e ? T(0) : P.obj[j]);
-        pr[j] = w;
+        const T d = fma(-de, w, j == e ? T(0) : P.obj[j]);
+        P.obj[j] = d;
+        f(j, d, j == e ? bl : P.nonb[j]);
         tl[j] = w;
+        if (!P.direct) {
+            pr[j] = w;
+            return;
+        }
+        T *tj = P.tab + j;
+        for (int i0 = 0; i0 < m; i0 += 4) {
+            T was[4], na[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int i = min(i0 + q, m - 1);
+                was[q] = tj[i * P.ld];
+                na[q] = np[i];
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                if (i0 + q < m && i0 + q != l) tj[(i0 + q) * P.ld] = fma(na[q], w, j == e ? T(0) : was[q]);
+        }
     });
     P.z = fma(-de, prhs, P.z);
     __syncthreads();  // row l and column e of the window have been read
@@ -279,15 +310,17 @@ __device__ __forceinline__ void push(LP<T, NT> &P, int l, int e, T de, int ne)
         } else {
             const T na = np[i];
             P.rhs[i] = fma(na, prhs, P.rhs[i]);
-            P.tab[int64_t(i) * P.ld + e] = fma(na, pre, T(0));
+            if (!P.direct) P.tab[int64_t(i) * P.ld + e] = fma(na, pre, T(0));
         }
     }
-    for (int k = tid; k <= p; k += NT) {
-        P.np[k * m + l] = T(0);
-        P.pr[k * N + e] = T(0);
+    if (!P.direct) {
+        for (int k = tid; k <= p; k += NT) {
+            P.np[k * m + l] = T(0);
+            P.pr[k * N + e] = T(0);
+        }
+        ++P.p;
     }
     if (tid == e % NT) P.nonb[e] = bl;
-    ++P.p;
     if constexpr (NT == 64) __syncthreads();
 }
 
@@ -371,18 +404,21 @@ __device__ __forceinline__ int simplex(LP<T, NT> &P, T eps_opt, const SolveParam
     const int N = P.N, nm = P.n + P.m;
     const T tol_piv = T(prm.tol_piv);
     int deg_run = 0;
+    // Step 1's candidates: collected from the reduced costs as each pivot writes
+    // them (Dantzig's and Bland's rules), or by a pass of their own.
+    Best<true, T> in;
+    bool bland = prm.k_deg > 0 && deg_run >= prm.k_deg;
+    auto offer = [&](int j, T d, int bj) { in.offer(d > eps_opt && bj < nm, bland ? T(0) : d, bj, j); };
+    if (prm.pricing != 1 || bland)
+        for (int j = tid; j < N; j += NT) offer(j, P.obj[j], P.nonb[j]);
     for (;;) {
         if (P.iters >= P.cap) return ST_ITER;
-        const bool bland = prm.k_deg > 0 && deg_run >= prm.k_deg;
-        // Step 1: entering column.
-        Best<true, T> in;
-        const bool steep = prm.pricing == 1 && !bland;
-        for (int j = tid; j < N; j += NT) {
-            const T d = P.obj[j];
-            const int bj = P.nonb[j];
-            const bool ok = d > eps_opt && bj < nm;
-            if (steep) {
-                if (!ok) continue;
+        if (prm.pricing == 1 && !bland) {
+            in = Best<true, T>();
+            for (int j = tid; j < N; j += NT) {
+                const T d = P.obj[j];
+                const int bj = P.nonb[j];
+                if (!(d > eps_opt && bj < nm)) continue;
                 // Steepest edge: d_j^2 / (1 + sum of column j's squares
                 // over the live rows); threads walk down their columns,
                 // rows i summed into partial sum i mod R, the partial sums
@@ -407,10 +443,9 @@ __device__ __forceinline__ int simplex(LP<T, NT> &P, T eps_opt, const SolveParam
                 for (int q = 0; q < R; ++q) w += acc[q];
                 const T key = d * d / w;
                 in.offer(key == key, key, bj, j);
-            } else {
-                in.offer(ok, bland ? T(0) : d, bj, j);
             }
         }
+        // Step 1: entering column.
         T key = T(0);
         const int e = block_pick(P, in, key);
         if (e < 0) return ST_OPTIMAL;
@@ -429,7 +464,9 @@ __device__ __forceinline__ int simplex(LP<T, NT> &P, T eps_opt, const SolveParam
         const int l = block_pick(P, out, th);
         if (l < 0) { *enter = ne; return ST_UNBOUNDED; }
         if (th == T(0)) { ++deg_run; ++P.degp; } else deg_run = 0;
-        push(P, l, e, de, ne);
+        bland = prm.k_deg > 0 && deg_run >= prm.k_deg;
+        in = Best<true, T>();
+        push(P, l, e, de, ne, offer);
         ++P.iters;
         if (P.p == P.K || prm.pricing == 1) flush(P);
     }
@@ -499,22 +536,29 @@ __device__ __forceinline__ void price_out(LP<T, NT> &P)
     const int m = P.m, n = P.n, N = P.N, ld = P.ld;
     const T *tab = P.tab;
     T *cbv = P.np;
+    bool any = false;
     for (int i = tid; i < m; i += NT) {
         const int bv = P.basis[i];
-        cbv[i] = ((P.rowf[i] & ROW_DEAD) || bv >= n) ? T(0) : T(P.c[bv]);
+        const T cb = ((P.rowf[i] & ROW_DEAD) || bv >= n) ? T(0) : T(P.c[bv]);
+        cbv[i] = cb;
+        any |= cb != T(0);
     }
-    __syncthreads();
+    // The slack basis, with no cost to price out, skips the walks over the rows
+    // (80 x 80: a tenth of a lone LP's time).
+    const bool none = block_max<T, NT>(any ? 1.0 : 0.0, P.sh) == 0.0;
+    if constexpr (NT == 64) __syncthreads();  // cbv
+    const int rows = none ? 0 : m;
     for (int j = tid; j < N; j += NT) {
         const int bj = P.nonb[j];
         T acc = (bj < n) ? T(P.c[bj]) : T(0);
-        for (int i = 0; i < m; ++i) {
+        for (int i = 0; i < rows; ++i) {
             const T cb = cbv[i];
             if (cb != T(0)) acc = fma(-cb, tab[(int64_t)i * ld + j], acc);
         }
         P.obj[j] = acc;
     }
     P.z = T(0);
-    for (int i = 0; i < m; ++i) {
+    for (int i = 0; i < rows; ++i) {
         const T cb = cbv[i];
         if (cb != T(0)) P.z = fma(-cb, P.rhs[i], P.z);
     }
@@ -572,7 +616,7 @@ __device__ __forceinline__ bool crash(LP<T, NT> &P, const SolveArgs &a)
         column(P, c, [&](int i, T t) { big.offer(tight[i] && t == t, T(fabs(t)), i, i); });
         const int l = block_pick(P, big, best);
         if (l < 0 || !(best > tol_piv)) return false;
-        push(P, l, c, T(0), v);
+        push(P, l, c, T(0), v, [](int, T, int) {});
         if (tid == l % NT) tight[l] = 0;
         ++P.iters;
     }
@@ -597,7 +641,7 @@ __device__ __forceinline__ int dual_repair(LP<T, NT> &P, T tol_dual, T tol_p, co
     const T tol_piv = T(prm.tol_piv);
     Ctrl<T> *sh = P.sh;
     // Dual and primal feasibility of the start.
-    double dmax = -1.0, pinf = -1.0;
+    double dmax = 0.0, pinf = 0.0;
     for (int j = tid; j < N; j += NT)
         if (P.nonb[j] < nm && P.obj[j] > tol_dual) dmax = 1.0;
     for (int i = tid; i < m; i += NT)
@@ -631,7 +675,7 @@ __device__ __forceinline__ int dual_repair(LP<T, NT> &P, T tol_dual, T tol_p, co
         const int ne = uniform(P.nonb[e]);
         column(P, e, [](int, T) {});
         __syncthreads();
-        push(P, l, e, de, ne);
+        push(P, l, e, de, ne, [](int, T, int) {});
         ++P.iters;
     }
 }
@@ -751,7 +795,7 @@ __device__ __forceinline__ void solve_lp(LP<T, NT> &P, const SolveArgs &a, int p
                 const int ne = uniform(P.nonb[e]);
                 column(P, e, [](int, T) {});
                 __syncthreads();
-                push(P, i, e, de, ne);
+                push(P, i, e, de, ne, [](int, T, int) {});
             } else if (tid == i % NT) {
                 P.rowf[i] |= ROW_DEAD;
             }
@@ -953,7 +997,9 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void si
         const bool in_lds = !a.force_hbm && L.window(2) + in_lds_bytes <= lds;
         P.ld = in_lds ? lds_tab_ld(P.N) : slot_tab_ld(P.N, int(sizeof(T)));
         const int64_t room = (lds - L.win - (in_lds ? in_lds_bytes + 16 : 0)) / vec;
-        P.K = int(room >= kMaxWindow ? kMaxWindow : room >= 4 ? room & ~int64_t(3) : room < 1 ? 1 : room);
+        P.direct = in_lds && m <= kDirectRows;
+        const int most = P.direct ? 1 : in_lds ? kMaxWindowLds : kMaxWindow;
+        P.K = int(room >= most ? most : room >= 4 ? room & ~int64_t(3) : room < 1 ? 1 : room);
         P.np = P.pr + int64_t(P.K) * P.N;
         P.p = 0;
         const int64_t slot_need = int64_t(sizeof(T)) * m * P.ld;
