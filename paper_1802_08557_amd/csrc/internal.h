@@ -239,6 +239,10 @@ int64_t wave_lds_aux_bytes(int rb, bool gather);
 int64_t wave_tab_bytes(int m, int cols, bool fp32);
 hipError_t simplex_wave_configure(int max_lds);
 
+// Rows up to which the workgroup kernel updates a tableau in LDS pivot by pivot
+// instead of through a window of deferred pivots.
+constexpr int kDirectRows = 12;
+
 // LDS of the workgroup kernel for an LP of m rows and N non-basic columns (byte
 // offsets): control block, index arrays, right-hand sides, reduced costs, then
 // the window of deferred pivots (a column of m and a row of N entries each),

@@ -127,6 +127,9 @@ int want_per_cu(const lp_ctx *ctx, int nt, int64_t num)
 // once, which its LDS or the batch limits (FP64, 64 against 128 against 256
 // threads: 20,000 LPs of 3 x 100 0.29, 0.47, 0.88 ms; of 30 x 100 1.12, 1.03,
 // 1.87 ms; of 12 x 300 2.95, 2.63, 2.15 ms; 30 LPs of 200 x 10 139, 93, 77 us).
+// The smallest have too little to share out between the barriers (214 LPs of 24 x 70
+// 73 us with 64, 76 us with 128; of 10 x 91, whose pivots update every entry at
+// once, 73 and 64 us).
 int block_threads(const lp_ctx *ctx, bool fp32, int m_max, int n_max, bool force_hbm, int placement, int64_t num)
 {
     const int64_t cells = int64_t(m_max + 1) * (n_max + 1);
@@ -134,7 +137,9 @@ int block_threads(const lp_ctx *ctx, bool fp32, int m_max, int n_max, bool force
     const int64_t lds = lds_with_tableau(L, fp32, m_max, n_max, std::min(kLeastWindowLds, want_window_lds(m_max, n_max)));
     if (force_hbm || lds > lds_budget(ctx, placement)) return cells <= 64 * 64 ? 64 : cells <= 256 * 256 ? 256 : 512;
     const int64_t per_cu = std::min<int64_t>(ctx->lds_per_cu / lds, want_per_cu(ctx, 64, num));
-    return cells <= 512 || per_cu >= 7 ? 64 : per_cu >= 4 ? 128 : 256;
+    if (per_cu >= 7) return 64;
+    if (cells <= 2048 && std::max(m_max, n_max) <= 128) return cells <= 512 || m_max > lpb::kDirectRows ? 64 : 128;
+    return per_cu >= 4 ? 128 : 256;
 }
 
 int plan_block(const lp_ctx *ctx, bool fp32, int nt, int m_max, int n_max, bool force_hbm, int placement,

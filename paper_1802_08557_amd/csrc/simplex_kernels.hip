@@ -199,13 +199,12 @@ __device__ __forceinline__ int block_pick(LP<T, NT> &P, const Best<MAX, T> &c, T
 // A tableau in LDS is swept at LDS speed, so sixteen pivots a window do: each pivot
 // reads half as many vectors of it as of thirty-two (1,000 LPs FP64, 32 / 16 pivots:
 // 100 x 100 344 / 335 us, 200 x 60 FP32 322 / 316 us).  Of at most kDirectRows rows
-// each pivot updates every entry at once (push), three or four operations a
-// column against walks over the window for the column and the row: 1,000 LPs
-// FP64 of 3 x 500 98 -> 77 us, of 6 x 80 80 -> 63 us, of 16 x 250 FP32 154 ->
-// 176 us, hence the line at eight.
+// each pivot updates every entry at once (push), a few operations a column against
+// walks over the window for the column and the row: 1,000 LPs FP64 of 3 x 500 98 ->
+// 77 us, of 10 x 91 94 -> 84 us, of 16 x 100 93 -> 92 us, of 24 x 70 100 -> 107 us,
+// hence the line at twelve.
 constexpr int kMaxWindow = 32;
 constexpr int kMaxWindowLds = 16;
-constexpr int kDirectRows = 8;
 
 // f(i, a) for every live row i of this thread with its entry a of column e of
 // the current tableau; the negated column becomes slot p of np (0 in dropped

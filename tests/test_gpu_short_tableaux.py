@@ -1,4 +1,4 @@
-"""Tableaux of few rows.  The workgroup kernel updates one of at most eight rows
+"""Tableaux of few rows.  The workgroup kernel updates one of at most twelve rows
 pivot by pivot when it lies in LDS and through windows of pivots when it lies in
 device memory: both against the oracle and bit for bit against each other, at the
 edges of the rule, with surplus columns, artificials and both pricing rules."""
@@ -29,7 +29,7 @@ def solve(ctx, bt, **kw):
 
 
 @pytest.mark.parametrize("pricing", [0, 1])
-@pytest.mark.parametrize("m,n", [(1, 65), (3, 100), (4, 511), (5, 64), (7, 129), (8, 65), (8, 300), (9, 65), (16, 100)])
+@pytest.mark.parametrize("m,n", [(1, 65), (3, 100), (4, 511), (5, 64), (7, 129), (8, 65), (8, 300), (12, 65), (13, 65), (12, 129), (16, 100)])
 def test_lds_and_memory_agree(ctx, m, n, pricing):
     for bt in (W.uniform_batch(9, m, n, seed=m + n), W.phase1_batch(9, m, n, seed=5 * m + n)):
         ref = oracle_solve(bt, pricing=pricing)
