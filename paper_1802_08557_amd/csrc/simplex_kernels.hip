@@ -138,6 +138,7 @@ struct LP {
     T *np, *pr;    // window: negated pivot columns [K][m], scaled pivot rows [K][N]
     int K, p;      // pivots the window holds at most, and now
     bool direct;   // each pivot updates the tableau at once; the window stays empty
+    bool steep;    // steepest-edge pricing
     T *tab;        // m x N in LDS or device memory, row stride ld, without the window's pivots
     T z;           // right-hand side of the objective row (minus its value)
     int turn;      // set of block_pick's slots
@@ -262,8 +263,8 @@ __device__ __forceinline__ void row(LP<T, NT> &P, int l, F f)
 // Step 3 for the pivot on (l, e), whose negated column is slot p of np with
 // a barrier since: it becomes slot p of the window, or (P.direct) updates the
 // tableau.  de, ne: the entering column's reduced cost and variable.
-// f(j, d, b) receives every column j of this thread with its new reduced cost and
-// variable.  Ends with a barrier only when the workgroup is one wavefront;
+// f(j, d, b, s) receives every column j of this thread with its new reduced cost
+// and variable and, under steepest edge, its weight.  Ends with a barrier only when the workgroup is one wavefront;
 // otherwise the next block_pick's or flush's barrier comes before anything
 // written here is read by another thread.
 template <typename T, int NT, typename F>
@@ -280,25 +281,38 @@ __device__ __forceinline__ void push(LP<T, NT> &P, int l, int e, T de, int ne, F
         const T w = j == e ? pre : t / pe;
         const T d = fma(-de, w, j == e ? T(0) : P.obj[j]);
         P.obj[j] = d;
-        f(j, d, j == e ? bl : P.nonb[j]);
+        const int bj = j == e ? bl : P.nonb[j];
         tl[j] = w;
         if (!P.direct) {
+            f(j, d, bj, T(1));
             pr[j] = w;
             return;
         }
-        T *tj = P.tab + j;
-        for (int i0 = 0; i0 < m; i0 += 4) {
-            T was[4], na[4];
+        // The rows of this column, eight loads in flight; the squares that steepest
+        // edge sums in the order of its own pass (simplex).
+        constexpr int R = 16 / int(sizeof(T)), U = 8;
+        T *tj = P.tab + j, acc[R];
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int i = min(i0 + q, m - 1);
-                was[q] = tj[i * P.ld];
-                na[q] = np[i];
+        for (int q = 0; q < R; ++q) acc[q] = T(0);
+        for (int i0 = 0; i0 < m; i0 += U) {
+            T t[U];
+#pragma unroll
+            for (int q = 0; q < U; ++q) t[q] = tj[int64_t(min(i0 + q, m - 1)) * P.ld];
+#pragma unroll
+            for (int q = 0; q < U; ++q) {
+                const int i = i0 + q;
+                if (i >= m) continue;
+                if (i != l) {
+                    t[q] = fma(np[i], w, j == e ? T(0) : t[q]);
+                    tj[int64_t(i) * P.ld] = t[q];
+                }
+                if (P.steep && !(P.rowf[i] & ROW_DEAD)) acc[q % R] = fma(t[q], t[q], acc[q % R]);
             }
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-                if (i0 + q < m && i0 + q != l) tj[(i0 + q) * P.ld] = fma(na[q], w, j == e ? T(0) : was[q]);
         }
+        T s = T(1);
+#pragma unroll
+        for (int q = 0; q < R; ++q) s += acc[q];
+        f(j, d, bj, s);
     });
     P.z = fma(-de, prhs, P.z);
     __syncthreads();  // row l and column e of the window have been read
@@ -403,47 +417,44 @@ __device__ __forceinline__ int simplex(LP<T, NT> &P, T eps_opt, const SolveParam
     const int N = P.N, nm = P.n + P.m;
     const T tol_piv = T(prm.tol_piv);
     int deg_run = 0;
-    // Step 1's candidates: collected from the reduced costs as each pivot writes
-    // them (Dantzig's and Bland's rules), or by a pass of their own.
+    // Step 1's candidates are collected from the reduced costs, and under steepest
+    // edge the weights, as each pivot writes them; the first ones here.
     Best<true, T> in;
     bool bland = prm.k_deg > 0 && deg_run >= prm.k_deg;
-    auto offer = [&](int j, T d, int bj) { in.offer(d > eps_opt && bj < nm, bland ? T(0) : d, bj, j); };
-    if (prm.pricing != 1 || bland)
-        for (int j = tid; j < N; j += NT) offer(j, P.obj[j], P.nonb[j]);
-    for (;;) {
-        if (P.iters >= P.cap) return ST_ITER;
-        if (prm.pricing == 1 && !bland) {
-            in = Best<true, T>();
-            for (int j = tid; j < N; j += NT) {
-                const T d = P.obj[j];
-                const int bj = P.nonb[j];
-                if (!(d > eps_opt && bj < nm)) continue;
-                // Steepest edge: d_j^2 / (1 + sum of column j's squares
-                // over the live rows); threads walk down their columns,
-                // rows i summed into partial sum i mod R, the partial sums
-                // then added in order -- the wavefront kernel's order, so
-                // both kernels choose the same column.
-                constexpr int R = 16 / int(sizeof(T));
-                T acc[R];
+    auto offer = [&](int j, T d, int bj, T w) {
+        const bool ok = d > eps_opt && bj < nm;
+        const T key = bland ? T(0) : P.steep ? d * d / w : d;
+        in.offer(ok && key == key, key, bj, j);
+    };
+    for (int j = tid; j < N; j += NT) {
+        T w = T(1);
+        if (P.steep) {
+            // Steepest edge: d_j^2 / (1 + sum of column j's squares
+            // over the live rows); threads walk down their columns,
+            // rows i summed into partial sum i mod R, the partial sums
+            // then added in order -- the wavefront kernel's order, so
+            // both kernels choose the same column.
+            constexpr int R = 16 / int(sizeof(T));
+            T acc[R];
 #pragma unroll
-                for (int q = 0; q < R; ++q) acc[q] = T(0);
-                for (int i0 = 0; i0 < P.m; i0 += R) {
+            for (int q = 0; q < R; ++q) acc[q] = T(0);
+            for (int i0 = 0; i0 < P.m; i0 += R) {
 #pragma unroll
-                    for (int q = 0; q < R; ++q) {
-                        const int i = i0 + q;
-                        if (i < P.m && !(P.rowf[i] & ROW_DEAD)) {
-                            const T t = P.tab[int64_t(i) * P.ld + j];
-                            acc[q] = fma(t, t, acc[q]);
-                        }
+                for (int q = 0; q < R; ++q) {
+                    const int i = i0 + q;
+                    if (i < P.m && !(P.rowf[i] & ROW_DEAD)) {
+                        const T t = P.tab[int64_t(i) * P.ld + j];
+                        acc[q] = fma(t, t, acc[q]);
                     }
                 }
-                T w = T(1);
-#pragma unroll
-                for (int q = 0; q < R; ++q) w += acc[q];
-                const T key = d * d / w;
-                in.offer(key == key, key, bj, j);
             }
+#pragma unroll
+            for (int q = 0; q < R; ++q) w += acc[q];
         }
+        offer(j, P.obj[j], P.nonb[j], w);
+    }
+    for (;;) {
+        if (P.iters >= P.cap) return ST_ITER;
         // Step 1: entering column.
         T key = T(0);
         const int e = block_pick(P, in, key);
@@ -467,7 +478,7 @@ __device__ __forceinline__ int simplex(LP<T, NT> &P, T eps_opt, const SolveParam
         in = Best<true, T>();
         push(P, l, e, de, ne, offer);
         ++P.iters;
-        if (P.p == P.K || prm.pricing == 1) flush(P);
+        if (P.p == P.K) flush(P);
     }
 }
 
@@ -615,7 +626,7 @@ __device__ __forceinline__ bool crash(LP<T, NT> &P, const SolveArgs &a)
         column(P, c, [&](int i, T t) { big.offer(tight[i] && t == t, T(fabs(t)), i, i); });
         const int l = block_pick(P, big, best);
         if (l < 0 || !(best > tol_piv)) return false;
-        push(P, l, c, T(0), v, [](int, T, int) {});
+        push(P, l, c, T(0), v, [](int, T, int, T) {});
         if (tid == l % NT) tight[l] = 0;
         ++P.iters;
     }
@@ -674,7 +685,7 @@ __device__ __forceinline__ int dual_repair(LP<T, NT> &P, T tol_dual, T tol_p, co
         const int ne = uniform(P.nonb[e]);
         column(P, e, [](int, T) {});
         __syncthreads();
-        push(P, l, e, de, ne, [](int, T, int) {});
+        push(P, l, e, de, ne, [](int, T, int, T) {});
         ++P.iters;
     }
 }
@@ -794,7 +805,7 @@ __device__ __forceinline__ void solve_lp(LP<T, NT> &P, const SolveArgs &a, int p
                 const int ne = uniform(P.nonb[e]);
                 column(P, e, [](int, T) {});
                 __syncthreads();
-                push(P, i, e, de, ne, [](int, T, int) {});
+                push(P, i, e, de, ne, [](int, T, int, T) {});
             } else if (tid == i % NT) {
                 P.rowf[i] |= ROW_DEAD;
             }
@@ -996,7 +1007,9 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void si
         const bool in_lds = !a.force_hbm && L.window(2) + in_lds_bytes <= lds;
         P.ld = in_lds ? lds_tab_ld(P.N) : slot_tab_ld(P.N, int(sizeof(T)));
         const int64_t room = (lds - L.win - (in_lds ? in_lds_bytes + 16 : 0)) / vec;
-        P.direct = in_lds && m <= kDirectRows;
+        // (Steepest edge reads every column of every pivot's tableau: no window.)
+        P.steep = a.prm.pricing == 1;
+        P.direct = P.steep || (in_lds && m <= kDirectRows);
         const int most = P.direct ? 1 : in_lds ? kMaxWindowLds : kMaxWindow;
         P.K = int(room >= most ? most : room >= 4 ? room & ~int64_t(3) : room < 1 ? 1 : room);
         P.np = P.pr + int64_t(P.K) * P.N;

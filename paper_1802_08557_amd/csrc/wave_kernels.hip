@@ -401,50 +401,81 @@ __device__ __forceinline__ int price(bool elig, T d, int nonb, bool bland)
     return __builtin_ctzll(ballot(in && nonb == bmin));
 }
 
-// Step 1 by steepest edge: each eligible lane sums the squares of its own
-// column over the live rows (the tableau must be swept), one partial sum per
-// component of a 16-byte vector of rows (the workgroup kernel's order).
-template <typename T, int RB>
-__device__ __forceinline__ int price_steepest(const WaveLP<T, RB> &P, bool elig)
+// Weights of steepest edge: 1 + the sum of the squares of this lane's column over
+// the live rows, row i into partial sum i mod R (the workgroup kernel's order).
+// With SWEEP the one pivot given by np (this lane's rows) and pr (its column)
+// reaches the tableau on the way, so that each pivot reads and writes the tableau
+// once and no pass of its own is left to Step 1.
+template <bool SWEEP, typename T, int RB>
+__device__ __forceinline__ T steepest_weight(const WaveLP<T, RB> &P, const T (&np)[RB], T pr)
 {
     const int lane = threadIdx.x;
-    const uint64_t dead0 = ballot((P.rowf[0] & (kRowDead | kRowPad)) != 0);
-    const uint64_t dead1 = RB > 1 ? ballot((P.rowf[RB - 1] & (kRowDead | kRowPad)) != 0) : 0;
-    constexpr int R = 16 / int(sizeof(T));
+    constexpr int R = 16 / int(sizeof(T)), U = 8;
     T acc[R];
 #pragma unroll
     for (int q = 0; q < R; ++q) acc[q] = T(0);
-    if (elig) {
-#pragma unroll 2
-        for (int i0 = 0; i0 < P.m; i0 += R) {
+    uint64_t dead[RB];
 #pragma unroll
-            for (int q = 0; q < R; ++q) {
-                const int i = i0 + q;
-                const T t = i < P.m ? P.tab[i * P.ld + lane] : T(0);
-                const uint64_t dm = i < 64 ? dead0 : dead1;
-                acc[q] = ((dm >> (i & 63)) & 1) ? acc[q] : fma(t, t, acc[q]);
+    for (int r = 0; r < RB; ++r) dead[r] = ballot((P.rowf[r] & (kRowDead | kRowPad)) != 0);
+    if (lane < P.N) {
+        static_for<0, RB>([&](auto r) {
+            const int rows = min(P.m - 64 * r, 64);
+            for (int i0 = 0; i0 < rows; i0 += U) {
+                T *at = P.tab + (64 * r + i0) * P.ld + lane;
+                if (i0 + U <= rows && !((dead[r] >> i0) & 0xff)) {
+                    T t[U];
+#pragma unroll
+                    for (int q = 0; q < U; ++q) t[q] = at[q * P.ld];
+#pragma unroll
+                    for (int q = 0; q < U; ++q) {
+                        if constexpr (SWEEP) {
+                            t[q] = fma(lane_get(np[r], i0 + q), pr, t[q]);
+                            at[q * P.ld] = t[q];
+                        }
+                        acc[q % R] = fma(t[q], t[q], acc[q % R]);
+                    }
+                    continue;
+                }
+#pragma unroll
+                for (int q = 0; q < U; ++q) {
+                    if (i0 + q >= rows) continue;
+                    T t = at[q * P.ld];
+                    if constexpr (SWEEP) {
+                        t = fma(lane_get(np[r], i0 + q), pr, t);
+                        at[q * P.ld] = t;
+                    }
+                    if (!((dead[r] >> (i0 + q)) & 1)) acc[q % R] = fma(t, t, acc[q % R]);
+                }
             }
-        }
+        });
     }
     T w = T(1);
 #pragma unroll
     for (int q = 0; q < R; ++q) w += acc[q];
+    return w;
+}
+
+// Step 1 by steepest edge from this lane's weight.
+template <typename T, int RB>
+__device__ __forceinline__ int price_steepest(const WaveLP<T, RB> &P, bool elig, T w)
+{
     const T key = elig ? P.d * P.d / w : T(0);
     const uint64_t any = ballot(elig);
     if (!any) return -1;
     const T best = wave_max_f(elig ? key : -t_inf<T>());
     const uint64_t tied = ballot(elig && key == best);
     if (__popcll(tied) == 1) return __builtin_ctzll(tied);
-    const bool in = (tied >> lane) & 1;
+    const bool in = (tied >> threadIdx.x) & 1;
     const int bmin = wave_min_i(in ? P.nonb : kBig);
     return __builtin_ctzll(ballot(in && P.nonb == bmin));
 }
 
 // One iteration with S pivots in the group being filled.  Returns -1 to go
-// on, else the status (the group then still holds S pivots).
-template <int S, typename T, int RB, int NG>
+// on, else the status (the group then still holds S pivots).  STEEP: steepest
+// edge, w this lane's weight.
+template <int S, bool STEEP, typename T, int RB, int NG>
 __device__ __forceinline__ int step(WaveLP<T, RB> &P, Window<T, RB, NG> &Q, T eps_opt, const SolveParams &prm,
-                                    int &deg_run, int *enter)
+                                    int &deg_run, int *enter, T w = T(1))
 {
     const int lane = threadIdx.x;
     if (P.iters >= P.cap) return kIterLimit;
@@ -452,7 +483,7 @@ __device__ __forceinline__ int step(WaveLP<T, RB> &P, Window<T, RB, NG> &Q, T ep
     // Step 1.
     const bool elig = lane < P.N && P.d > eps_opt && P.nonb < P.n + P.m;
     int e;
-    if (S == 0 && prm.pricing == 1 && !bland) e = price_steepest<T, RB>(P, elig);
+    if (STEEP && !bland) e = price_steepest<T, RB>(P, elig, w);
     else e = price<T>(elig, P.d, P.nonb, bland);
     if (e < 0) return kOptimal;
     // Step 2: each lane's best row (ties to the smaller basic index), then
@@ -508,15 +539,10 @@ __device__ __forceinline__ int run_group(WaveLP<T, RB> &P, Window<T, RB, NG> &Q,
                                          int &deg_run, int *enter)
 {
     if constexpr (S < 4) {
-        const int r = step<S>(P, Q, eps_opt, prm, deg_run, enter);
+        const int r = step<S, false>(P, Q, eps_opt, prm, deg_run, enter);
         if (r >= 0) {
             pad_group<S>(Q.grp[NG]);
             return r;
-        }
-        // Steepest edge reads every column: a sweep after every pivot.
-        if (S == 0 && prm.pricing == 1) {
-            pad_group<1>(Q.grp[NG]);
-            return -1;
         }
         return run_group<S + 1>(P, Q, eps_opt, prm, deg_run, enter);
     }
@@ -529,10 +555,19 @@ __device__ __forceinline__ int simplex(WaveLP<T, RB> &P, T eps_opt, const SolveP
     int deg_run = 0;
     Window<T, RB, NG> Q;
     Q.n = 0;
+    if (prm.pricing == 1) {
+        // Steepest edge reads every column of every pivot's tableau: no window.
+        T w = steepest_weight<false>(P, P.pcol, T(0));
+        for (;;) {
+            const int r = step<0, true>(P, Q, eps_opt, prm, deg_run, enter, w);
+            if (r >= 0) return r;
+            w = steepest_weight<true>(P, Q.grp[NG].np[0], Q.grp[NG].pr[0]);
+        }
+    }
     for (;;) {
         const int r = run_group<0>(P, Q, eps_opt, prm, deg_run, enter);
         if (r >= 0 && !P.keep) return r;
-        if (r >= 0 || Q.n == NG || prm.pricing == 1) {
+        if (r >= 0 || Q.n == NG) {
             flush(P, Q, Q.n + 1);
             Q.n = 0;
             if (r >= 0) return r;
