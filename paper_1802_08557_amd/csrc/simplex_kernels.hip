@@ -288,9 +288,9 @@ __device__ __forceinline__ void push(LP<T, NT> &P, int l, int e, T de, int ne, F
             pr[j] = w;
             return;
         }
-        // The rows of this column, eight loads in flight; the squares that steepest
+        // The rows of this column, four loads in flight; the squares that steepest
         // edge sums in the order of its own pass (simplex).
-        constexpr int R = 16 / int(sizeof(T)), U = 8;
+        constexpr int R = 16 / int(sizeof(T)), U = 4;
         T *tj = P.tab + j, acc[R];
 #pragma unroll
         for (int q = 0; q < R; ++q) acc[q] = T(0);
@@ -902,7 +902,9 @@ __device__ __forceinline__ void reject_lp(const LP<T, NT> &P, const SolveArgs &a
     }
 }
 
-template <typename T, int NT>
+// STEEP: steepest-edge pricing, a kernel of its own so that its code costs the
+// default rule's no registers (in one kernel 500 x 500 FP64 took 8.2 ms, not 7.3).
+template <typename T, int NT, bool STEEP>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void simplex_kernel(SolveArgs a)
 {
     extern __shared__ __align__(16) char smem[];
@@ -1008,7 +1010,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void si
         P.ld = in_lds ? lds_tab_ld(P.N) : slot_tab_ld(P.N, int(sizeof(T)));
         const int64_t room = (lds - L.win - (in_lds ? in_lds_bytes + 16 : 0)) / vec;
         // (Steepest edge reads every column of every pivot's tableau: no window.)
-        P.steep = a.prm.pricing == 1;
+        P.steep = STEEP;
         P.direct = P.steep || (in_lds && m <= kDirectRows);
         const int most = P.direct ? 1 : in_lds ? kMaxWindowLds : kMaxWindow;
         P.K = int(room >= most ? most : room >= 4 ? room & ~int64_t(3) : room < 1 ? 1 : room);
@@ -1045,7 +1047,10 @@ __global__ void set_i32_kernel(int32_t *p, int32_t value)
 template <typename T, int NT>
 hipError_t launch_t(const SolveArgs &a, int grid, hipStream_t s)
 {
-    hipLaunchKernelGGL((simplex_kernel<T, NT>), dim3(grid), dim3(NT), a.lds_bytes, s, a);
+    if (a.prm.pricing == 1)
+        hipLaunchKernelGGL((simplex_kernel<T, NT, true>), dim3(grid), dim3(NT), a.lds_bytes, s, a);
+    else
+        hipLaunchKernelGGL((simplex_kernel<T, NT, false>), dim3(grid), dim3(NT), a.lds_bytes, s, a);
     return hipGetLastError();
 }
 
@@ -1053,7 +1058,7 @@ template <typename T, int NT>
 int occ_t(int lds)
 {
     int blocks = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, (const void *)simplex_kernel<T, NT>,
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, (const void *)simplex_kernel<T, NT, false>,
                                                      NT, lds) != hipSuccess)
         return 0;
     return blocks;
@@ -1089,10 +1094,14 @@ int64_t simplex_ctrl_bytes(bool fp32) { return fp32 ? sizeof(Ctrl<float>) : size
 hipError_t simplex_configure(int max_lds)
 {
     const void *fns[] = {
-        (const void *)simplex_kernel<float, 64>, (const void *)simplex_kernel<double, 64>,
-        (const void *)simplex_kernel<float, 128>, (const void *)simplex_kernel<double, 128>,
-        (const void *)simplex_kernel<float, 256>, (const void *)simplex_kernel<double, 256>,
-        (const void *)simplex_kernel<float, 512>, (const void *)simplex_kernel<double, 512>};
+        (const void *)simplex_kernel<float, 64, false>, (const void *)simplex_kernel<double, 64, false>,
+        (const void *)simplex_kernel<float, 128, false>, (const void *)simplex_kernel<double, 128, false>,
+        (const void *)simplex_kernel<float, 256, false>, (const void *)simplex_kernel<double, 256, false>,
+        (const void *)simplex_kernel<float, 512, false>, (const void *)simplex_kernel<double, 512, false>,
+        (const void *)simplex_kernel<float, 64, true>, (const void *)simplex_kernel<double, 64, true>,
+        (const void *)simplex_kernel<float, 128, true>, (const void *)simplex_kernel<double, 128, true>,
+        (const void *)simplex_kernel<float, 256, true>, (const void *)simplex_kernel<double, 256, true>,
+        (const void *)simplex_kernel<float, 512, true>, (const void *)simplex_kernel<double, 512, true>};
     for (const void *f : fns) {
         hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, max_lds);
         if (e != hipSuccess) return e;

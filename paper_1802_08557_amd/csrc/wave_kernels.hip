@@ -549,13 +549,13 @@ __device__ __forceinline__ int run_group(WaveLP<T, RB> &P, Window<T, RB, NG> &Q,
     return -1;
 }
 
-template <typename T, int RB, int NG>
+template <bool STEEP, typename T, int RB, int NG>
 __device__ __forceinline__ int simplex(WaveLP<T, RB> &P, T eps_opt, const SolveParams &prm, int *enter)
 {
     int deg_run = 0;
     Window<T, RB, NG> Q;
     Q.n = 0;
-    if (prm.pricing == 1) {
+    if (STEEP && prm.pricing == 1) {
         // Steepest edge reads every column of every pivot's tableau: no window.
         T w = steepest_weight<false>(P, P.pcol, T(0));
         for (;;) {
@@ -848,7 +848,9 @@ __device__ __forceinline__ void fetch(int64_t item, Fetch<RB, PFD> &F)
 // 1e5 uniform 50 x 50 FP64 0.83 / 0.83 / 1.00 ms).
 constexpr int kGroups = 1;
 
-template <typename T, int RB, int PFD, bool WARM = false>
+// STEEP: steepest-edge pricing, apart so that its code costs the default rule's no
+// registers (in one kernel 100,000 LPs of 50 x 50 FP64 took 0.85 ms, not 0.78).
+template <typename T, int RB, int PFD, bool WARM = false, bool STEEP = WARM>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(PFD > 0 ? 2 : (sizeof(T) == 4 ? (RB == 1 ? 5 : 4) : (RB == 2 ? 2 : 3))))) void simplex_wave_kernel(SolveArgs a)
 {
     extern __shared__ __align__(16) char smem[];
@@ -1127,7 +1129,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(PFD > 0 ? 2 
                     if (WARM && warm_ok)
                         r = dual_repair(P, pend, T(1e-5 * fmax(1.0, cnorm)), T(a.prm.tol_feas * (1.0 + bnorm)), a.prm);
                 }
-                if (r == kPrimal) r = simplex<T, RB, NG>(P, eps_opt, a.prm, &enter);
+                if (r == kPrimal) r = simplex<STEEP, T, RB, NG>(P, eps_opt, a.prm, &enter);
                 if (phase == 2) {
                     status = r;
                     if (WARM && warm_ok) warm_defer = status != kOptimal;
@@ -1237,10 +1239,10 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(PFD > 0 ? 2 
 }
 
 
-template <typename T, int RB, int PFD, bool WARM = false>
+template <typename T, int RB, int PFD, bool WARM = false, bool STEEP = WARM>
 hipError_t launch_t(const SolveArgs &a, int grid, hipStream_t s)
 {
-    hipLaunchKernelGGL((simplex_wave_kernel<T, RB, PFD, WARM>), dim3(grid), dim3(64), a.lds_bytes, s, a);
+    hipLaunchKernelGGL((simplex_wave_kernel<T, RB, PFD, WARM, STEEP>), dim3(grid), dim3(64), a.lds_bytes, s, a);
     return hipGetLastError();
 }
 
@@ -1257,6 +1259,9 @@ int occ_t(int lds)
 template <typename T>
 hipError_t launch_rb(int rb, bool pf, const SolveArgs &a, int grid, hipStream_t s)
 {
+    if (a.prm.pricing == 1)
+        return rb == 1 ? launch_t<T, 1, 0, false, true>(a, grid, s)
+             : rb == 2 ? launch_t<T, 2, 0, false, true>(a, grid, s) : hipErrorInvalidValue;
     if (rb == 1) return pf ? launch_t<T, 1, NPF>(a, grid, s) : launch_t<T, 1, 0>(a, grid, s);
     if (rb == 2) return pf ? launch_t<T, 2, NPF>(a, grid, s) : launch_t<T, 2, 0>(a, grid, s);
     return hipErrorInvalidValue;
@@ -1312,6 +1317,10 @@ hipError_t simplex_wave_configure(int max_lds)
                          (const void *)simplex_wave_kernel<float, 2, NPF>, (const void *)simplex_wave_kernel<double, 2, NPF>,
                          (const void *)simplex_wave_kernel<float, 1, 0>,   (const void *)simplex_wave_kernel<double, 1, 0>,
                          (const void *)simplex_wave_kernel<float, 2, 0>,   (const void *)simplex_wave_kernel<double, 2, 0>,
+                         (const void *)simplex_wave_kernel<float, 1, 0, false, true>,
+                         (const void *)simplex_wave_kernel<double, 1, 0, false, true>,
+                         (const void *)simplex_wave_kernel<float, 2, 0, false, true>,
+                         (const void *)simplex_wave_kernel<double, 2, 0, false, true>,
                          (const void *)simplex_wave_kernel<double, 1, 0, true>,
                          (const void *)simplex_wave_kernel<double, 2, 0, true>};
     for (const void *f : fns) {
