@@ -282,9 +282,9 @@ __device__ __forceinline__ void push(LP<T, NT> &P, int l, int e, T de, int ne, F
         const T d = fma(-de, w, j == e ? T(0) : P.obj[j]);
         P.obj[j] = d;
         const int bj = j == e ? bl : P.nonb[j];
+        if (!P.steep) f(j, d, bj, T(1));
         tl[j] = w;
         if (!P.direct) {
-            f(j, d, bj, T(1));
             pr[j] = w;
             return;
         }
@@ -309,6 +309,7 @@ __device__ __forceinline__ void push(LP<T, NT> &P, int l, int e, T de, int ne, F
                 if (P.steep && !(P.rowf[i] & ROW_DEAD)) acc[q % R] = fma(t[q], t[q], acc[q % R]);
             }
         }
+        if (!P.steep) return;
         T s = T(1);
 #pragma unroll
         for (int q = 0; q < R; ++q) s += acc[q];
@@ -423,8 +424,12 @@ __device__ __forceinline__ int simplex(LP<T, NT> &P, T eps_opt, const SolveParam
     bool bland = prm.k_deg > 0 && deg_run >= prm.k_deg;
     auto offer = [&](int j, T d, int bj, T w) {
         const bool ok = d > eps_opt && bj < nm;
-        const T key = bland ? T(0) : P.steep ? d * d / w : d;
-        in.offer(ok && key == key, key, bj, j);
+        if (P.steep) {
+            const T key = bland ? T(0) : d * d / w;
+            in.offer(ok && key == key, key, bj, j);
+        } else {
+            in.offer(ok, bland ? T(0) : d, bj, j);
+        }
     };
     for (int j = tid; j < N; j += NT) {
         T w = T(1);
