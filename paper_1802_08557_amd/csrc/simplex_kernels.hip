@@ -54,7 +54,8 @@ struct Ctrl {
     int ng, nart, neq, bad;
     int next;
     int cnt;  // scratch tally (warm start)
-    int pad[2];
+    int inf;  // overflowed: an infinity or NaN was seen
+    int pad;
     T rv[2][8];  // block_pick: one slot per wavefront, two sets used in turn
     int ri[2][8];
     int rp[2][8];
@@ -184,7 +185,8 @@ __device__ __forceinline__ int block_pick(LP<T, NT> &P, const Best<MAX, T> &c, T
 // which it replaces rather than updates, go to tab at once and the window's
 // entries of that row and column become 0 (push), so that every entry takes
 // the operations of one sweep per pivot in their order, and the sweep (flush)
-// comes once per K pivots.
+// comes once per K pivots.  (Past the range of T the two differ: 0 times infinity
+// leaves NaN in an entry that its pivot replaced.  See overflowed.)
 //
 // Why a window: the sweep reads and writes the whole tableau, which for the
 // large LPs of a batch lives in device memory and bounds the kernel by the
@@ -487,6 +489,23 @@ __device__ __forceinline__ int simplex(LP<T, NT> &P, T eps_opt, const SolveParam
     }
 }
 
+// Whether some reduced cost or right-hand side is not finite, that is, whether the
+// window may have held an infinity or NaN: an entry of a pivot's scaled row that
+// is not finite makes its column's reduced cost so, for good, and one of its
+// column its row's right-hand side.  The caller then solves the LP again with
+// every pivot in the tableau at once (P.direct).
+template <typename T, int NT>
+__device__ __forceinline__ bool overflowed(LP<T, NT> &P)
+{
+    bool odd = false;
+    for (int j = threadIdx.x; j < P.N; j += NT) odd |= !isfinite(P.obj[j]);
+    for (int i = threadIdx.x; i < P.m; i += NT) odd |= !isfinite(P.rhs[i]);
+    if constexpr (NT == 64) return ballot(odd) != 0;
+    if (odd) P.sh->inf = 1;
+    __syncthreads();
+    return uniform(P.sh->inf) != 0;
+}
+
 // A1/A2: non-basic and basic index arrays, then the tableau rows and right-hand
 // sides (sign-normalised so every rhs is >= 0, with a -1 surplus entry per >=
 // row).  Returns whether this thread saw a non-finite entry of A.
@@ -732,89 +751,98 @@ __device__ __forceinline__ void solve_lp(LP<T, NT> &P, const SolveArgs &a, int p
     // (FP64 only: single-precision solves start from the slack basis.)
     bool warm = sizeof(T) == 8 && !invalid && a.warm_basis && !a.warm_rows && P.nart == 0 && uniform(a.status[P.k]) == ST_OPTIMAL &&
                 !(a.warm_viol && uniform(a.warm_viol[P.k]) > a.warm_max_viol);
-    if (sizeof(T) == 8 && warm && !crash<T, NT>(P, a)) {
-        // The crash stopped part-way: rebuild the slack-basis tableau.
-        warm = false;
-        __syncthreads();
-        fill_tableau<T, NT>(P);
-        P.iters = 0;
-        __syncthreads();
-    }
     if (invalid) status = ST_INVALID;
-    // Phase I where some row needs an artificial, then Phase II.
-    for (int phase = P.nart > 0 ? 1 : 2; status == ST_OPTIMAL; phase = 2) {
-        T eps_opt;
-        if (phase == 1) {
-            // Objective row: the sum of the artificial rows (in row order).
-            double dmax = 0.0;
-            for (int j = tid; j < N; j += NT) {
-                T acc = T(0);
-                for (int i = 0; i < m; ++i)
-                    if (row_sense(P.rowf[i]) != LE) acc += tab[(int64_t)i * ld + j];
-                P.obj[j] = acc;
-                dmax = fmax(dmax, fabs(double(acc)));
-            }
-            P.z = T(0);
-            for (int i = 0; i < m; ++i)
-                if (row_sense(P.rowf[i]) != LE) P.z += P.rhs[i];
+    for (bool again = false; !invalid;) {
+        if (again) {
+            // From the slack basis, the tableau rebuilt.
+            warm = again = false;
             __syncthreads();
-            eps_opt = T(a.prm.tol_opt * fmax(1.0, block_max<T, NT>(dmax, sh)));
-        } else {
-            price_out<T, NT>(P);
-            eps_opt = T(a.prm.tol_opt * fmax(1.0, cnorm));
-            if (sizeof(T) == 8 && warm) {
+            for (int i = tid; i < m; i += NT) P.rowf[i] &= ~ROW_DEAD;
+            if (tid == 0) sh->inf = 0;
+            fill_tableau<T, NT>(P);
+            P.iters = P.it1 = P.degp = 0;
+            enter = -1;
+            status = ST_OPTIMAL;
+            __syncthreads();
+        }
+        // A crash that stops part-way leaves a tableau of no use.
+        if (sizeof(T) == 8 && warm && (!crash<T, NT>(P, a) || overflowed(P))) {
+            again = true;
+            continue;
+        }
+        // Phase I where some row needs an artificial, then Phase II.
+        for (int phase = P.nart > 0 ? 1 : 2; status == ST_OPTIMAL; phase = 2) {
+            T eps_opt;
+            int r = kPrimal;
+            if (phase == 1) {
+                // Objective row: the sum of the artificial rows (in row order).
+                double dmax = 0.0;
+                for (int j = tid; j < N; j += NT) {
+                    T acc = T(0);
+                    for (int i = 0; i < m; ++i)
+                        if (row_sense(P.rowf[i]) != LE) acc += tab[(int64_t)i * ld + j];
+                    P.obj[j] = acc;
+                    dmax = fmax(dmax, fabs(double(acc)));
+                }
+                P.z = T(0);
+                for (int i = 0; i < m; ++i)
+                    if (row_sense(P.rowf[i]) != LE) P.z += P.rhs[i];
+                __syncthreads();
+                eps_opt = T(a.prm.tol_opt * fmax(1.0, block_max<T, NT>(dmax, sh)));
+            } else {
+                price_out<T, NT>(P);
+                eps_opt = T(a.prm.tol_opt * fmax(1.0, cnorm));
                 // Single-precision level for the start's reduced costs.
-                const int r = dual_repair<T, NT>(P, T(1e-5 * fmax(1.0, cnorm)), T(a.prm.tol_feas * (1.0 + bnorm)),
-                                                 a.prm);
-                if (r == -1) {
-                    // Neither primal nor dual feasible: solve from the slack basis.
-                    warm = false;
+                if (sizeof(T) == 8 && warm)
+                    r = dual_repair<T, NT>(P, T(1e-5 * fmax(1.0, cnorm)), T(a.prm.tol_feas * (1.0 + bnorm)), a.prm);
+            }
+            if (r == kPrimal) r = simplex<T, NT>(P, eps_opt, a.prm, &enter);
+            // -1: a start neither primal nor dual feasible.
+            if (r == -1 || (!P.direct && overflowed(P))) {
+                P.direct |= r != -1;
+                again = true;
+                break;
+            }
+            if (phase == 2) {
+                status = r;
+                break;
+            }
+            P.it1 = P.iters;
+            enter = -1;
+            if (r == ST_ITER) status = ST_ITER;
+            else if (r == ST_UNBOUNDED) status = ST_NUMERICAL;
+            else if (-double(P.z) < -a.prm.tol_feas * (1.0 + bnorm)) status = ST_INFEASIBLE;
+            if (status != ST_OPTIMAL) break;
+            // Drive basic artificials out, in row order; drop redundant rows.
+            const T tol_piv = T(a.prm.tol_piv);
+            for (int i = 0;; ++i) {
+                if (i == m || P.p == P.K) flush(P);
+                if (i == m) break;
+                __syncthreads();
+                if (uniform(P.basis[i]) < n + m) continue;
+                T best = T(0);
+                Best<false, T> at;
+                row(P, i, [&](int j, T t) {
+                    const int bj = P.nonb[j];
+                    at.offer(bj < n + m && fabs(t) > tol_piv, T(0), bj, j);
+                });
+                const int e = block_pick(P, at, best);
+                if (e >= 0) {
+                    const T de = P.obj[e];
+                    const int ne = uniform(P.nonb[e]);
+                    column(P, e, [](int, T) {});
                     __syncthreads();
-                    fill_tableau<T, NT>(P);
-                    P.iters = 0;
-                    __syncthreads();
-                    price_out<T, NT>(P);
-                } else if (r != kPrimal) {
-                    status = r;
-                    break;
+                    push(P, i, e, de, ne, [](int, T, int, T) {});
+                } else if (tid == i % NT) {
+                    P.rowf[i] |= ROW_DEAD;
                 }
             }
-        }
-        const int r = simplex<T, NT>(P, eps_opt, a.prm, &enter);
-        if (phase == 2) {
-            status = r;
-            break;
-        }
-        P.it1 = P.iters;
-        enter = -1;
-        if (r == ST_ITER) status = ST_ITER;
-        else if (r == ST_UNBOUNDED) status = ST_NUMERICAL;
-        else if (-double(P.z) < -a.prm.tol_feas * (1.0 + bnorm)) status = ST_INFEASIBLE;
-        if (status != ST_OPTIMAL) break;
-        // Drive basic artificials out, in row order; drop redundant rows.
-        const T tol_piv = T(a.prm.tol_piv);
-        for (int i = 0;; ++i) {
-            if (i == m || P.p == P.K) flush(P);
-            if (i == m) break;
-            __syncthreads();
-            if (uniform(P.basis[i]) < n + m) continue;
-            T best = T(0);
-            Best<false, T> at;
-            row(P, i, [&](int j, T t) {
-                const int bj = P.nonb[j];
-                at.offer(bj < n + m && fabs(t) > tol_piv, T(0), bj, j);
-            });
-            const int e = block_pick(P, at, best);
-            if (e >= 0) {
-                const T de = P.obj[e];
-                const int ne = uniform(P.nonb[e]);
-                column(P, e, [](int, T) {});
-                __syncthreads();
-                push(P, i, e, de, ne, [](int, T, int, T) {});
-            } else if (tid == i % NT) {
-                P.rowf[i] |= ROW_DEAD;
+            if (!P.direct && overflowed(P)) {
+                P.direct = again = true;
+                break;
             }
         }
+        if (!again) break;
     }
 
     // A8: extraction.  x_j = rhs of the row where j is basic, else 0;
@@ -967,7 +995,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void si
         }
 
         // A1: sign-normalise and classify rows (sense after flipping rows with b < 0).
-        if (tid == 0) sh->bad = 0;
+        if (tid == 0) sh->bad = sh->inf = 0;
         __syncthreads();
         bool bad = false;
         for (int i = tid; i < m; i += NT) {

@@ -78,6 +78,7 @@ struct WaveLP {
     T d;        // this lane's objective-row entry
     int iters, it1, degp, cap;
     bool keep;  // the tableau is read again when the current phase ends
+    bool alone; // no window
 };
 
 // Pivots that the tableau in LDS does not hold yet, oldest first in np / pr:
@@ -87,7 +88,8 @@ struct WaveLP {
 // it replaces rather than updates, are written to tab at once, and the
 // window's entries of that row and column become 0, so every entry goes
 // through the same operations in the same order as with one sweep of the
-// tableau per pivot.
+// tableau per pivot.  (Past the range of T the two differ: 0 times infinity leaves
+// NaN in an entry that its pivot replaced.  See overflowed.)
 //
 // Why a window: a pivot reads one column and one row of the tableau, and with
 // the window both cost a short chain of fmas on registers.  The sweep, which
@@ -264,24 +266,53 @@ __device__ __forceinline__ T row(const WaveLP<T, RB> &L, const Window<T, RB, NG>
     return v;
 }
 
-// Step 3 for the pivot on (l, e) of the current tableau: it becomes slot S of
-// the group being filled.  L.pcol holds the pivot column (0 for dead and
-// padding rows), rowv lane j's entry of the pivot row, prow_rhs the scaled
-// right-hand side of row l.  The objective row and every right-hand side are
-// updated in their owners' registers, and the index arrays swapped.  S = 4:
-// the slot is `slot`, known at run time, and unused slots hold 0.
+// The pivot row of (l, e) scaled: lane j's entry of the new row l, 1 / PE in
+// column e.  rowv is its entry of row l, L.pcol holds the pivot column.
+template <typename T, int RB>
+__device__ __forceinline__ T scaled_row(const WaveLP<T, RB> &L, int l, int e, T rowv)
+{
+    return (int(threadIdx.x) == e ? T(1) : rowv) / row_get<RB>(L.pcol, l);
+}
+
+// Step 3 for the pivot on (l, e) outside the tableau: the objective row, every
+// right-hand side and the index arrays are updated in their owners' registers.
+// L.pcol holds the pivot column (0 for dead and padding rows), prow the scaled
+// row, prow_rhs the scaled right-hand side of row l.
+template <typename T, int RB>
+__device__ __forceinline__ void advance(WaveLP<T, RB> &L, int l, int e, T prow, T prow_rhs)
+{
+    const int lane = threadIdx.x;
+    const bool at_e = lane == e;
+    const T de = lane_get(L.d, e);
+    L.d = fma(-de, prow, at_e ? T(0) : L.d);
+    L.z = fma(-de, prow_rhs, L.z);
+#pragma unroll
+    for (int r = 0; r < RB; ++r)
+        L.rhs[r] = lane + 64 * r == l ? prow_rhs : fma(-L.pcol[r], prow_rhs, L.rhs[r]);  // (padding rows: 0 stays 0)
+}
+
+// The variables of row l and column e change places.
+template <typename T, int RB>
+__device__ __forceinline__ void swap_index(WaveLP<T, RB> &L, int l, int e)
+{
+    const int bl = row_get<RB>(L.basis, l);
+    const int ne = lane_get(L.nonb, e);
+#pragma unroll
+    for (int r = 0; r < RB; ++r)
+        if (int(threadIdx.x) + 64 * r == l) L.basis[r] = ne;
+    if (int(threadIdx.x) == e) L.nonb = bl;
+}
+
+// The pivot becomes slot S of the group being filled.  S = 4: the slot is `slot`,
+// known at run time, and unused slots hold 0.
 template <int S, typename T, int RB, int NG>
-__device__ __forceinline__ void push(WaveLP<T, RB> &L, Window<T, RB, NG> &Q, int l, int e, T rowv, T prow_rhs,
+__device__ __forceinline__ void push(WaveLP<T, RB> &L, Window<T, RB, NG> &Q, int l, int e, T prow, T prow_rhs,
                                      int slot = S)
 {
     const int lane = threadIdx.x;
     const int m = L.m, C = L.C;
-    const T pe = row_get<RB>(L.pcol, l);
     const bool at_e = lane == e;
-    const T prow = (at_e ? T(1) : rowv) / pe;  // 1 / PE in column e
-    const T de = lane_get(L.d, e);
-    L.d = fma(-de, prow, at_e ? T(0) : L.d);
-    L.z = fma(-de, prow_rhs, L.z);
+    advance(L, l, e, prow, prow_rhs);
     const T pre = lane_get(prow, e);
     T *tab = L.tab;
     bool at_l[RB];
@@ -289,10 +320,7 @@ __device__ __forceinline__ void push(WaveLP<T, RB> &L, Window<T, RB, NG> &Q, int
     for (int r = 0; r < RB; ++r) {
         const int i = lane + 64 * r;
         at_l[r] = i == l;
-        if (i < m) {
-            L.rhs[r] = at_l[r] ? prow_rhs : fma(-L.pcol[r], prow_rhs, L.rhs[r]);
-            tab[i * L.ld + e] = at_l[r] ? pre : fma(-L.pcol[r], pre, T(0));
-        }
+        if (i < m) tab[i * L.ld + e] = at_l[r] ? pre : fma(-L.pcol[r], pre, T(0));
     }
     if (lane < C && !at_e) tab[l * L.ld + lane] = prow;
     // Row l and column e now come from tab alone.
@@ -312,13 +340,43 @@ __device__ __forceinline__ void push(WaveLP<T, RB> &L, Window<T, RB, NG> &Q, int
             Q.grp[NG].np[k][r] = mine ? w : w0;
         });
     });
-    const int bl = row_get<RB>(L.basis, l);
-    const int ne = lane_get(L.nonb, e);
-#pragma unroll
-    for (int r = 0; r < RB; ++r)
-        if (at_l[r]) L.basis[r] = ne;
-    if (at_e) L.nonb = bl;
+    swap_index(L, l, e);
 }
+
+// The pivot in the tableau itself (no pivot waits in a window): row l and column e
+// are replaced, every other entry takes its fma.
+template <typename T, int RB>
+__device__ __forceinline__ void replace(WaveLP<T, RB> &L, int l, int e, T prow, T prow_rhs)
+{
+    const int lane = threadIdx.x;
+    advance(L, l, e, prow, prow_rhs);
+    swap_index(L, l, e);
+    static_for<0, RB>([&](auto r) {
+        const int rows = min(L.m - 64 * r, 64);
+#pragma unroll 2
+        for (int i = 0; i < rows; ++i) {
+            const T a = lane_get(L.pcol[r], i);
+            T *at = L.tab + (64 * r + i) * L.ld + L.colat;
+            const T t = *at, v = 64 * r + i == l ? prow : fma(-a, prow, lane == e ? T(0) : t);
+            if (lane < L.C) *at = v;
+        }
+    });
+}
+
+// Whether some reduced cost or right-hand side is not finite, that is, whether the
+// window may have held an infinity or NaN: an entry of a pivot's scaled row that
+// is not finite makes its column's reduced cost so, for good, and one of its
+// column its row's right-hand side.  The caller then solves the LP again with
+// every pivot in the tableau at once (L.alone).
+template <typename T, int RB>
+__device__ __forceinline__ bool overflowed(const WaveLP<T, RB> &L)
+{
+    bool odd = !isfinite(L.d);
+    static_for<0, RB>([&](auto r) { odd |= !isfinite(L.rhs[r]); });
+    return ballot(odd) != 0;
+}
+
+constexpr int kAgain = 64;  // the status of such an LP until then
 
 // Slots S .. 3 of the group being filled hold no pivot.
 template <int S, typename T, int RB>
@@ -343,8 +401,8 @@ __device__ __forceinline__ void keep_group(Window<T, RB, NG> &Q)
     ++Q.n;
 }
 
-// The pivots outside the simplex loop (drive-out, crash, dual simplex): a window
-// whose slots are filled one at a time, unused ones 0.
+// The pivots of a warm start (crash, dual simplex): a window whose slots are
+// filled one at a time, unused ones 0.
 template <typename T, int RB, int NG>
 struct Pending {
     Window<T, RB, NG> Q;
@@ -367,7 +425,7 @@ struct Pending {
     // Pivot on (l, e) whose column is in L.pcol and whose row is rowv.
     __device__ __forceinline__ void pivot(WaveLP<T, RB> &L, int l, int e, T rowv)
     {
-        push<4>(L, Q, l, e, rowv, row_get<RB>(L.rhs, l) / row_get<RB>(L.pcol, l), s);
+        push<4>(L, Q, l, e, scaled_row(L, l, e, rowv), row_get<RB>(L.rhs, l) / row_get<RB>(L.pcol, l), s);
         if (++s < 4 || Q.n == NG) return;
         keep_group(Q);
         s = 0;
@@ -471,9 +529,9 @@ __device__ __forceinline__ int price_steepest(const WaveLP<T, RB> &P, bool elig,
 }
 
 // One iteration with S pivots in the group being filled.  Returns -1 to go
-// on, else the status (the group then still holds S pivots).  STEEP: steepest
-// edge, w this lane's weight.
-template <int S, bool STEEP, typename T, int RB, int NG>
+// on, else the status (the group then still holds S pivots).  ALONE: the pivot
+// goes to the tableau itself.  STEEP: steepest edge, w this lane's weight.
+template <int S, bool STEEP, bool ALONE = false, typename T, int RB, int NG>
 __device__ __forceinline__ int step(WaveLP<T, RB> &P, Window<T, RB, NG> &Q, T eps_opt, const SolveParams &prm,
                                     int &deg_run, int *enter, T w = T(1))
 {
@@ -522,12 +580,13 @@ __device__ __forceinline__ int step(WaveLP<T, RB> &P, Window<T, RB, NG> &Q, T ep
     const int l = RB == 1 ? src : lane_get(row_loc, src);
     const T th = lane_get(th_loc, src);
     if (th == T(0)) { ++deg_run; ++P.degp; } else deg_run = 0;
-    const T rowv = row<S>(P, Q, l);
+    const T prow = scaled_row(P, l, e, row<S>(P, Q, l));
     // The scaled right-hand side of row l is the ratio itself where it is positive.
     const T bl = row_get<RB>(P.rhs, l);
     T prow_rhs = th;
     if (!(bl > T(0))) prow_rhs = bl / row_get<RB>(P.pcol, l);
-    push<S>(P, Q, l, e, rowv, prow_rhs);
+    if constexpr (ALONE) replace(P, l, e, prow, prow_rhs);
+    else push<S>(P, Q, l, e, prow, prow_rhs);
     ++P.iters;
     return -1;
 }
@@ -564,8 +623,14 @@ __device__ __forceinline__ int simplex(WaveLP<T, RB> &P, T eps_opt, const SolveP
             w = steepest_weight<true>(P, Q.grp[NG].np[0], Q.grp[NG].pr[0]);
         }
     }
+    if (!STEEP && P.alone)
+        for (;;) {
+            const int r = step<0, false, true>(P, Q, eps_opt, prm, deg_run, enter);
+            if (r >= 0) return r;
+        }
     for (;;) {
         const int r = run_group<0>(P, Q, eps_opt, prm, deg_run, enter);
+        if (r >= 0 && overflowed(P)) return kAgain;
         if (r >= 0 && !P.keep) return r;
         if (r >= 0 || Q.n == NG) {
             flush(P, Q, Q.n + 1);
@@ -714,7 +779,7 @@ __device__ __forceinline__ int dual_repair(WaveLP<T, RB> &P, Pending<T, RB, NG> 
         }
         const bool feasible = !ballot(rl >= 0);
         if (feasible || W.full()) W.sweep(P);
-        if (feasible) return kPrimal;
+        if (feasible) return overflowed(P) ? kAgain : kPrimal;
         const T vmin = wave_min_f(vl);
         const uint64_t tied = ballot(rl >= 0 && vl == vmin);
         int src = __builtin_ctzll(tied);
@@ -866,10 +931,33 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(PFD > 0 ? 2 
     int64_t cur = blockIdx.x, nxt = queue.second(blockIdx.x);
     Fetch<RB, PFD> F;
     if (cur < total) fetch<RB, PFD>(cur, F);
+    // LPs to solve again pivot by pivot (see overflowed): a list through their
+    // status entries, taken up when the work items have run out.
+    int64_t redo = -1;
+    int alone = 0;  // 1: cur is one of them
     while (cur < total) {
+        asm volatile("" : "+v"(alone));  // (opaque, or the loop is copied for either value)
+        alone = uniform(alone);
         int qv = 0;
         if (lane == 0 && a.queue) qv = queue.pop(a.queue);
         const int64_t k = F.k;
+        // What F is loaded with while cur is solved (a last LP reloads itself, so the
+        // loads are unconditional and land in the registers that cur's came in).
+        const int64_t ahead = nxt < total ? nxt : !STEEP && redo >= 0 ? redo : cur;
+        // The step to that LP.
+        auto next_item = [&] {
+            if (nxt < total) {
+                cur = nxt;
+                nxt = queue.item(lane_get(qv, 0));
+            } else if (!STEEP && redo >= 0) {
+                const volatile int32_t *link = a.status;
+                cur = redo;
+                redo = uniform(link[a.ids ? int64_t(uniform(a.ids[cur])) : cur]);
+                alone = 1;
+            } else {
+                cur = total;
+            }
+        };
         WaveLP<T, RB> P;
         P.k = k;
         P.m = F.m; P.n = F.n;
@@ -1045,17 +1133,15 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(PFD > 0 ? 2 
 #pragma unroll
         for (int r = 0; r < RB; ++r) bm = fmax(bm, fabs(bv[r]));
         const double bnorm = wave_max_f(bm);
-        // The registers of F are free again: start loading the next LP.  (The
-        // last LP of a wavefront reloads itself, so the loads are unconditional
-        // and land in the registers the current LP's came in.)
-        fetch<RB, PFD>(nxt < total ? nxt : cur, F);
+        // The registers of F are free again: start loading the next LP.
+        fetch<RB, PFD>(ahead, F);
         if (!fits) {
-            cur = nxt;
-            nxt = queue.item(lane_get(qv, 0));
+            next_item();
             continue;
         }
         const bool invalid = ballot(bad) != 0;
         P.iters = 0; P.it1 = 0; P.degp = 0;
+        P.alone = alone;
         P.cap = a.prm.max_iters > 0 ? a.prm.max_iters : 50 * (m + n + (m - neq) + nart);
         P.d = T(0);
         P.z = T(0);
@@ -1066,7 +1152,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(PFD > 0 ? 2 
         // and only for all-<= LPs; any other LP is solved from the slack basis
         // right here.  An LP whose repair fails is deferred.
         bool warm_ok = false, warm_defer = false;
-        Pending<T, RB, WARM ? NG : 0> pend;
+        Pending<T, RB, NG> pend;  // warm start
         if (invalid) {
             status = kInvalid;
         } else {
@@ -1076,7 +1162,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(PFD > 0 ? 2 
                 if (warm_ok) {
                     P.keep = true;
                     pend.clear();
-                    warm_defer = !crash(P, pend, a, k);
+                    warm_defer = !crash(P, pend, a, k) || overflowed(P);
                 }
             }
             // Phase I where some row needs an artificial, then Phase II.
@@ -1130,6 +1216,10 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(PFD > 0 ? 2 
                         r = dual_repair(P, pend, T(1e-5 * fmax(1.0, cnorm)), T(a.prm.tol_feas * (1.0 + bnorm)), a.prm);
                 }
                 if (r == kPrimal) r = simplex<STEEP, T, RB, NG>(P, eps_opt, a.prm, &enter);
+                if (WARM && r == kAgain) {
+                    warm_defer = true;
+                    break;
+                }
                 if (phase == 2) {
                     status = r;
                     if (WARM && warm_ok) warm_defer = status != kOptimal;
@@ -1139,6 +1229,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(PFD > 0 ? 2 
                 enter = -1;
                 if (r == kIterLimit) status = kIterLimit;
                 else if (r == kUnbounded) status = kNumerical;
+                else if (r == kAgain) status = kAgain;
                 else if (-double(P.z) < -a.prm.tol_feas * (1.0 + bnorm)) status = kInfeasible;
                 if (status != kOptimal) break;
                 // Drive basic artificials out in row order; drop redundant rows.
@@ -1154,10 +1245,12 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(PFD > 0 ? 2 
                         if (lane < N && P.nonb < n + m) ok = fabs(tab[i * ld + lane]) > tol_piv;
                         const int e = price<T>(ok, T(0), P.nonb, true);
                         if (e >= 0) {
-                            pend.clear();
-                            pend.load_pcol(P, e);
-                            pend.pivot(P, i, e, pend.load_row(P, i));
-                            pend.sweep(P);
+#pragma unroll
+                            for (int q = 0; q < RB; ++q)
+                                P.pcol[q] = P.rowf[q] & (kRowDead | kRowPad) ? T(0) : tab[P.rowat[q] + e];
+                            const T rowv = tab[i * ld + P.colat];
+                            replace(P, i, e, scaled_row(P, i, e, rowv),
+                                    row_get<RB>(P.rhs, i) / row_get<RB>(P.pcol, i));
                         } else if (lane == bit) {
                             P.rowf[r] |= kRowDead;
                         }
@@ -1173,8 +1266,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(PFD > 0 ? 2 
                 const int slot = a.defer_base + atomicAdd(a.defer_count, 1);
                 a.defer_ids[slot] = int32_t(k);
             }
-            cur = nxt;
-            nxt = queue.item(lane_get(qv, 0));
+            next_item();
             continue;
         }
 
@@ -1231,8 +1323,19 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(PFD > 0 ? 2 
                 if (i < m) out.basis_out[P.ro + i] = (P.rowf[r] & kRowDead) ? -1 : P.basis[r];
             }
         }
-        cur = nxt;
-        nxt = queue.item(lane_get(qv, 0));
+        if (!STEEP && uniform(status) == kAgain) {
+            // Onto the list; the last LP of all is in F already.
+            if (ahead == cur) {
+                alone = 1;
+                continue;
+            }
+            const int64_t was = cur;
+            next_item();
+            if (lane == 0) *const_cast<volatile int32_t *>(a.status + k) = int32_t(redo);
+            redo = was;
+            continue;
+        }
+        next_item();
     }
     drain_memory();
     if (lane == 0) finish_launch(a.queue, a.reset_extra);
