@@ -363,6 +363,66 @@ __device__ __forceinline__ void replace(WaveLP<T, RB> &L, int l, int e, T prow, 
     });
 }
 
+// The same for steepest edge, which reads every column of every pivot's tableau:
+// returns this lane's weight in the new one (weight), so that no pass of its own is
+// left to Step 1.  Every lane stays active, those past the last column repeating it
+// to the store, because the row owners' entries are read across lanes.
+template <typename T, int RB>
+__device__ __forceinline__ T replace_and_weigh(WaveLP<T, RB> &L, int l, int e, T prow, T prow_rhs)
+{
+    const int lane = threadIdx.x;
+    advance(L, l, e, prow, prow_rhs);
+    swap_index(L, l, e);
+    prow = L.colat == e ? lane_get(prow, e) : prow;
+    // Column e starts from 0, and row l from its new entries with a multiplier of 0
+    // (0 times infinity is NaN: a scaled row that is not finite has row l left out).
+    T np[RB];
+    static_for<0, RB>([&](auto r) {
+        if (lane + 64 * r < L.m) L.tab[(lane + 64 * r) * L.ld + e] = T(0);
+        np[r] = lane + 64 * r == l ? T(0) : -L.pcol[r];
+    });
+    if (lane < L.C) L.tab[l * L.ld + lane] = prow;
+    const bool skip_l = ballot(!isfinite(prow)) != 0;
+    constexpr int R = 16 / int(sizeof(T)), U = 8;
+    T acc[R];
+#pragma unroll
+    for (int q = 0; q < R; ++q) acc[q] = T(0);
+    static_for<0, RB>([&](auto r) {
+        const int rows = min(L.m - 64 * r, 64);
+        const uint64_t dead = ballot((L.rowf[r] & kRowDead) != 0);
+        uint64_t odd = dead;  // rows whose group of U takes a look at each
+        if (skip_l && (l >> 6) == r) odd |= uint64_t(1) << (l & 63);
+        for (int i0 = 0; i0 < rows; i0 += U) {
+            T *at = L.tab + (64 * r + i0) * L.ld + L.colat;
+            if (i0 + U <= rows && !((odd >> i0) & 0xff)) {
+                T t[U];
+#pragma unroll
+                for (int q = 0; q < U; ++q) t[q] = at[q * L.ld];
+#pragma unroll
+                for (int q = 0; q < U; ++q) {
+                    t[q] = fma(lane_get(np[r], i0 + q), prow, t[q]);
+                    acc[q % R] = fma(t[q], t[q], acc[q % R]);
+                }
+#pragma unroll
+                for (int q = 0; q < U; ++q) at[q * L.ld] = t[q];
+                continue;
+            }
+#pragma unroll
+            for (int q = 0; q < U; ++q) {
+                if (i0 + q >= rows) continue;
+                const T a = lane_get(np[r], i0 + q), t0 = at[q * L.ld];
+                const T t = 64 * r + i0 + q == l ? prow : fma(a, prow, t0);
+                at[q * L.ld] = t;
+                if (!((dead >> (i0 + q)) & 1)) acc[q % R] = fma(t, t, acc[q % R]);
+            }
+        }
+    });
+    T w = T(1);
+#pragma unroll
+    for (int q = 0; q < R; ++q) w += acc[q];
+    return w;
+}
+
 // Whether some reduced cost or right-hand side is not finite, that is, whether the
 // window may have held an infinity or NaN: an entry of a pivot's scaled row that
 // is not finite makes its column's reduced cost so, for good, and one of its
@@ -459,67 +519,43 @@ __device__ __forceinline__ int price(bool elig, T d, int nonb, bool bland)
     return __builtin_ctzll(ballot(in && nonb == bmin));
 }
 
-// Weights of steepest edge: 1 + the sum of the squares of this lane's column over
-// the live rows, row i into partial sum i mod R (the workgroup kernel's order).
-// With SWEEP the one pivot given by np (this lane's rows) and pr (its column)
-// reaches the tableau on the way, so that each pivot reads and writes the tableau
-// once and no pass of its own is left to Step 1.
-template <bool SWEEP, typename T, int RB>
-__device__ __forceinline__ T steepest_weight(const WaveLP<T, RB> &P, const T (&np)[RB], T pr)
+// Weight of steepest edge: 1 + the sum of the squares of this lane's column over the
+// live rows, row i into partial sum i mod R (the workgroup kernel's order).
+template <typename T, int RB>
+__device__ __forceinline__ T weight(const WaveLP<T, RB> &P)
 {
-    const int lane = threadIdx.x;
     constexpr int R = 16 / int(sizeof(T)), U = 8;
     T acc[R];
 #pragma unroll
     for (int q = 0; q < R; ++q) acc[q] = T(0);
-    uint64_t dead[RB];
+    static_for<0, RB>([&](auto r) {
+        const int rows = min(P.m - 64 * r, 64);
+        const uint64_t dead = ballot((P.rowf[r] & kRowDead) != 0);
+#pragma unroll 1
+        for (int i0 = 0; i0 < rows; i0 += U) {
+            const T *at = P.tab + (64 * r + i0) * P.ld + P.colat;
+            T t[U];
 #pragma unroll
-    for (int r = 0; r < RB; ++r) dead[r] = ballot((P.rowf[r] & (kRowDead | kRowPad)) != 0);
-    if (lane < P.N) {
-        static_for<0, RB>([&](auto r) {
-            const int rows = min(P.m - 64 * r, 64);
-            for (int i0 = 0; i0 < rows; i0 += U) {
-                T *at = P.tab + (64 * r + i0) * P.ld + lane;
-                if (i0 + U <= rows && !((dead[r] >> i0) & 0xff)) {
-                    T t[U];
+            for (int q = 0; q < U; ++q) t[q] = at[min(q, rows - 1 - i0) * P.ld];
 #pragma unroll
-                    for (int q = 0; q < U; ++q) t[q] = at[q * P.ld];
-#pragma unroll
-                    for (int q = 0; q < U; ++q) {
-                        if constexpr (SWEEP) {
-                            t[q] = fma(lane_get(np[r], i0 + q), pr, t[q]);
-                            at[q * P.ld] = t[q];
-                        }
-                        acc[q % R] = fma(t[q], t[q], acc[q % R]);
-                    }
-                    continue;
-                }
-#pragma unroll
-                for (int q = 0; q < U; ++q) {
-                    if (i0 + q >= rows) continue;
-                    T t = at[q * P.ld];
-                    if constexpr (SWEEP) {
-                        t = fma(lane_get(np[r], i0 + q), pr, t);
-                        at[q * P.ld] = t;
-                    }
-                    if (!((dead[r] >> (i0 + q)) & 1)) acc[q % R] = fma(t, t, acc[q % R]);
-                }
-            }
-        });
-    }
+            for (int q = 0; q < U; ++q)
+                if (i0 + q < rows && !((dead >> (i0 + q)) & 1)) acc[q % R] = fma(t[q], t[q], acc[q % R]);
+        }
+    });
     T w = T(1);
 #pragma unroll
     for (int q = 0; q < R; ++q) w += acc[q];
     return w;
 }
 
-// Step 1 by steepest edge from this lane's weight.
+// Step 1 by steepest edge from this lane's weight.  (A key that is not a number --
+// both its terms overflowed -- is not eligible.)
 template <typename T, int RB>
 __device__ __forceinline__ int price_steepest(const WaveLP<T, RB> &P, bool elig, T w)
 {
-    const T key = elig ? P.d * P.d / w : T(0);
-    const uint64_t any = ballot(elig);
-    if (!any) return -1;
+    const T key = P.d * P.d / w;
+    elig &= key == key;
+    if (!ballot(elig)) return -1;
     const T best = wave_max_f(elig ? key : -t_inf<T>());
     const uint64_t tied = ballot(elig && key == best);
     if (__popcll(tied) == 1) return __builtin_ctzll(tied);
@@ -530,10 +566,10 @@ __device__ __forceinline__ int price_steepest(const WaveLP<T, RB> &P, bool elig,
 
 // One iteration with S pivots in the group being filled.  Returns -1 to go
 // on, else the status (the group then still holds S pivots).  ALONE: the pivot
-// goes to the tableau itself.  STEEP: steepest edge, w this lane's weight.
+// goes to the tableau itself.  STEEP: steepest edge, *w this lane's weight.
 template <int S, bool STEEP, bool ALONE = false, typename T, int RB, int NG>
 __device__ __forceinline__ int step(WaveLP<T, RB> &P, Window<T, RB, NG> &Q, T eps_opt, const SolveParams &prm,
-                                    int &deg_run, int *enter, T w = T(1))
+                                    int &deg_run, int *enter, T *w = nullptr)
 {
     const int lane = threadIdx.x;
     if (P.iters >= P.cap) return kIterLimit;
@@ -541,7 +577,7 @@ __device__ __forceinline__ int step(WaveLP<T, RB> &P, Window<T, RB, NG> &Q, T ep
     // Step 1.
     const bool elig = lane < P.N && P.d > eps_opt && P.nonb < P.n + P.m;
     int e;
-    if (STEEP && !bland) e = price_steepest<T, RB>(P, elig, w);
+    if (STEEP && !bland) e = price_steepest<T, RB>(P, elig, *w);
     else e = price<T>(elig, P.d, P.nonb, bland);
     if (e < 0) return kOptimal;
     // Step 2: each lane's best row (ties to the smaller basic index), then
@@ -585,7 +621,8 @@ __device__ __forceinline__ int step(WaveLP<T, RB> &P, Window<T, RB, NG> &Q, T ep
     const T bl = row_get<RB>(P.rhs, l);
     T prow_rhs = th;
     if (!(bl > T(0))) prow_rhs = bl / row_get<RB>(P.pcol, l);
-    if constexpr (ALONE) replace(P, l, e, prow, prow_rhs);
+    if constexpr (STEEP) *w = replace_and_weigh(P, l, e, prow, prow_rhs);
+    else if constexpr (ALONE) replace(P, l, e, prow, prow_rhs);
     else push<S>(P, Q, l, e, prow, prow_rhs);
     ++P.iters;
     return -1;
@@ -615,12 +652,10 @@ __device__ __forceinline__ int simplex(WaveLP<T, RB> &P, T eps_opt, const SolveP
     Window<T, RB, NG> Q;
     Q.n = 0;
     if (STEEP && prm.pricing == 1) {
-        // Steepest edge reads every column of every pivot's tableau: no window.
-        T w = steepest_weight<false>(P, P.pcol, T(0));
+        T w = weight(P);
         for (;;) {
-            const int r = step<0, true>(P, Q, eps_opt, prm, deg_run, enter, w);
+            const int r = step<0, true, true>(P, Q, eps_opt, prm, deg_run, enter, &w);
             if (r >= 0) return r;
-            w = steepest_weight<true>(P, Q.grp[NG].np[0], Q.grp[NG].pr[0]);
         }
     }
     if (!STEEP && P.alone)
@@ -790,10 +825,10 @@ __device__ __forceinline__ int dual_repair(WaveLP<T, RB> &P, Pending<T, RB, NG> 
         }
         const int l = lane_get(rl, src);
         const T tlj = W.load_row(P, l);
-        const bool el = lane < N && P.nonb < nm && tlj < -tol_piv;
+        const T ratio = (P.d < T(0) ? P.d : T(0)) / tlj;
+        const bool el = lane < N && P.nonb < nm && tlj < -tol_piv && ratio == ratio;
         if (!ballot(el)) return kInfeasible;  // row l cannot reach its bound
-        const T ratio = el ? (P.d < T(0) ? P.d : T(0)) / tlj : t_inf<T>();
-        const T rmin = wave_min_f(ratio);
+        const T rmin = wave_min_f(el ? ratio : t_inf<T>());
         const uint64_t rt = ballot(el && ratio == rmin);
         int e = __builtin_ctzll(rt);
         if (__popcll(rt) > 1) {
@@ -916,7 +951,7 @@ constexpr int kGroups = 1;
 // STEEP: steepest-edge pricing, apart so that its code costs the default rule's no
 // registers (in one kernel 100,000 LPs of 50 x 50 FP64 took 0.85 ms, not 0.78).
 template <typename T, int RB, int PFD, bool WARM = false, bool STEEP = WARM>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(PFD > 0 ? 2 : (sizeof(T) == 4 ? (RB == 1 ? 5 : 4) : (RB == 2 ? 2 : 3))))) void simplex_wave_kernel(SolveArgs a)
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(PFD > 0 ? 2 : (sizeof(T) == 4 ? (RB == 1 ? 5 : 4) - STEEP : (RB == 2 ? 2 : 3))))) void simplex_wave_kernel(SolveArgs a)
 {
     extern __shared__ __align__(16) char smem[];
     constexpr int NG = kGroups;

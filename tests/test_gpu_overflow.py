@@ -62,3 +62,17 @@ def test_windows_match_pivot_by_pivot(ctx, m, n, precision, span):
         if precision == 0:
             assert np.array_equal(st, st2)
             assert np.array_equal(obj, obj2, equal_nan=True) and np.array_equal(x, x2, equal_nan=True)
+
+
+# Steepest edge: more rows than columns (the pivot column's owners past the last
+# column take part in every sweep), weights and keys that overflow.
+@pytest.mark.parametrize("m,n,N", [(8, 7, 20000), (12, 4, 20000), (60, 9, 4000), (100, 11, 2000)])
+def test_steepest_edge_matches_workgroup_kernel(ctx, m, n, N):
+    from paper_1802_08557_amd.lpbatch import DeviceBatch
+    dev = DeviceBatch.from_host(extreme(N, m, n, m * n, 305.0))
+    st, obj, x, stats = solve(ctx, dev, pricing=1, block_threads=64)
+    for kw in (dict(), dict(block_threads=256, placement=2)):
+        st2, obj2, x2, stats2 = solve(ctx, dev, pricing=1, **kw)
+        assert np.array_equal(st, st2), np.flatnonzero(st != st2)[:5]
+        assert np.array_equal(obj, obj2, equal_nan=True) and np.array_equal(x, x2, equal_nan=True)
+        assert np.array_equal(stats[:, :3], stats2[:, :3])
