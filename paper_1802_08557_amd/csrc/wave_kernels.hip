@@ -968,7 +968,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(PFD > 0 ? 2 
     if (cur < total) fetch<RB, PFD>(cur, F);
     // LPs to solve again pivot by pivot (see overflowed): a list through their
     // status entries, taken up when the work items have run out.
-    int64_t redo = -1;
+    int redo = -1;
     int alone = 0;  // 1: cur is one of them
     while (cur < total) {
         asm volatile("" : "+v"(alone));  // (opaque, or the loop is copied for either value)
@@ -976,10 +976,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(PFD > 0 ? 2 
         int qv = 0;
         if (lane == 0 && a.queue) qv = queue.pop(a.queue);
         const int64_t k = F.k;
-        // What F is loaded with while cur is solved (a last LP reloads itself, so the
-        // loads are unconditional and land in the registers that cur's came in).
-        const int64_t ahead = nxt < total ? nxt : !STEEP && redo >= 0 ? redo : cur;
-        // The step to that LP.
+        // The step to the LP that F was loaded with.
         auto next_item = [&] {
             if (nxt < total) {
                 cur = nxt;
@@ -1168,8 +1165,10 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(PFD > 0 ? 2 
 #pragma unroll
         for (int r = 0; r < RB; ++r) bm = fmax(bm, fabs(bv[r]));
         const double bnorm = wave_max_f(bm);
-        // The registers of F are free again: start loading the next LP.
-        fetch<RB, PFD>(ahead, F);
+        // The registers of F are free again: start loading the next LP.  (The
+        // last one reloads itself, so the loads are unconditional and land in the
+        // registers the current LP's came in.)
+        fetch<RB, PFD>(nxt < total ? nxt : !STEEP && redo >= 0 ? redo : cur, F);
         if (!fits) {
             next_item();
             continue;
@@ -1360,13 +1359,13 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(PFD > 0 ? 2 
         }
         if (!STEEP && uniform(status) == kAgain) {
             // Onto the list; the last LP of all is in F already.
-            if (ahead == cur) {
+            if (nxt >= total && redo < 0) {
                 alone = 1;
                 continue;
             }
-            const int64_t was = cur;
+            const int was = int(cur);
             next_item();
-            if (lane == 0) *const_cast<volatile int32_t *>(a.status + k) = int32_t(redo);
+            if (lane == 0) *const_cast<volatile int32_t *>(a.status + P.k) = redo;
             redo = was;
             continue;
         }
