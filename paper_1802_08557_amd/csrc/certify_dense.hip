@@ -34,7 +34,6 @@ namespace {
 constexpr int kTightD = 32, kDeadD = 64;
 constexpr int DPF = 40;  // doubles of A per lane: LPs of at most 64 * 40 entries
 
-__device__ __forceinline__ void dsync() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
 __device__ __forceinline__ bool dall(bool v) { return __ballot(!v) == 0; }
 
 // Column stride of the staged A: the smallest odd number of 16-byte units that
@@ -147,7 +146,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void ce
             // then proves the LP unbounded.
             const bool origin = !__ballot(lane < m && sen != kLE && bi != 0.0);
             if (lane < n) colfl[lane] = 0;
-            dsync();
+            wave_sync();
             if (lane < m) {
                 if (v < -1 || v >= n + 2 * m) {
                     bad = true;
@@ -163,7 +162,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void ce
                     atomicAnd(&rowfl[v - n - m], ~kTightD);
                 }
             }
-            dsync();
+            wave_sync();
             const int rf = lane < m ? rowfl[lane] : 0;
             const bool isbasic = lane < n && colfl[lane] != 0;
             const uint64_t tmask = __ballot(lane < m && (rf & kTightD));
@@ -174,7 +173,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void ce
             const int spos = isbasic ? __popcll(smask & lanemask_lt(lane)) : -1;
             if (tpos >= 0) tlist[tpos] = lane;
             if (spos >= 0) slist[spos] = lane;
-            dsync();
+            wave_sync();
             const double bnorm = wave_max_f(lane < m ? fabs(bi) : 0.0), cnorm = wave_max_f(lane < n ? fabs(cj) : 0.0);
             const double tol_p = a.tol_feas * (1.0 + bnorm);
             const double tol_d = a.tol_opt * fmax(1.0, cnorm);
@@ -212,7 +211,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void ce
                 rz = (lane < K) ? sgt * btl : 0.0;
                 cs = (lane < K) ? csl : 0.0;
                 const double amax = wave_max_f(am);
-                dsync();
+                wave_sync();
                 for (int p = 0; p < K; ++p) {
                     const double vp = (lane < K && pos == kBig) ? fabs(colv) : -1.0;
                     // Every lane's reciprocal, computed while the maximum is
@@ -249,7 +248,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void ce
                         }
                     }
                     colv = nextv;
-                    dsync();
+                    wave_sync();
                 }
                 if (!ok) cert |= LP_CERT_SINGULAR_BIT;
             }
@@ -313,7 +312,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void ce
                 const double yt = __shfl(wr, pos < 64 ? pos : 0);
                 const double ysg = yt * sgt;  // dual times the row's sign
                 if (lane < K) yv[lane] = yt;
-                dsync();
+                wave_sync();
 
                 // Primal certificate: x_S and every non-tight row's slack (lane i: row i).
                 bool pf = !(lane < K) || xr >= -tol_p;
@@ -413,9 +412,9 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void ce
                         const double tol_r = a.tol_feas;
                         bool ok2 = !(lane < K) || -wd >= -tol_r;
                         double gain = (lane < K) ? __shfl(cj, sl) * -wd : 0.0;
-                        dsync();
+                        wave_sync();
                         if (lane < K) xsv[lane] = wd;  // x_S is no longer needed
-                        dsync();
+                        wave_sync();
                         if (lane < m && !(rf & kTightD)) {
                             const double sg = (rf & kRowNeg) ? -1.0 : 1.0;
                             double ad = (q < n) ? tab[q * ldm + lane] : 0.0;
@@ -456,7 +455,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void ce
                 a.fb_ids[slot] = int32_t(k);
             }
         }
-        dsync();
+        wave_sync();
         cur = nxt;
         nxt = queue.item(lane_get(qv, 0));
     }

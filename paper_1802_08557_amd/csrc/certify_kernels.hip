@@ -617,8 +617,6 @@ __global__ __launch_bounds__(NT) void certify_kernel(CertArgs a)
 // Compiler-level ordering point for a wavefront's own LDS traffic: the
 // hardware keeps one wavefront's LDS accesses in program order, so a fence at
 // wavefront scope is all that keeps the compiler from reordering them.
-__device__ __forceinline__ void wave_sync() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
-
 __device__ __forceinline__ bool wave_all(bool v) { return __ballot(!v) == 0; }
 
 // The same certificate with one wavefront per LP and no workgroup barrier:

@@ -357,6 +357,12 @@ __device__ __forceinline__ LateArgs late_args()
     return p;
 }
 
+// Orders a wavefront's LDS and memory accesses around the call.  Lanes of one
+// wavefront that exchange data through LDS need no instruction for it -- its accesses
+// take effect in order -- but the compiler must not move one lane's read of another
+// lane's entry across the store.
+__device__ __forceinline__ void wave_sync() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
+
 __device__ __forceinline__ uint64_t lanemask_lt(int lane)
 {
     return (uint64_t(1) << lane) - 1;

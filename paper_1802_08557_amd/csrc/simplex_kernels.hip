@@ -262,8 +262,8 @@ __device__ __forceinline__ void row(LP<T, NT> &P, int l, F f)
     }
 }
 
-// Step 3 for the pivot on (l, e), whose negated column is slot p of np with
-// a barrier since: it becomes slot p of the window, or (P.direct) updates the
+// Step 3 for the pivot on (l, e), whose negated column is slot p of np, written
+// before a block_pick or a barrier: it becomes slot p of the window, or (P.direct) updates the
 // tableau.  de, ne: the entering column's reduced cost and variable.
 // f(j, d, b, s) receives every column j of this thread with its new reduced cost
 // and variable and, under steepest edge, its weight.  Ends with a barrier only when the workgroup is one wavefront;
@@ -276,6 +276,7 @@ __device__ __forceinline__ void push(LP<T, NT> &P, int l, int e, T de, int ne, F
     const int m = P.m, N = P.N, p = P.p;
     T *np = P.np + p * m, *pr = P.pr + p * N;
     T *tl = P.tab + int64_t(l) * P.ld;
+    if constexpr (NT == 64) wave_sync();  // (block_pick has a barrier for larger workgroups)
     const T pe = -np[l];
     const T prhs = P.rhs[l] / pe, pre = T(1) / pe;
     const int bl = uniform(P.basis[l]);

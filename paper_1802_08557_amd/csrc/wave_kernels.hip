@@ -173,6 +173,7 @@ __device__ __forceinline__ void flush_tiles(WaveLP<T, RB> &L, const Window<T, RB
     Ptr at = place(0);
     Row c;
     static_for<0, NCT>([&](auto ct) { c[ct] = {T(0), T(0), T(0), T(0)}; });
+    wave_sync();
     load(at, c);
     // Whole row tiles, the next one's reads in flight during the products.
     static_for<0, 4 * RB>([&](auto rt) {
@@ -228,6 +229,7 @@ __device__ __forceinline__ void flush(WaveLP<T, RB> &L, Window<T, RB, NG> &Q, in
     else if (nct == 3) flush_tiles<3>(L, Q, count);
     else if (nct == 2) flush_tiles<2>(L, Q, count);
     else flush_tiles<1>(L, Q, count);
+    wave_sync();
 }
 
 // This lane's rows of column e of the current tableau, S pivots in the group
@@ -323,6 +325,7 @@ __device__ __forceinline__ void push(WaveLP<T, RB> &L, Window<T, RB, NG> &Q, int
         if (i < m) tab[i * L.ld + e] = at_l[r] ? pre : fma(-L.pcol[r], pre, T(0));
     }
     if (lane < C && !at_e) tab[l * L.ld + lane] = prow;
+    wave_sync();
     // Row l and column e now come from tab alone.
     static_for<0, NG + 1>([&](auto g) {
         if (g < NG && NG - g > Q.n) return;
@@ -361,6 +364,7 @@ __device__ __forceinline__ void replace(WaveLP<T, RB> &L, int l, int e, T prow, 
             if (lane < L.C) *at = v;
         }
     });
+    wave_sync();
 }
 
 // The same for steepest edge, which reads every column of every pivot's tableau:
@@ -382,6 +386,7 @@ __device__ __forceinline__ T replace_and_weigh(WaveLP<T, RB> &L, int l, int e, T
         np[r] = lane + 64 * r == l ? T(0) : -L.pcol[r];
     });
     if (lane < L.C) L.tab[l * L.ld + lane] = prow;
+    wave_sync();
     const bool skip_l = ballot(!isfinite(prow)) != 0;
     constexpr int R = 16 / int(sizeof(T)), U = 8;
     T acc[R];
@@ -417,6 +422,7 @@ __device__ __forceinline__ T replace_and_weigh(WaveLP<T, RB> &L, int l, int e, T
             }
         }
     });
+    wave_sync();
     T w = T(1);
 #pragma unroll
     for (int q = 0; q < R; ++q) w += acc[q];
@@ -1058,6 +1064,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(PFD > 0 ? 2 
         P.colat = min(lane, C - 1);
 
         // A2: index arrays and the tableau (row-major in LDS).
+        wave_sync();  // colrow, rowid
         P.nonb = kBig;
         const double cj = fresh_copy(F.cv);
         if (fits) {
@@ -1142,6 +1149,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(PFD > 0 ? 2 
                 }
             }
             // Rows with b < 0 are negated (sign normalisation).
+            wave_sync();
 #pragma unroll
             for (int r = 0; r < RB; ++r) {
                 uint64_t neg = ballot(lane + 64 * r < m && (P.rowf[r] & kRowNeg));
@@ -1159,6 +1167,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(PFD > 0 ? 2 
                     for (int g = 0; g < ng; ++g) tab[i * ld + n + g] = (sc[r] == n + g) ? T(-1) : T(0);
             }
         }
+        wave_sync();
         }  // fits
         const double cnorm = wave_max_f(fabs(cj));
         double bm = 0.0;
@@ -1308,7 +1317,9 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(PFD > 0 ? 2 
         const auto &out = *late_args();
         // The tableau is free now: x is staged in its place.
         T *xv = tab;
+        wave_sync();
         if (lane < n) xv[lane] = T(0);
+        wave_sync();
         if (status == kOptimal) {
 #pragma unroll
             for (int r = 0; r < RB; ++r) {
@@ -1317,6 +1328,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(PFD > 0 ? 2 
                 if (i < m && bvr < n && !(P.rowf[r] & kRowDead)) xv[bvr] = P.rhs[r];
             }
         }
+        wave_sync();
         const double xj = (lane < n) ? double(xv[lane]) : 0.0;
         if (lane < n) out.x[P.co + lane] = (status == kOptimal) ? xj : __builtin_nan("");
         double z = (lane < n) ? fma(cj, xj, 0.0) : 0.0;
