@@ -61,6 +61,8 @@ struct SolveArgs {
     int32_t *defer_count;     //   from defer_ids[defer_base] on (the workgroup kernel
     int32_t defer_base;       //   then drains them)
     int32_t lds_bytes;        // dynamic LDS of each workgroup
+    int32_t least_window;     // workgroup kernel: pivots that the window beside a tableau in LDS
+                              // must hold (>= kLeastWindow), or it goes to device memory
     int32_t force_hbm;        // 1: never keep the tableau in LDS
     int32_t refine_stats;     // 1: a re-solve -- pivots go to stats[4], stats[3] = 1
     // Warm start of a re-solve (wavefront kernel, FP64, all-<= LPs): LP k
@@ -243,6 +245,9 @@ hipError_t simplex_wave_configure(int max_lds);
 // instead of through a window of deferred pivots.
 constexpr int kDirectRows = 12;
 
+// The least window (pivots) that the workgroup kernel asks for beside its arrays.
+constexpr int kLeastWindow = 2;
+
 // LDS of the workgroup kernel for an LP of m rows and N non-basic columns (byte
 // offsets): control block, index arrays, right-hand sides, reduced costs, then
 // the window of deferred pivots (a column of m and a row of N entries each),
@@ -272,6 +277,10 @@ __host__ __device__ inline LdsLayout lds_layout(int m, int N, int64_t tsize, int
 // multiple of four, so that walking a column spreads over the banks; in device
 // memory: whole cache lines of 128 bytes.
 __host__ __device__ inline int lds_tab_ld(int N) { return N & 3 ? N : N + 1; }
+__host__ __device__ inline int64_t lds_tab_bytes(int m, int N, int tsize)
+{
+    return int64_t(tsize) * m * lds_tab_ld(N);
+}
 __host__ __device__ inline int slot_tab_ld(int N, int tsize)
 {
     const int R = 128 / tsize;

@@ -107,10 +107,27 @@ int want_window_lds(int m_max, int n_max)
     return std::max(2, std::min(kWantWindowLds, std::min(m_max, n_max) / 2));
 }
 
-// LDS of a workgroup that holds the tableau and a window of K pivots beside it.
-int64_t lds_with_tableau(const lpb::LdsLayout &L, bool fp32, int m_max, int n_max, int K)
+// Pivots that a window beside a tableau in LDS holds at least.  A shorter one is swept
+// so often that device memory with its long window is the better place (FP64, 30
+// LPs: 80 x 232 309 us in LDS with a window of two, 245 in device memory, 290 x 65
+// 376 and 231, 23 x 712 266 and 202; 300 LPs of 80 x 232 433 and 235).  A caller who
+// asks for LDS gets it wherever the kernel can work at all.
+int least_window_lds(int placement)
 {
-    return L.window(K) + int64_t(m_max) * lpb::lds_tab_ld(n_max) * (fp32 ? 4 : 8) + 16;
+    return placement == LP_PLACE_LDS ? lpb::kLeastWindow : kLeastWindowLds;
+}
+
+// LDS of a workgroup that holds the tableau and a window of K pivots beside it -- or,
+// where that does not fit, of as few as a window may hold; 0 where that does not either.
+int64_t lds_with_tableau(const lpb::LdsLayout &L, bool fp32, int m_max, int n_max, int K, int placement, int64_t budget)
+{
+    const int64_t tab = lpb::lds_tab_bytes(m_max, n_max, fp32 ? 4 : 8);
+    for (int k : {K, std::min(K, kLeastWindowLds)}) {
+        const int64_t lds = L.window(k) + tab + 16;  // (the kernel may round its window down by 16 bytes)
+        if (lds <= budget) return lds;
+    }
+    const int64_t lds = L.window(least_window_lds(placement)) + tab;
+    return lds <= budget ? lds : 0;
 }
 
 // Workgroups of nt threads that a CU gets of a launch over num LPs when nothing
@@ -134,8 +151,9 @@ int block_threads(const lp_ctx *ctx, bool fp32, int m_max, int n_max, bool force
 {
     const int64_t cells = int64_t(m_max + 1) * (n_max + 1);
     const lpb::LdsLayout L = lpb::lds_layout(m_max, n_max, fp32 ? 4 : 8, lpb::simplex_ctrl_bytes(fp32));
-    const int64_t lds = lds_with_tableau(L, fp32, m_max, n_max, std::min(kLeastWindowLds, want_window_lds(m_max, n_max)));
-    if (force_hbm || lds > lds_budget(ctx, placement)) return cells <= 64 * 64 ? 64 : cells <= 256 * 256 ? 256 : 512;
+    const int64_t lds = lds_with_tableau(L, fp32, m_max, n_max, std::min(kLeastWindowLds, want_window_lds(m_max, n_max)),
+                                         placement, lds_budget(ctx, placement));
+    if (force_hbm || !lds) return cells <= 64 * 64 ? 64 : cells <= 256 * 256 ? 256 : 512;
     const int64_t per_cu = std::min<int64_t>(ctx->lds_per_cu / lds, want_per_cu(ctx, 64, num));
     if (per_cu >= 7) return 64;
     if (cells <= 2048 && std::max(m_max, n_max) <= 128) return cells <= 512 || m_max > lpb::kDirectRows ? 64 : 128;
@@ -149,20 +167,21 @@ int plan_block(const lp_ctx *ctx, bool fp32, int nt, int m_max, int n_max, bool 
     const int ncol_worst = n_max + m_max;
     // The launch must hold the index arrays and a window of two pivots for every
     // LP whatever its surplus columns; budgets are for the common case of none.
-    const int64_t least = lpb::lds_layout(m_max, ncol_worst, ts, ctrl).window(2);
+    const int64_t least = lpb::lds_layout(m_max, ncol_worst, ts, ctrl).window(lpb::kLeastWindow);
     if (least > ctx->max_lds)
         return fail(LP_ERR_ARG, "LP of %d rows x %d columns needs %lld bytes of LDS for its index arrays "
                     "(device limit %d)", m_max, ncol_worst, (long long)least, ctx->max_lds);
     const lpb::LdsLayout L = lpb::lds_layout(m_max, n_max, ts, ctrl);
     const int want = want_per_cu(ctx, nt, num), budget = int(lds_budget(ctx, placement));
-    auto with_tab = [&](int K) { return std::max(least, lds_with_tableau(L, fp32, m_max, n_max, K)); };
+    auto with_tab = [&](int K) { return lds_with_tableau(L, fp32, m_max, n_max, K, placement, budget); };
     auto per_cu = [&](int64_t lds) { return lpb::simplex_blocks_per_cu(fp32, nt, int(lds)); };
-    const int K = want_window_lds(m_max, n_max), K_least = std::min(K, kLeastWindowLds);
-    int64_t lds = std::max(least, std::min<int64_t>(ctx->max_lds, L.window(kWantWindow)));
-    if (!force_hbm && with_tab(K_least) <= budget) {
+    const int K = want_window_lds(m_max, n_max);
+    int64_t lds = std::min<int64_t>(ctx->max_lds, L.window(kWantWindow));
+    if (!force_hbm && with_tab(K)) {
         lds = with_tab(K);
-        if (lds > budget || per_cu(lds) < want) lds = with_tab(K_least);
+        if (per_cu(lds) < want) lds = with_tab(std::min(K, kLeastWindowLds));
     }
+    lds = std::max(least, lds);
     B.per_cu = std::min(per_cu(lds), want);
     if (B.per_cu < 1) return fail(LP_ERR_HIP, "occupancy query failed for %d threads, %lld B LDS", nt, (long long)lds);
     // Each workgroup takes the CU's LDS / per_cu: longer windows, and every LP
@@ -268,6 +287,7 @@ int queue_pass(lp_ctx *ctx, const Plan &P, lpb::SolveArgs a, const lp_options &o
     BlockPlan B;
     if (int rc = plan_block(ctx, fp32, nt, P.m_max, P.n_max, a.force_hbm, opts.placement, P.num, B)) return rc;
     a.lds_bytes = int32_t(B.lds);
+    a.least_window = least_window_lds(opts.placement);
     a.slot_bytes = B.slot_bytes;
     // When the wavefront kernel was offered every LP, this launch only drains
     // the few it deferred: one workgroup per CU is plenty and keeps its end cheap.
@@ -369,6 +389,7 @@ int launch_block(lp_ctx *ctx, bool fp32, lpb::SolveArgs a, const BinLaunch &B, c
     if (int rc = plan_block(ctx, fp32, B.nt, B.m_max, B.n_max, B.force_hbm, B.placement, num, L)) return rc;
     a.force_hbm = B.force_hbm;
     a.lds_bytes = int32_t(L.lds);
+    a.least_window = least_window_lds(B.placement);
     a.slot_bytes = L.slot_bytes;
     int64_t grid = std::min<int64_t>(num, int64_t(L.per_cu) * ctx->num_cu);
     if (grid_cap > 0) grid = std::min(grid, grid_cap);

@@ -987,7 +987,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void si
         P.rowf = reinterpret_cast<int *>(smem + L.rowf);
         P.colrow = reinterpret_cast<int *>(smem + L.colrow);
         P.rhs = reinterpret_cast<T *>(smem + L.rhs);
-        if (L.window(2) > int64_t(a.lds_bytes)) {
+        if (L.window(kLeastWindow) > int64_t(a.lds_bytes)) {
             reject_lp<T, NT>(P, a);
             __syncthreads();
             item = uniform(sh->next);
@@ -1036,11 +1036,11 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void si
         P.nonb = reinterpret_cast<int *>(smem + L.nonb);
         P.obj = reinterpret_cast<T *>(smem + L.obj);
         P.pr = reinterpret_cast<T *>(smem + L.win);
-        // The tableau in LDS when it fits beside a window of at least two
-        // pivots; the window takes what is left, in whole groups of four.
+        // The tableau in LDS when it fits beside the least window; the window
+        // takes what is left, in whole groups of four.
         const int64_t lds = a.lds_bytes, vec = int64_t(sizeof(T)) * (m + P.N);
-        const int64_t in_lds_bytes = int64_t(sizeof(T)) * m * lds_tab_ld(P.N);
-        const bool in_lds = !a.force_hbm && L.window(2) + in_lds_bytes <= lds;
+        const int64_t in_lds_bytes = lds_tab_bytes(m, P.N, sizeof(T));
+        const bool in_lds = !a.force_hbm && L.window(a.least_window) + in_lds_bytes <= lds;
         P.ld = in_lds ? lds_tab_ld(P.N) : slot_tab_ld(P.N, int(sizeof(T)));
         const int64_t room = (lds - L.win - (in_lds ? in_lds_bytes + 16 : 0)) / vec;
         // (Steepest edge reads every column of every pivot's tableau: no window.)
@@ -1051,7 +1051,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void si
         P.np = P.pr + int64_t(P.K) * P.N;
         P.p = 0;
         const int64_t slot_need = int64_t(sizeof(T)) * m * P.ld;
-        if (L.window(2) > lds || (!in_lds && (!a.scratch || slot_need > a.slot_bytes))) {
+        if (L.window(kLeastWindow) > lds || (!in_lds && (!a.scratch || slot_need > a.slot_bytes))) {
             reject_lp<T, NT>(P, a);
         } else if (in_lds) {
             P.tab = reinterpret_cast<T *>(smem + L.window(P.K));
