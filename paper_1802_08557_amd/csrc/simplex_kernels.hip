@@ -218,13 +218,15 @@ __device__ __forceinline__ void column(LP<T, NT> &P, int e, F f)
     const int m = P.m, N = P.N, p = P.p;
     T *np = P.np;
     const T *pe = P.pr + e;
-    // Two rows a turn: their loads from the tableau are in flight together.
+    // Two rows a turn: their loads from the tableau are in flight together.  (The walk
+    // over the window in turns of eight pivots against four: FP32 2,000 LPs of 117 x
+    // 150 667 against 705 us, 300 of 16 x 100 90 and 98 us, FP64 within 2 %.)
     for (int i = threadIdx.x; i < m; i += 2 * NT) {
         const int i1 = i + NT;
         const bool two = i1 < m;
         const int ib = two ? i1 : i;
         T a0 = P.tab[int64_t(i) * P.ld + e], a1 = P.tab[int64_t(ib) * P.ld + e];
-#pragma unroll 4
+#pragma unroll 8
         for (int k = 0; k < p; ++k) {
             const T s = pe[k * N];
             a0 = fma(np[k * m + i], s, a0);
@@ -251,7 +253,7 @@ __device__ __forceinline__ void row(LP<T, NT> &P, int l, F f)
         const bool two = j1 < N;
         const int jb = two ? j1 : j;
         T t0 = tl[j], t1 = tl[jb];
-#pragma unroll 4
+#pragma unroll 8
         for (int k = 0; k < p; ++k) {
             const T s = nl[k * m];
             t0 = fma(s, pr[k * N + j], t0);
