@@ -88,6 +88,12 @@ int64_t lds_budget(const lp_ctx *ctx, int placement)
     return placement == LP_PLACE_LDS ? ctx->max_lds : ctx->max_lds / 3;
 }
 
+// LDS is handed out in units of 1,280 bytes (a CU has 128 of them), which the occupancy
+// query does not know: a third of a CU rounded to anything else leaves room for two
+// workgroups, and a launch over 600 LPs then takes two rounds (12 x 100 FP64 101 us
+// against 80, 16 x 100 106 and 83).
+constexpr int64_t kLdsUnit = 1280;
+
 // LDS of one workgroup of the workgroup kernel and how many of them share a
 // CU, for LPs of at most m_max x n_max.
 struct BlockPlan {
@@ -186,7 +192,7 @@ int plan_block(const lp_ctx *ctx, bool fp32, int nt, int m_max, int n_max, bool 
     if (B.per_cu < 1) return fail(LP_ERR_HIP, "occupancy query failed for %d threads, %lld B LDS", nt, (long long)lds);
     // Each workgroup takes the CU's LDS / per_cu: longer windows, and every LP
     // whose tableau fits there is solved from LDS instead of a device-memory slot.
-    const int64_t share = std::min<int64_t>(ctx->max_lds, (int64_t(ctx->lds_per_cu) / B.per_cu) & ~int64_t(255));
+    const int64_t share = std::min<int64_t>(ctx->max_lds, int64_t(ctx->lds_per_cu) / B.per_cu / kLdsUnit * kLdsUnit);
     if (share > lds && per_cu(share) >= B.per_cu) lds = share;
     B.lds = lds;
     B.slot_bytes = lpb::align16(int64_t(m_max) * lpb::slot_tab_ld(ncol_worst, int(ts)) * ts);
