@@ -152,7 +152,9 @@ int want_per_cu(const lp_ctx *ctx, int nt, int64_t num)
 // 1.87 ms; of 12 x 300 2.95, 2.63, 2.15 ms; 30 LPs of 200 x 10 139, 93, 77 us).
 // The smallest have too little to share out between the barriers (214 LPs of 24 x 70
 // 73 us with 64, 76 us with 128; of 10 x 91, whose pivots update every entry at
-// once, 73 and 64 us).
+// once, 73 and 64 us).  Three LPs to a CU are twelve wavefronts at 256 threads, so a
+// launch of that many would take two rounds (600 of 24 x 100 127 us against 94 with
+// 128, of 40 x 100 158 and 121; with more LPs 256 threads are as good or better).
 int block_threads(const lp_ctx *ctx, bool fp32, int m_max, int n_max, bool force_hbm, int placement, int64_t num)
 {
     const int64_t cells = int64_t(m_max + 1) * (n_max + 1);
@@ -160,10 +162,10 @@ int block_threads(const lp_ctx *ctx, bool fp32, int m_max, int n_max, bool force
     const int64_t lds = lds_with_tableau(L, fp32, m_max, n_max, std::min(kLeastWindowLds, want_window_lds(m_max, n_max)),
                                          placement, lds_budget(ctx, placement));
     if (force_hbm || !lds) return cells <= 64 * 64 ? 64 : cells <= 256 * 256 ? 256 : 512;
-    const int64_t per_cu = std::min<int64_t>(ctx->lds_per_cu / lds, want_per_cu(ctx, 64, num));
+    const int64_t want = want_per_cu(ctx, 64, num), per_cu = std::min<int64_t>(ctx->lds_per_cu / lds, want);
     if (per_cu >= 7) return 64;
     if (cells <= 2048 && std::max(m_max, n_max) <= 128) return cells <= 512 || m_max > lpb::kDirectRows ? 64 : 128;
-    return per_cu >= 4 ? 128 : 256;
+    return per_cu >= 4 || (per_cu == 3 && want == 3) ? 128 : 256;
 }
 
 int plan_block(const lp_ctx *ctx, bool fp32, int nt, int m_max, int n_max, bool force_hbm, int placement,
