@@ -203,11 +203,14 @@ typedef enum { LP_PRICE_DANTZIG = 0, LP_PRICE_STEEPEST_EDGE = 1 } lp_pricing;
  * kernel takes is one launch as well.  With LP_FLAG_AUTOTUNE, a launch whose
  * bin is not yet in the context's table -- size bins 0..3 by tableau cells
  * ((m+1)(n+1) <= 64^2, 128^2, 256^2, larger) for batches of one size, bin 4
- * for the launch of a mixed batch -- is first timed on a sample of up to 512
- * of its LPs for each workgroup size (64, 128, 256, 512) and placement (LDS
- * when it fits, or device memory), and the fastest is kept in the context for
- * later calls.  The call is then synchronous; results are as without the
- * flag. */
+ * for the launch of a mixed batch -- is first timed on a sample of up to 2,048
+ * of its LPs, planned as the whole launch will be: the launch it would get
+ * without the flag, and each workgroup size (64, 128, 256, 512) with each
+ * placement (automatic, LDS wherever it fits, device memory).  Candidates that
+ * beat the untuned launch on the sample are timed against it on the whole
+ * launch, and the fastest is kept in the context for later calls.  A placement
+ * that the caller asks for still holds.  The call is then synchronous; results
+ * are as without the flag. */
 #define LP_FLAG_AUTOTUNE 4u
 
 void lp_options_init(lp_options *opts);

@@ -130,7 +130,7 @@ struct HostPipe {
 // Tuned launch of one size bin of the workgroup kernel.
 struct TuneEntry {
     int nt;         // workgroup size
-    int force_hbm;  // 1: tableaux in device-memory slots; 0: in LDS whenever they fit
+    int placement;  // as lp_options.placement: 0, LP_PLACE_LDS or LP_PLACE_HBM
 };
 
 inline int tune_key(int bin, bool fp32) { return bin * 2 + (fp32 ? 1 : 0); }

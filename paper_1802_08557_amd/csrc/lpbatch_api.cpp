@@ -355,11 +355,6 @@ int bin_of(int64_t m, int64_t n)
     return cells <= 64 * 64 ? 0 : cells <= 128 * 128 ? 1 : cells <= 256 * 256 ? 2 : 3;
 }
 
-// Untuned workgroup size: two workgroups of 256 threads per CU hide more of each
-// pivot's latency than one of 512 (uneven 10..300 batch FP64 66 against 79 ms,
-// FP32 46 against 70 ms).
-int default_threads(int) { return 256; }
-
 // FNV-1a over the batch's shapes and the planning flags (the plan cache key).
 uint64_t shape_hash(int64_t num, const int32_t *m, const int32_t *n, uint32_t flags)
 {
@@ -384,6 +379,7 @@ struct BinLaunch {
     int nt = 64;
     bool force_hbm = false;
     int placement = 0;  // lp_options.placement of the call (LP_PLACE_LDS lifts the budget)
+    int64_t plan_num = 0;  // LPs that the launch is planned for; 0: those it gets
 };
 
 // One persistent launch of the workgroup kernel over the work items
@@ -394,7 +390,9 @@ int launch_block(lp_ctx *ctx, bool fp32, lpb::SolveArgs a, const BinLaunch &B, c
                  hipStream_t stream, bool timing, const char *name)
 {
     BlockPlan L;
-    if (int rc = plan_block(ctx, fp32, B.nt, B.m_max, B.n_max, B.force_hbm, B.placement, num, L)) return rc;
+    if (int rc = plan_block(ctx, fp32, B.nt, B.m_max, B.n_max, B.force_hbm, B.placement,
+                            B.plan_num ? B.plan_num : num, L))
+        return rc;
     a.force_hbm = B.force_hbm;
     a.lds_bytes = int32_t(L.lds);
     a.least_window = least_window_lds(B.placement);
@@ -417,45 +415,70 @@ int launch_block(lp_ctx *ctx, bool fp32, lpb::SolveArgs a, const BinLaunch &B, c
     return LP_OK;
 }
 
-// Trial launches of one bin's sample: every (workgroup size, placement)
-// candidate is timed with events on `stream` and the fastest stored in the
-// context's table.  Synchronous.  The sampled LPs' outputs are overwritten
-// by the real solve that follows.
-int autotune_bin(lp_ctx *ctx, bool fp32, const lpb::SolveArgs &a, BinLaunch B, int bin, const int32_t *d_sample,
-                 int64_t n_sample, int32_t *q, hipStream_t stream)
+// LPs of a launch that the autotuner times each candidate on: as many as the device
+// holds at once with the smallest workgroups.
+constexpr int64_t kTuneSample = 2048;
+
+// Trial launches of one bin, planned as the launch over all `num` LPs (d_all) will be.
+// Every candidate -- the untuned launch, then each workgroup size and placement -- is
+// timed with events on `stream` on the sample; the two best that beat the untuned one
+// by 5 % are then timed against it on the whole launch, and the fastest is stored in
+// the context's table.  (A sample favours workgroups that finish its largest LPs
+// soonest.  On samples alone 512 threads won for 10,000 mixed LPs of 10..300, whose
+// launch they slow down: FP64 75 against 59 ms, FP32 64 against 46 ms.)  Synchronous.
+// The LPs' outputs are overwritten by the real solve that follows.
+int autotune_bin(lp_ctx *ctx, bool fp32, const lpb::SolveArgs &a, BinLaunch B, int untuned_nt, int bin,
+                 const int32_t *d_all, int64_t num, const int32_t *d_sample, int64_t n_sample, int32_t *q,
+                 hipStream_t stream)
 {
     hipEvent_t e0 = lpb::take_event(ctx), e1 = lpb::take_event(ctx);
     if (!e0 || !e1) return fail(LP_ERR_HIP, "could not create timing events");
-    float best = 1e30f, best_place[2] = {1e30f, 1e30f};
-    lpb::TuneEntry choice{default_threads(bin), 0}, choice_place[2] = {choice, choice};
-    const int cand_nt[4] = {64, 128, 256, 512};
+    std::vector<lpb::TuneEntry> cand{{untuned_nt, 0}};
+    for (int placement : {0, LP_PLACE_LDS, LP_PLACE_HBM})
+        for (int nt : {64, 128, 256, 512})
+            if (placement != 0 || nt != untuned_nt) cand.push_back({nt, placement});
+    // Time of one launch of candidate t over `count` LPs of ids, kept where it is less.
+    auto trial = [&](size_t t, const int32_t *ids, int64_t count, float &best) {
+        BinLaunch T = B;
+        T.nt = cand[t].nt;
+        T.placement = cand[t].placement;
+        T.force_hbm = T.placement == LP_PLACE_HBM;
+        T.plan_num = num;
+        HIP_TRY(hipEventRecord(e0, stream));
+        int rc = launch_block(ctx, fp32, a, T, ids, count, nullptr, 0, nullptr, 0, q, stream, false, "");
+        if (rc != LP_OK) return rc;
+        HIP_TRY(hipEventRecord(e1, stream));
+        HIP_TRY(hipEventSynchronize(e1));
+        float ms = 0.f;
+        HIP_TRY(hipEventElapsedTime(&ms, e0, e1));
+        best = std::min(best, ms);
+        return int(LP_OK);
+    };
     // One untimed launch first (cold caches would otherwise count against the
-    // first candidate), then every candidate twice, its faster time kept.
-    for (int rep = -1; rep < 2; ++rep)
-        for (int hbm = 0; hbm < 2; ++hbm)
-            for (int nt : cand_nt) {
-                if (rep < 0 && (hbm || nt != cand_nt[0])) continue;
-                BinLaunch T = B;
-                T.nt = nt;
-                T.force_hbm = hbm != 0;
-                T.placement = hbm ? LP_PLACE_HBM : LP_PLACE_LDS;  // LDS whenever the tableau fits
-                HIP_TRY(hipEventRecord(e0, stream));
-                int rc = launch_block(ctx, fp32, a, T, d_sample, n_sample, nullptr, 0, nullptr, 0, q, stream,
-                                      false, "");
-                if (rc != LP_OK) return rc;
-                HIP_TRY(hipEventRecord(e1, stream));
-                HIP_TRY(hipEventSynchronize(e1));
-                float ms = 0.f;
-                HIP_TRY(hipEventElapsedTime(&ms, e0, e1));
-                if (rep >= 0 && ms < best_place[hbm]) { best_place[hbm] = ms; choice_place[hbm] = lpb::TuneEntry{nt, hbm}; }
-            }
-    // Device-memory placement only when it wins by 5 %: the sample holds at
-    // most 512 LPs, and on whole mixed batches the LDS share measured faster
-    // whenever the two were within a few percent on the sample.
-    const int pick = best_place[1] < 0.95f * best_place[0] ? 1 : 0;
-    best = best_place[pick];
-    choice = choice_place[pick];
-    ctx->tune[lpb::tune_key(bin, fp32)] = choice;
+    // first candidate), then every candidate twice.
+    float unused = 1e30f;
+    if (int rc = trial(0, d_sample, n_sample, unused)) return rc;
+    std::vector<float> best(cand.size(), 1e30f);
+    for (int rep = 0; rep < 2; ++rep)
+        for (size_t t = 0; t < cand.size(); ++t)
+            if (int rc = trial(t, d_sample, n_sample, best[t])) return rc;
+    std::vector<size_t> finals;
+    for (size_t t = 1; t < cand.size(); ++t)
+        if (best[t] < 0.95f * best[0]) finals.push_back(t);
+    std::sort(finals.begin(), finals.end(), [&](size_t x, size_t y) { return best[x] < best[y]; });
+    finals.resize(std::min<size_t>(finals.size(), 2));
+    size_t pick = finals.empty() ? 0 : finals[0];
+    if (!finals.empty() && n_sample < num) {
+        pick = 0;
+        finals.push_back(0);
+        for (size_t t : finals) best[t] = 1e30f;
+        for (int rep = 0; rep < 2; ++rep)
+            for (size_t t : finals)
+                if (int rc = trial(t, d_all, num, best[t])) return rc;
+        for (size_t t : finals)
+            if (best[t] < 0.98f * best[0] && best[t] < best[pick]) pick = t;
+    }
+    ctx->tune[lpb::tune_key(bin, fp32)] = cand[pick];
     ctx->events_used -= 2;  // give the two events back to the pool
     return LP_OK;
 }
@@ -467,6 +490,15 @@ struct BinSpan {
     int m_max, n_max;
     int64_t sample_offset, sample_count;
 };
+
+// Workgroup size of a bin's launch without tuning.  Mixed sizes: two workgroups of 256
+// threads per CU hide more of each pivot's latency than one of 512 (uneven 10..300
+// batch FP64 66 against 79 ms, FP32 46 against 70 ms).
+int untuned_threads(const lp_ctx *ctx, const Plan &P, const lp_options &opts, const BinSpan &sp)
+{
+    return P.uniform ? block_threads(ctx, P.fp32, P.m_max, P.n_max, opts.placement == LP_PLACE_HBM, opts.placement, sp.count)
+                     : 256;
+}
 
 // Main pass of an uneven batch: the wavefront kernel for the LPs it fits,
 // one workgroup-kernel launch per size bin (largest bin first), then one
@@ -482,7 +514,8 @@ int queue_binned(lp_ctx *ctx, const Plan &P, const lpb::SolveArgs &a, const lp_o
         BinLaunch B;
         B.m_max = sp.m_max;
         B.n_max = sp.n_max;
-        int rc = autotune_bin(ctx, fp32, a, B, sp.bin, d_samples + sp.sample_offset, sp.sample_count, pc.bq, stream);
+        int rc = autotune_bin(ctx, fp32, a, B, untuned_threads(ctx, P, opts, sp), sp.bin,
+                              d_block ? d_block + sp.offset : nullptr, sp.count, d_samples + sp.sample_offset, sp.sample_count, pc.bq, stream);
         if (rc != LP_OK) return rc;
     }
     bool no_defer = false;
@@ -497,10 +530,9 @@ int queue_binned(lp_ctx *ctx, const Plan &P, const lpb::SolveArgs &a, const lp_o
         B.n_max = sp.n_max;
         auto it = ctx->tune.find(lpb::tune_key(sp.bin, fp32));
         const bool tuned = it != ctx->tune.end();
-        B.nt = tuned ? it->second.nt : default_threads(sp.bin);
-        B.force_hbm = tuned && it->second.force_hbm != 0;
-        B.placement = tuned ? (B.force_hbm ? LP_PLACE_HBM : LP_PLACE_LDS) : opts.placement;
-        if (opts.placement == LP_PLACE_HBM) B.force_hbm = true;
+        B.nt = tuned ? it->second.nt : untuned_threads(ctx, P, opts, sp);
+        B.placement = tuned && opts.placement == 0 ? it->second.placement : opts.placement;
+        B.force_hbm = B.placement == LP_PLACE_HBM;
         int rc = launch_block(ctx, fp32, a, B, d_block + sp.offset, sp.count, nullptr, 0, nullptr, 0, pc.bq, stream,
                               timing, bname);
         if (rc != LP_OK) return rc;
@@ -850,13 +882,13 @@ int lp_batch_solve_ex(lp_ctx *ctx, int64_t num_lps, const double *A, const doubl
         sp.m_max = P.m0;
         sp.n_max = P.n0;
         sp.sample_offset = 0;
-        sp.sample_count = std::min<int64_t>(num_lps, 512);
+        sp.sample_count = std::min(num_lps, kTuneSample);
         for (int64_t t = 0; t < sp.sample_count; ++t) samples.push_back(int32_t(t * num_lps / sp.sample_count));
         bins.push_back(sp);
     } else if (binned) {
         // Every LP the wavefront kernel cannot take, in one launch, ordered by
         // estimated work (largest first); the autotuner's sample is every
-        // stride-th LP of that order, at most 512.
+        // stride-th LP of that order.
         std::stable_sort(block_ids.begin(), block_ids.end(),
                          [&](int32_t x, int32_t y) { return lp_cost(m[x], n[x]) > lp_cost(m[y], n[y]); });
         BinSpan sp;
@@ -867,7 +899,7 @@ int lp_batch_solve_ex(lp_ctx *ctx, int64_t num_lps, const double *A, const doubl
         sp.n_max = 0;
         for (int32_t k : block_ids) { sp.m_max = std::max(sp.m_max, m[k]); sp.n_max = std::max(sp.n_max, n[k]); }
         sp.sample_offset = 0;
-        const int64_t want = std::min<int64_t>(sp.count, 512);
+        const int64_t want = std::min(sp.count, kTuneSample);
         for (int64_t t = 0; t < want; ++t) samples.push_back(block_ids[size_t(t * sp.count / want)]);
         sp.sample_count = want;
         bins.push_back(sp);
@@ -1212,7 +1244,7 @@ int lp_ctx_tuning(lp_ctx *ctx, int32_t *entries, int cap)
             entries[4 * i + 0] = kv.first / 2;
             entries[4 * i + 1] = kv.first % 2;
             entries[4 * i + 2] = kv.second.nt;
-            entries[4 * i + 3] = kv.second.force_hbm;
+            entries[4 * i + 3] = kv.second.placement == LP_PLACE_HBM;
         }
         ++i;
     }
