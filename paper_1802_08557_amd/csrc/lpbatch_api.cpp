@@ -1066,21 +1066,27 @@ int lp_batch_solve_ex(lp_ctx *ctx, int64_t num_lps, const double *A, const doubl
             HIP_TRY(lpb::launch_certify_wave(W, ca, int(cgrid), stream));
             t.done();
         } else {
-            // One workgroup per LP.  A batch of one size wants many LPs in
-            // flight: 64 threads, LU blocks up to 32 x 32 in LDS, larger ones in the
-            // workgroup's device-memory slot (2,000 of 117 x 150: 103 us against
-            // 195 us with 256 threads; 3,000 of 300 x 200: 365 against 495 us).  A
-            // batch of mixed sizes is bound by its large LPs, whose blocks of up
-            // to 160 x 160 pay a device-memory round trip per LU step: 256 threads
-            // and blocks of up to 80 KB less the vectors in LDS (10,000 of 10..300:
-            // 12.3 -> 9.0 ms, 400 of 20..300: 3.8 -> 1.8 ms).
-            const int cnt_nt = P.uniform ? 64 : 256;
+            // One workgroup per LP.  With 64 threads, and LU blocks up to 32 x 32 in
+            // LDS (larger ones in the workgroup's device-memory slot), many LPs are
+            // in flight; with 256, and blocks of up to 80 KB less the vectors in LDS,
+            // each is done sooner.  A CU with one or two LPs is better off with 256
+            // (100 LPs of 300 x 300 122 -> 97 us, 300 of 66..80 300 -> 224, of 100..120
+            // 636 -> 350).  With more, the LU steps of large blocks, each a
+            // device-memory round trip, are worth it the larger the blocks are (64
+            // against 256 threads: 1,000 of 66..80 355 and 424 us, 1,000 of 100..120 812
+            // and 705, 2,000 of 100..120 976 and 1169, of 110..150 1617 and 1544, 3,000
+            // of 10..300 7.05 and 3.45 ms); LPs of one size are told from their bound
+            // on the block only, and the random ones have small blocks (1,000 of 300 x
+            // 300 209 and 238 us, 2,000 of 117 x 150 97 and 196).
+            const bool few = num_lps <= 2 * ctx->num_cu, some = num_lps <= 4 * ctx->num_cu;
+            const bool wide = few || (!P_full.uniform && kmax > (some ? 96 : 128));
+            const int cnt_nt = wide ? 256 : 64;
             const int64_t base = lpb::certify_lds_bytes(P_full.m_max, P_full.n_max, false);
             const int64_t kl = std::min(kmax, 32);
             const int64_t least = base + 8 * kl * kl;
             if (least > ctx->max_lds) return fail(LP_ERR_ARG, "LP too large for the certificate kernel");
             const int64_t most = std::min<int64_t>(base + 8 * int64_t(kmax) * kmax, ctx->max_lds / 2);
-            const int64_t clds = P.uniform ? least : std::max(least, most);
+            const int64_t clds = wide ? std::max(least, most) : least;
             ca.lds_bytes = int32_t(clds);
             const int per_cu = lpb::certify_blocks_per_cu(cnt_nt, int(clds));
             if (per_cu < 1) return fail(LP_ERR_HIP, "occupancy query failed for the certificate kernel");
