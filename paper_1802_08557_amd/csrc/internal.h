@@ -229,12 +229,12 @@ hipError_t simplex_configure(int max_lds);
 // One-wavefront-per-LP kernel (wave_kernels.hip) for LPs of at most 64
 // non-basic columns and 64*rb rows (rb = 1 or 2).
 // pf: the instantiation that prefetches each next LP's A into registers
-// (LPs of at most wave_prefetch_elems() entries, A not row-gathered).
+// (rb = 1, LPs of at most wave_prefetch_elems() entries, A not row-gathered).
 hipError_t launch_simplex_wave(bool fp32, int rb, bool pf, const SolveArgs &a, int grid, hipStream_t s);
 // The warm-start (repair) instantiation: FP64, no prefetch; a.warm_basis set.
 hipError_t launch_simplex_wave_warm(int rb, const SolveArgs &a, int grid, hipStream_t s);
-int simplex_wave_warm_blocks_per_cu(int rb, int lds_bytes);
-int simplex_wave_blocks_per_cu(bool fp32, int rb, bool pf, int lds_bytes);
+int simplex_wave_warm_blocks_per_cu(int rb, bool steep, int lds_bytes);
+int simplex_wave_blocks_per_cu(bool fp32, int rb, bool pf, bool steep, int lds_bytes);
 int wave_prefetch_elems();
 int64_t wave_lds_aux_bytes(int rb, bool gather);
 // LDS bytes of a wavefront tableau with m rows and `cols` columns.

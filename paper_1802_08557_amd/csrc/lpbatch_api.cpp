@@ -220,15 +220,14 @@ int launch_wave(lp_ctx *ctx, bool fp32, const lpb::SolveArgs &a, PassCounters pc
     w.defer_count = pc.defer;
     w.defer_base = defer_base;
     const bool gather = a.shared && a.row_subset;
-    const bool warm = a.warm_basis != nullptr && !fp32;
+    const bool warm = a.warm_basis != nullptr && !fp32, steep = a.prm.pricing == LP_PRICE_STEEPEST_EDGE;
     // Prefetching A one LP ahead (measured faster for 50 x 50 in both
     // precisions) when every LP's A fits the prefetch registers; larger or
-    // row-gathered LPs take the leaner instantiation, which runs more
-    // wavefronts per SIMD.
-    const bool fits_pf = int64_t(wm_max) * wn_max <= lpb::wave_prefetch_elems() && !gather && !warm;
+    // row-gathered LPs and those of more than 64 rows take the leaner instantiation.
+    const bool fits_pf = int64_t(wm_max) * wn_max <= lpb::wave_prefetch_elems() && rb == 1 && !gather && !warm;
     auto per_cu_at = [&](bool pf, int64_t lds) {
-        return warm ? lpb::simplex_wave_warm_blocks_per_cu(rb, int(lds))
-                    : lpb::simplex_wave_blocks_per_cu(fp32, rb, pf, int(lds));
+        return warm ? lpb::simplex_wave_warm_blocks_per_cu(rb, steep, int(lds))
+                    : lpb::simplex_wave_blocks_per_cu(fp32, rb, pf, steep, int(lds));
     };
     // Budget for the common case of no surplus columns; an LP needing more is
     // deferred -- except where a tableau with a surplus column in every row

@@ -657,7 +657,7 @@ __device__ __forceinline__ int simplex(WaveLP<T, RB> &P, T eps_opt, const SolveP
     int deg_run = 0;
     Window<T, RB, NG> Q;
     Q.n = 0;
-    if (STEEP && prm.pricing == 1) {
+    if constexpr (STEEP) {
         T w = weight(P);
         for (;;) {
             const int r = step<0, true, true>(P, Q, eps_opt, prm, deg_run, enter, &w);
@@ -858,10 +858,12 @@ __host__ __device__ constexpr int64_t wave_aux_bytes(int rb, bool gather)
     return align16(4 * 64 * rb) + (gather ? align16(4 * 64 * rb) : 0);
 }
 
-// Doubles of A each lane prefetches: LPs with m * n <= 64 * NPF have their
-// whole constraint matrix loaded into registers one LP ahead.  Batches of
+// Doubles of A each lane prefetches: LPs of up to 64 rows with m * n <= 64 * NPF have
+// their whole constraint matrix loaded into registers one LP ahead.  Batches of
 // larger (or row-gathered) LPs use the instantiation without the prefetch
-// registers, which leaves room for more wavefronts per SIMD.
+// registers.  (With two rows a lane the window leaves no registers for it: FP64 spilled
+// 72, 20,000 LPs of 100 x 25 434 us with prefetch, 282 without, of 66 x 4 178 and 90;
+// FP32, which did not spill, 400 and 391, 206 and 165.)
 constexpr int NPF = 40;
 
 // An LP's geometry and input data, loaded into registers ahead of its solve.
@@ -954,10 +956,21 @@ __device__ __forceinline__ void fetch(int64_t item, Fetch<RB, PFD> &F)
 // 1e5 uniform 50 x 50 FP64 0.83 / 0.83 / 1.00 ms).
 constexpr int kGroups = 1;
 
+// Wavefronts per SIMD that the registers are allotted for.  FP64 without prefetch: two
+// hold everything in registers, three spill (20,000 LPs of 60 x 60 417 us with three, 396
+// with two, of 50 x 64 349 and 334).  The repair kernel spilled 190 registers at three
+// and 70 at two; 65 to 128 rows leave LDS for one wavefront per SIMD anyway.  FP32: five
+// (one block of rows) and four spill a few registers outside the pivots, which costs less
+// than a wavefront (screened 120 x 40 3.95 ms with five, 3.99 with four).
+template <typename T, int RB, int PFD, bool WARM>
+constexpr int kWavesPerSimd = PFD > 0 ? 2 : WARM ? 3 - RB : sizeof(T) == 8 ? 2 : 6 - RB;
+
 // STEEP: steepest-edge pricing, apart so that its code costs the default rule's no
-// registers (in one kernel 100,000 LPs of 50 x 50 FP64 took 0.85 ms, not 0.78).
-template <typename T, int RB, int PFD, bool WARM = false, bool STEEP = WARM>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(PFD > 0 ? 2 : (sizeof(T) == 4 ? (RB == 1 ? 5 : 4) - STEEP : (RB == 2 ? 2 : 3))))) void simplex_wave_kernel(SolveArgs a)
+// registers (in one kernel 100,000 LPs of 50 x 50 FP64 took 0.85 ms, not 0.78), nor the
+// window those of steepest edge, which has none (20,000 of 20 x 20 157 us with both
+// in one, 118 apart).
+template <typename T, int RB, int PFD, bool WARM = false, bool STEEP = false>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kWavesPerSimd<T, RB, PFD, WARM>))) void simplex_wave_kernel(SolveArgs a)
 {
     extern __shared__ __align__(16) char smem[];
     constexpr int NG = kGroups;
@@ -1112,8 +1125,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(PFD > 0 ? 2 
                     }
                 }
             } else {
-                // (Eight loads in flight for FP32 LPs of up to 64 rows keeps them
-                // within the registers of five wavefronts per SIMD.)
+                // (Eight loads in flight for FP32 LPs of up to 64 rows, which have the
+                // registers of five wavefronts per SIMD.)
                 constexpr int UB = (sizeof(T) == 4 && RB == 1) ? 8 : 16;
                 for (int f0 = 0; f0 < mn; f0 += 64 * UB) {
                     double av[UB];
@@ -1388,19 +1401,19 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(PFD > 0 ? 2 
 }
 
 
-template <typename T, int RB, int PFD, bool WARM = false, bool STEEP = WARM>
+template <typename T, int RB, int PFD, bool WARM = false, bool STEEP = false>
 hipError_t launch_t(const SolveArgs &a, int grid, hipStream_t s)
 {
     hipLaunchKernelGGL((simplex_wave_kernel<T, RB, PFD, WARM, STEEP>), dim3(grid), dim3(64), a.lds_bytes, s, a);
     return hipGetLastError();
 }
 
-template <typename T, int RB, int PFD, bool WARM = false>
+template <typename T, int RB, int PFD, bool WARM = false, bool STEEP = false>
 int occ_t(int lds)
 {
     int blocks = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
-            &blocks, (const void *)simplex_wave_kernel<T, RB, PFD, WARM>, 64, lds) != hipSuccess)
+            &blocks, (const void *)simplex_wave_kernel<T, RB, PFD, WARM, STEEP>, 64, lds) != hipSuccess)
         return 0;
     return blocks;
 }
@@ -1412,16 +1425,15 @@ hipError_t launch_rb(int rb, bool pf, const SolveArgs &a, int grid, hipStream_t 
         return rb == 1 ? launch_t<T, 1, 0, false, true>(a, grid, s)
              : rb == 2 ? launch_t<T, 2, 0, false, true>(a, grid, s) : hipErrorInvalidValue;
     if (rb == 1) return pf ? launch_t<T, 1, NPF>(a, grid, s) : launch_t<T, 1, 0>(a, grid, s);
-    if (rb == 2) return pf ? launch_t<T, 2, NPF>(a, grid, s) : launch_t<T, 2, 0>(a, grid, s);
-    return hipErrorInvalidValue;
+    return rb == 2 && !pf ? launch_t<T, 2, 0>(a, grid, s) : hipErrorInvalidValue;
 }
 
 template <typename T>
-int occ_rb(int rb, bool pf, int lds)
+int occ_rb(int rb, bool pf, bool steep, int lds)
 {
+    if (steep) return rb == 1 ? occ_t<T, 1, 0, false, true>(lds) : rb == 2 ? occ_t<T, 2, 0, false, true>(lds) : 0;
     if (rb == 1) return pf ? occ_t<T, 1, NPF>(lds) : occ_t<T, 1, 0>(lds);
-    if (rb == 2) return pf ? occ_t<T, 2, NPF>(lds) : occ_t<T, 2, 0>(lds);
-    return 0;
+    return rb == 2 && !pf ? occ_t<T, 2, 0>(lds) : 0;
 }
 
 }  // namespace
@@ -1440,30 +1452,30 @@ hipError_t launch_simplex_wave(bool fp32, int rb, bool pf, const SolveArgs &a, i
     return fp32 ? launch_rb<float>(rb, pf, a, grid, s) : launch_rb<double>(rb, pf, a, grid, s);
 }
 
-int simplex_wave_blocks_per_cu(bool fp32, int rb, bool pf, int lds)
+int simplex_wave_blocks_per_cu(bool fp32, int rb, bool pf, bool steep, int lds)
 {
-    return fp32 ? occ_rb<float>(rb, pf, lds) : occ_rb<double>(rb, pf, lds);
+    return fp32 ? occ_rb<float>(rb, pf, steep, lds) : occ_rb<double>(rb, pf, steep, lds);
 }
 
 hipError_t launch_simplex_wave_warm(int rb, const SolveArgs &a, int grid, hipStream_t s)
 {
     if (!a.warm_basis || (a.warm_rows && a.warm_m < 1)) return hipErrorInvalidValue;
-    if (rb == 1) return launch_t<double, 1, 0, true>(a, grid, s);
-    if (rb == 2) return launch_t<double, 2, 0, true>(a, grid, s);
+    const bool steep = a.prm.pricing == 1;
+    if (rb == 1) return steep ? launch_t<double, 1, 0, true, true>(a, grid, s) : launch_t<double, 1, 0, true>(a, grid, s);
+    if (rb == 2) return steep ? launch_t<double, 2, 0, true, true>(a, grid, s) : launch_t<double, 2, 0, true>(a, grid, s);
     return hipErrorInvalidValue;
 }
 
-int simplex_wave_warm_blocks_per_cu(int rb, int lds)
+int simplex_wave_warm_blocks_per_cu(int rb, bool steep, int lds)
 {
-    if (rb == 1) return occ_t<double, 1, 0, true>(lds);
-    if (rb == 2) return occ_t<double, 2, 0, true>(lds);
+    if (rb == 1) return steep ? occ_t<double, 1, 0, true, true>(lds) : occ_t<double, 1, 0, true>(lds);
+    if (rb == 2) return steep ? occ_t<double, 2, 0, true, true>(lds) : occ_t<double, 2, 0, true>(lds);
     return 0;
 }
 
 hipError_t simplex_wave_configure(int max_lds)
 {
     const void *fns[] = {(const void *)simplex_wave_kernel<float, 1, NPF>, (const void *)simplex_wave_kernel<double, 1, NPF>,
-                         (const void *)simplex_wave_kernel<float, 2, NPF>, (const void *)simplex_wave_kernel<double, 2, NPF>,
                          (const void *)simplex_wave_kernel<float, 1, 0>,   (const void *)simplex_wave_kernel<double, 1, 0>,
                          (const void *)simplex_wave_kernel<float, 2, 0>,   (const void *)simplex_wave_kernel<double, 2, 0>,
                          (const void *)simplex_wave_kernel<float, 1, 0, false, true>,
@@ -1471,7 +1483,9 @@ hipError_t simplex_wave_configure(int max_lds)
                          (const void *)simplex_wave_kernel<float, 2, 0, false, true>,
                          (const void *)simplex_wave_kernel<double, 2, 0, false, true>,
                          (const void *)simplex_wave_kernel<double, 1, 0, true>,
-                         (const void *)simplex_wave_kernel<double, 2, 0, true>};
+                         (const void *)simplex_wave_kernel<double, 2, 0, true>,
+                         (const void *)simplex_wave_kernel<double, 1, 0, true, true>,
+                         (const void *)simplex_wave_kernel<double, 2, 0, true, true>};
     for (const void *f : fns) {
         hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, max_lds);
         if (e != hipSuccess) return e;
