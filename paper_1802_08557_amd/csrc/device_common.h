@@ -83,34 +83,6 @@ __device__ __forceinline__ double buffer_f64(__amdgpu_buffer_rsrc_t rs, int byte
     return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(rs, byte_off, 0, 0));
 }
 
-// Lexicographic argmin over the wavefront of (k1, k2) carrying p.  Keys are
-// unique (k2 is a Bland index) or all invalid, so every lane ends with the
-// same winner.
-template <typename T>
-__device__ __forceinline__ void wave_argmin(T &k1, int &k2, int &p)
-{
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-        const T o1 = __shfl_xor(k1, off);
-        const int o2 = __shfl_xor(k2, off);
-        const int op = __shfl_xor(p, off);
-        if (o1 < k1 || (o1 == k1 && o2 < k2)) { k1 = o1; k2 = o2; p = op; }
-    }
-}
-
-// The same lexicographic argmin with DPP / permlane reductions instead of
-// shuffles through LDS: the least k1, then the least k2 among the lanes that
-// hold it, then p from the lowest lane holding both (all 64 lanes active).
-template <typename T>
-__device__ __forceinline__ void wave_argmin_dpp(T &k1, int &k2, int &p);
-
-__device__ __forceinline__ double wave_max(double v)
-{
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v = fmax(v, __shfl_xor(v, off));
-    return v;
-}
-
 // ---- DPP / permlane reductions (all 64 lanes must be active) ---------------
 // Lane patterns (checked on gfx950): quad_perm [1,0,3,2] and [2,3,0,1] swap
 // neighbours at distance 1 and 2, row_half_mirror reverses each group of 8,
@@ -286,19 +258,6 @@ template <typename T>
 __device__ __forceinline__ int mfma_row(int q, int v)
 {
     return sizeof(T) == 8 ? q + 4 * v : 4 * q + v;
-}
-
-template <typename T>
-__device__ __forceinline__ void wave_argmin_dpp(T &k1, int &k2, int &p)
-{
-    const T best = wave_min_f(k1);
-    const bool tie = k1 == best;
-    const int kmin = wave_min_i(tie ? k2 : kBig);
-    const uint64_t win = __ballot(tie && k2 == kmin);
-    const int src = win ? __builtin_ctzll(win) : 0;
-    k1 = best;
-    k2 = kmin;
-    p = lane_get(p, src);
 }
 
 // Worker b of `workers` in a launch's work queue: its first two items are b and

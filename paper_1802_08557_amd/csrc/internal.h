@@ -180,7 +180,6 @@ struct MlpAdam {
 hipError_t launch_adamw(float *w, const float *g, float *m, float *v, uint16_t *w16, int64_t count,
                         const MlpAdam &h, const int64_t (&decay)[6], hipStream_t s);
 hipError_t launch_cast_params(const float *w, uint16_t *w16, int64_t count, hipStream_t s);
-hipError_t launch_topk(const float *S, int64_t B, int O, int k, int32_t *out, hipStream_t s);
 // Fused inference (all layers and the top-k, tiles of 64 directions):
 // scores [B][120] and/or topk [B][k] (either may be NULL).
 hipError_t launch_mlp_infer(const float *dirs, int64_t B, const uint16_t *w16, const float *w32, float *scores,
@@ -217,7 +216,6 @@ hipError_t noalloc_scratch_address(void **ptr);
 
 // Launchers (simplex_kernels.hip).  Return the hipError_t of the launch.
 hipError_t launch_zero_i32(int32_t *p, int count, hipStream_t s);
-hipError_t launch_set_i32(int32_t *p, int32_t value, hipStream_t s);
 hipError_t launch_simplex(bool fp32, int nt, const SolveArgs &a, int grid, hipStream_t s);
 // Workgroups of the simplex kernel that fit one CU with this LDS (occupancy query).
 int simplex_blocks_per_cu(bool fp32, int nt, int lds_bytes);

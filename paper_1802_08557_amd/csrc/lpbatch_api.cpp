@@ -51,7 +51,6 @@ struct Plan {
     int32_t m0, n0, m_max, n_max;
     int64_t mn_max;
     bool fp32;
-    int64_t ts;
 };
 
 // Counters of one solve pass (wavefront kernel + workgroup kernel).
@@ -344,7 +343,6 @@ int queue_pass(lp_ctx *ctx, const Plan &P, lpb::SolveArgs a, const lp_options &o
 // the workgroup's device-memory slot), so the launch ends on small LPs instead
 // of idling between per-size launches.  Workgroup size and placement come from
 // the context's tuning table (filled by the autotuner) or a heuristic.
-constexpr int kBins = 4;
 // Tuning-table bin of the single workgroup-kernel launch of a batch of mixed sizes.
 constexpr int kMixedBin = 4;
 
@@ -789,7 +787,6 @@ int lp_batch_solve_ex(lp_ctx *ctx, int64_t num_lps, const double *A, const doubl
         if (sa > (int64_t(1) << 60)) return fail(LP_ERR_ARG, "batch size overflows");
     }
     P.fp32 = opts.precision == LP_PREC_FP32_CERT64;
-    P.ts = P.fp32 ? 4 : 8;
     // Shared constraints, optionally screened: the first pass solves every LP
     // on its subset_m rows only, and the certificate judges the basis on all rows.
     const bool shared = opts.shared != 0;
@@ -1107,7 +1104,6 @@ int lp_batch_solve_ex(lp_ctx *ctx, int64_t num_lps, const double *A, const doubl
         // FP64 re-solve of every LP the certificate rejected, on all of its rows.
         Plan P64 = P_full;
         P64.fp32 = false;
-        P64.ts = 8;
         lpb::SolveArgs a64 = a;
         a64.prm = fill_params(opts, false);
         a64.basis_out = nullptr;
@@ -1185,7 +1181,6 @@ int lp_batch_solve_noalloc(lp_ctx *ctx, int64_t num_lps, const double *A, const 
     P.n0 = P.n_max = n;
     P.mn_max = int64_t(m) * n;
     P.fp32 = false;
-    P.ts = 8;
     lp_options opts;
     lp_options_init(&opts);
     lpb::SolveArgs a;

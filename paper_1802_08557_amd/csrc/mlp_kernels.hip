@@ -9,8 +9,7 @@
 // batch -- dW, bias gradients, mean loss (mlp_sums_kernel).  Every reduction
 // runs in a fixed order, so a training step is deterministic.
 //
-// The remaining kernels: AdamW on the FP32 master weights with a fresh BF16
-// copy, and a standalone per-direction top-k.
+// The remaining kernel: AdamW on the FP32 master weights with a fresh BF16 copy.
 #include <math.h>
 #include <stdint.h>
 
@@ -56,28 +55,6 @@ __global__ void cast_params_kernel(const float *w, uint16_t *w16, int64_t count)
 {
     const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
     if (i < count) w16[i] = to_bf16(w[i]);
-}
-
-// Top-k of each row of S [B][O] (O <= 128): one wavefront per row; the entry
-// of rank r (number of entries that are larger, or equal with a lower index)
-// goes to out[b][r] when r < k.
-__global__ __launch_bounds__(64) void topk_kernel(const float *S, int64_t B, int O, int k, int32_t *out)
-{
-    const int64_t b = blockIdx.x;
-    if (b >= B) return;
-    __shared__ float s[128];
-    const int lane = threadIdx.x;
-    for (int j = lane; j < O; j += 64) s[j] = S[b * O + j];
-    __syncthreads();
-    for (int j = lane; j < O; j += 64) {
-        const float v = s[j];
-        int r = 0;
-        for (int t = 0; t < O; ++t) {
-            const float u = s[t];
-            r += (u > v || (u == v && t < j)) ? 1 : 0;
-        }
-        if (r < k) out[b * k + r] = j;
-    }
 }
 
 
@@ -657,13 +634,6 @@ hipError_t mlp_configure()
 {
     return hipFuncSetAttribute((const void *)mlp_infer_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
                                int(infer_lds_bytes()));
-}
-
-hipError_t launch_topk(const float *S, int64_t B, int O, int k, int32_t *out, hipStream_t s)
-{
-    if (B <= 0) return hipSuccess;
-    hipLaunchKernelGGL(topk_kernel, dim3(unsigned(B)), dim3(64), 0, s, S, B, O, k, out);
-    return hipGetLastError();
 }
 
 }  // namespace lpb
