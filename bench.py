@@ -58,8 +58,10 @@ def surplus_columns(batch):
 
 
 def algorithmic_bytes(batch, stats, tsize):
-    """Per-launch algorithmic bytes, split by where each LP's tableau lived
-    (stats column 6).  N = n + surplus columns non-basic columns.
+    """Bytes of one sweep of the tableau per pivot, split by where each LP's
+    tableau lived (stats column 6): what the textbook method moves, not what the
+    kernels do, which sweep once per window of up to 8 (wavefront kernel) or 32
+    (workgroup kernel) pivots.  N = n + surplus columns non-basic columns.
       * one wavefront per LP (placement 1): the m x N constraint block lives in
         LDS (the objective row and the right-hand sides stay in registers):
         s*m*N written by the build, then read and written once per pivot;
@@ -81,43 +83,47 @@ def algorithmic_bytes(batch, stats, tsize):
 
 
 def roofline(per_kernel, dom, lds_bytes, hbm_bytes, peaks, workload_name):
-    """Roofline of the dominant solve kernel: the busier memory tier for the
-    algorithmic bytes, T = max(LDS bytes / LDS peak, HBM bytes / HBM peak),
-    against the kernel's measured time per solve.
+    """Roofline of the dominant solve kernel: the busier memory tier,
+    T = max(LDS bytes / LDS peak, HBM bytes / HBM peak), against the kernel's
+    measured time per solve.
 
-    The algorithmic LDS bytes of a pivot are one read and one write of the
-    tableau (plus one write to build it), so the LDS peak is the rate the
-    device itself reaches on that mix: 16-byte reads each followed by a
-    16-byte write (lp_measure_peaks' read+write stream).  Reads alone run at
-    about 2.5x the rate of writes alone on gfx950, so the read-only rate
-    overstates what a half-write stream can reach; frac is also given
-    against it and against the nominal 128 B/clk/CU.  The HBM peak is the
-    published 8 TB/s (a device copy reaches hbm_copy).  traffic: measured
-    HBM bytes per launch (FETCH_SIZE + WRITE_SIZE, calibrated), null when
-    the kernel sources changed since the counters were taken; lds_traffic:
-    the same from the LDS bandwidth counters."""
+    bytes_basis says which bytes.  "counters": measured HBM (FETCH_SIZE +
+    WRITE_SIZE) and LDS (LDS bandwidth counters) bytes per launch, calibrated;
+    also given as traffic and lds_traffic.  Without them (the kernel sources
+    changed since the counters were taken, or none exist for the workload)
+    "one sweep per pivot": the bytes of algorithmic_bytes (lds_bytes, hbm_bytes),
+    always given as *_bytes_alg.  The kernels move fewer, so on that basis
+    achieved is a rate to compare with one-sweep-per-pivot methods and frac may
+    exceed 1.
+
+    The LDS peak is the rate the device itself reaches on the sweep's mix:
+    16-byte reads each followed by a 16-byte write (lp_measure_peaks'
+    read+write stream).  Reads alone run at about 2.5x the rate of writes alone
+    on gfx950; lds_frac_vs_read_peak and lds_frac_vs_nominal are against the
+    read-only rate and the nominal 128 B/clk/CU.  The HBM peak is the published
+    8 TB/s (a device copy reaches hbm_copy)."""
     lds_mix = peaks.get("lds_read_write", 0.0)
     lds_peak = lds_mix if lds_mix > 0 else LDS_NOMINAL
     lds_read = peaks.get("lds_read", 0.0)
     dom_s = per_kernel[dom] * 1e-3
-    if lds_bytes / lds_peak >= hbm_bytes / PEAK_HBM:
-        roof = dict(bound="lds", achieved=lds_bytes / dom_s / 1e9, peak=lds_peak / 1e9, unit="GB/s",
-                    frac=lds_bytes / dom_s / lds_peak)
-    else:
-        roof = dict(bound="hbm", achieved=hbm_bytes / dom_s / 1e9, peak=PEAK_HBM / 1e9, unit="GB/s",
-                    frac=hbm_bytes / dom_s / PEAK_HBM)
     tr = measured_traffic(dom, workload_name)
-    roof["traffic"] = tr["hbm"] if tr else None
-    roof.update(kernel=dom, kernel_ms=per_kernel[dom], lds_bytes_alg=lds_bytes, hbm_bytes_alg=hbm_bytes,
+    measured = bool(tr and tr["hbm"] is not None and tr["lds"] is not None)
+    lds, hbm = (tr["lds"], tr["hbm"]) if measured else (lds_bytes, hbm_bytes)
+    if lds / lds_peak >= hbm / PEAK_HBM:
+        roof = dict(bound="lds", achieved=lds / dom_s / 1e9, peak=lds_peak / 1e9, unit="GB/s",
+                    frac=lds / dom_s / lds_peak)
+    else:
+        roof = dict(bound="hbm", achieved=hbm / dom_s / 1e9, peak=PEAK_HBM / 1e9, unit="GB/s",
+                    frac=hbm / dom_s / PEAK_HBM)
+    roof.update(bytes_basis="counters" if measured else "one sweep per pivot",
+                traffic=tr["hbm"] if tr else None, lds_traffic=tr["lds"] if tr else None,
+                kernel=dom, kernel_ms=per_kernel[dom], lds_bytes_alg=lds_bytes, hbm_bytes_alg=hbm_bytes,
                 lds_peak_basis="measured 16-byte read+write" if lds_mix > 0 else "nominal 128 B/clk/CU",
-                lds_frac=lds_bytes / dom_s / lds_peak,
-                lds_frac_vs_read_peak=lds_bytes / dom_s / lds_read if lds_read > 0 else None,
-                lds_frac_vs_nominal=lds_bytes / dom_s / LDS_NOMINAL,
-                hbm_frac=hbm_bytes / dom_s / PEAK_HBM,
-                lds_traffic=tr["lds"] if tr else None)
+                lds_frac=lds / dom_s / lds_peak,
+                lds_frac_vs_read_peak=lds / dom_s / lds_read if lds_read > 0 else None,
+                lds_frac_vs_nominal=lds / dom_s / LDS_NOMINAL,
+                hbm_frac=hbm / dom_s / PEAK_HBM)
     if tr and tr["hbm"]:
-        # Measured bytes over the same time: below the algorithmic figure when
-        # pivots share sweeps (one pass of the tableau for two or three pivots).
         roof.update(traffic_gb_per_s=tr["hbm"] / dom_s / 1e9, traffic_frac=tr["hbm"] / dom_s / PEAK_HBM)
     return roof
 
@@ -165,7 +171,8 @@ KERNEL_SOURCES = ("paper_1802_08557_amd/csrc/wave_kernels.hip",
                   "paper_1802_08557_amd/csrc/certify_kernels.hip",
                   "paper_1802_08557_amd/csrc/certify_dense.hip",
                   "paper_1802_08557_amd/csrc/device_common.h",
-                  "paper_1802_08557_amd/csrc/internal.h")
+                  "paper_1802_08557_amd/csrc/internal.h",
+                  "paper_1802_08557_amd/csrc/lpbatch_api.cpp")  # threads, placement and LDS (window lengths)
 
 
 def kernel_source_hash():

@@ -74,10 +74,6 @@ bool wave_fit(const lp_ctx *ctx, int64_t mk, int64_t nk, bool fp32, bool gather)
                ctx->max_lds;
 }
 
-// Queues one solve pass.  The LPs are either the n_wave + n_block LPs given by
-// host-built id lists already on the device (wave_ids, and block ids at the
-// front of defer_ids), or -- when list_count is set -- the device list
-// list_ids[0 .. *list_count), all offered to the wavefront kernel first.
 // LDS a workgroup-kernel tableau may take.  By default at most a third of
 // the CU's LDS, so that three or more workgroups share a CU and hide each
 // other's latency; a larger tableau streams from its device-memory slot

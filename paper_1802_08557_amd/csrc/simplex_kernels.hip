@@ -194,10 +194,8 @@ __device__ __forceinline__ int block_pick(LP<T, NT> &P, const Best<MAX, T> &c, T
 // and right-hand sides (kept current in LDS), one column and one row.  K is
 // what the LP's LDS leaves (LdsLayout), at most kMaxWindow.  Measured against
 // three pivots per sweep on the vector units: 1,000 LPs of 500 x 500 FP64 23.5 ->
-// 7.3 ms (sixteen pivots per sweep; a sweep still takes half of an LP's time,
-// at the HBM copy rate), 10,000 uneven LPs of 10..300 FP64 140 -> 60 ms and FP32
-// 86 -> 40 ms (42 % sweeps, 37 % the device-memory latency of the one column and
-// row, 14 % the reductions), 2,000 LPs of 117 x 150 FP32 1.14 -> 0.63 ms.
+// 7.3 ms (sixteen pivots per sweep), 10,000 uneven LPs of 10..300 FP64 140 -> 59 ms
+// and FP32 86 -> 41 ms, 2,000 LPs of 117 x 150 FP32 1.14 -> 0.55 ms.
 //
 // A tableau in LDS is swept at LDS speed, so sixteen pivots a window do: each pivot
 // reads half as many vectors of it as of thirty-two (1,000 LPs FP64, 32 / 16 pivots:
@@ -938,7 +936,7 @@ __device__ __forceinline__ void reject_lp(const LP<T, NT> &P, const SolveArgs &a
 }
 
 // STEEP: steepest-edge pricing, a kernel of its own so that its code costs the
-// default rule's no registers (in one kernel 500 x 500 FP64 took 8.2 ms, not 7.3).
+// default rule's no registers (in one kernel 500 x 500 FP64 took 8.2 ms, apart 7.3).
 template <typename T, int NT, bool STEEP>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void simplex_kernel(SolveArgs a)
 {

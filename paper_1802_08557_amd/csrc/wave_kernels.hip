@@ -18,10 +18,12 @@
 // before and after the ratio test, three LDS round trips) at the occupancy the
 // tableaux leave -- two wavefronts per SIMD for 50 x 50 FP64, one for 120 x 40 --
 // and, for LPs of few pivots, the read of A from HBM (a 50 x 50 batch cut off
-// after one pivot runs at 5.2 TB/s).  Measured against one or two pivots per
-// sweep of a column-major tableau on the vector units (same work queue): 1e5
-// uniform 50 x 50 FP64 1137 -> 830 us, its FP32 solve 940 -> 690 us, 1e5 support
-// LPs of 120 x 40 FP64 12.80 -> 7.82 ms, screened FP32 2.13 -> 1.63 ms.
+// after one pivot takes 0.45 of the 0.82 ms, 4.6 TB/s).  Measured against one or
+// two pivots per sweep of a column-major tableau on the vector units (same work
+// queue): 1e5 uniform 50 x 50 FP64 1137 -> 840 us, its FP32 solve 940 -> 710 us, 1e5
+// support LPs of 120 x 40 FP64 12.8 -> 8.1 ms, screened FP32 2.13 -> 1.63 ms.  (The
+// code that solves LPs again which overflow, see overflowed, takes 3, 1, 2 and 0 %
+// of these.)
 // The arithmetic of every element (fma(-pcol_i, prow_j, t_ij), prow_j =
 // t_lj / PE, Phase I and Phase II objective rows summed in row order) is the
 // same as in the workgroup kernel, so both give bitwise-identical results.
@@ -958,15 +960,16 @@ constexpr int kGroups = 1;
 
 // Wavefronts per SIMD that the registers are allotted for.  FP64 without prefetch: two
 // hold everything in registers, three spill (20,000 LPs of 60 x 60 417 us with three, 396
-// with two, of 50 x 64 349 and 334).  The repair kernel spilled 190 registers at three
-// and 70 at two; 65 to 128 rows leave LDS for one wavefront per SIMD anyway.  FP32: five
+// with two, of 50 x 64 349 and 334).  The repair kernel spills 190 registers at three and
+// none at two, with two blocks of rows 70 at two and none at one, and 65 to 128 rows
+// leave LDS for one wavefront per SIMD anyway.  FP32: five
 // (one block of rows) and four spill a few registers outside the pivots, which costs less
 // than a wavefront (screened 120 x 40 3.95 ms with five, 3.99 with four).
 template <typename T, int RB, int PFD, bool WARM>
 constexpr int kWavesPerSimd = PFD > 0 ? 2 : WARM ? 3 - RB : sizeof(T) == 8 ? 2 : 6 - RB;
 
 // STEEP: steepest-edge pricing, apart so that its code costs the default rule's no
-// registers (in one kernel 100,000 LPs of 50 x 50 FP64 took 0.85 ms, not 0.78), nor the
+// registers (in one kernel 100,000 LPs of 50 x 50 FP64 took 9 % longer), nor the
 // window those of steepest edge, which has none (20,000 of 20 x 20 157 us with both
 // in one, 118 apart).
 template <typename T, int RB, int PFD, bool WARM = false, bool STEEP = false>
